@@ -23,13 +23,15 @@
 // Rows y = 2p and 2p+1 share one complex line (real and imaginary part) of stride
 // S = 2 (K2/2 + 1).  A complex FFT of the line along z gives the spectra of both rows,
 // separated by X_2p[k] = (Z[k] + conj Z[K2-k]) / 2 and X_2p+1[k] = (Z[k] - conj Z[K2-k]) / 2i;
-// the inverse runs the same steps backwards.  The one-dimensional transforms are self-sorting
-// (Stockham) mixed-radix FFTs (radices 2 to 7) done in place through registers, with the
-// roots of unity in LDS (computed in FP64).
+// the inverse runs the same steps backwards.  The one-dimensional transforms (plane_fft.h) take
+// their first points straight from global memory (or from the spread's sums) and cross LDS once
+// where the length is a product of two supported radices; the roots of unity are in LDS (computed
+// in FP64).
 #include <algorithm>
 #include <type_traits>
 
 #include "common.h"
+#include "plane_fft.h"
 #include "reduce.h"
 #include "spline.h"
 
@@ -43,238 +45,20 @@ constexpr int kPlThreads = 512;         // threads per workgroup of the row-chun
 constexpr int kPlThreadsLarge = 256;    // the same on large grids, in smaller row chunks
 constexpr int kPlLargeWG = 1024;        // row-chunk workgroups of 512 threads above which a grid is large
 constexpr int kPlTargetWGLarge = 3456;  // row-chunk workgroups the chunking aims at on a large grid
-constexpr int kPlColMaxKc = 16;         // columns per column chunk at most on a large grid
-constexpr int kPlColThreads = 256;      // threads per workgroup of the column passes (y and x lines)
-constexpr int kPlMaxB = 1;              // butterflies per thread in one FFT round (row passes)
-constexpr int kPlColMaxB = 2;           // the same in the column passes: a stage's lines in one round
-constexpr int kPlLoads = 8;             // global loads a thread keeps in flight when filling LDS
-constexpr int kPlConvTotal = 8192;      // fixed-point values a row-chunk workgroup converts at most
-constexpr int kPlSplit = 4;             // split / combine items per thread in one round
+constexpr int kPlColThreads = 512;      // threads per workgroup of the column passes at most
 constexpr size_t kPlLdsMax = 64 * 1024; // LDS of one workgroup
 constexpr int kPlTargetWG = 432;        // workgroups per row-chunk pass the chunking aims at
-constexpr int kPlColTargetWG = 432;     // workgroups per column pass
 // Wave priority of the transform and interpolation passes: they run beside the real-space tiles
 // (second stream) and are latency bound, so their waves issue first where both share a SIMD;
 // the tiles fill the remaining issue slots (solve 1.44 -> 1.40 ms on water_96000).
 constexpr int kPlPassPrio = 3;
-
-// Factorisation of a transform length into radices 2..7 (host-computed).
-struct PlaneDim {
-    int n, nr;
-    int rad[12];
-};
-
-// Element (line l, point n) of a set of lines: l ls + (n div 2) s2 + (n mod 2) h.
-struct LineMap {
-    int ls, s2, h;
-    __device__ __forceinline__ int operator()(int l, int n) const { return l * ls + (n >> 1) * s2 + (n & 1) * h; }
-};
-
-// Quotient of non-negative integers a < 2^22 by b >= 1 through FP32: floor((a + 1/2) / b) with
-// a correctly rounded reciprocal is off by at most (a + 1/2) / b * 2^-23 < 1 / (2b), less than the
-// distance of (a + 1/2) / b to the nearest integer, so the truncation is exact.  Used for the
-// line / point split of thread indices (an integer division is a long instruction sequence).
-struct SmallDiv {
-    int b;
-    float inv;
-    __device__ __forceinline__ explicit SmallDiv(int bb) : b(bb), inv(1.0f / (float)bb) {}
-    __device__ __forceinline__ int quot(int a) const { return (int)(((float)a + 0.5f) * inv); }
-};
-
-template <typename C> __device__ __forceinline__ C cmul(C a, C b)
-{
-    return C{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
-}
-template <typename C> __device__ __forceinline__ C cadd(C a, C b) { return C{a.x + b.x, a.y + b.y}; }
-template <typename C> __device__ __forceinline__ C csub(C a, C b) { return C{a.x - b.x, a.y - b.y}; }
-// multiplication by SIGN i
-template <int SIGN, typename C> __device__ __forceinline__ C mul_i(C a)
-{
-    return SIGN < 0 ? C{a.y, -a.x} : C{-a.y, a.x};
-}
-
-// three-point DFT with omega = exp(SIGN 2 pi i / 3)
-template <int SIGN, typename C> __device__ __forceinline__ void dft3(C& a, C& b, C& c)
-{
-    using R = decltype(a.x);
-    const R h = (R)0.86602540378443864676;
-    const C t = cadd(b, c), s = csub(b, c);
-    const C m = C{a.x - (R)0.5 * t.x, a.y - (R)0.5 * t.y};
-    const C rs = mul_i<SIGN>(C{h * s.x, h * s.y});
-    a = cadd(a, t);
-    b = cadd(m, rs);
-    c = csub(m, rs);
-}
-
-// In-place RAD-point DFT: v[q] <- sum_r v[r] exp(SIGN 2 pi i r q / RAD).
-template <int RAD, int SIGN, typename C> __device__ __forceinline__ void dft(C (&v)[RAD])
-{
-    using R = decltype(v[0].x);
-    if constexpr (RAD == 2) {
-        const C a = v[0], b = v[1];
-        v[0] = cadd(a, b);
-        v[1] = csub(a, b);
-    } else if constexpr (RAD == 3) {
-        dft3<SIGN>(v[0], v[1], v[2]);
-    } else if constexpr (RAD == 4) {
-        const C a = cadd(v[0], v[2]), b = csub(v[0], v[2]), c = cadd(v[1], v[3]), d = mul_i<SIGN>(csub(v[1], v[3]));
-        v[0] = cadd(a, c);
-        v[2] = csub(a, c);
-        v[1] = cadd(b, d);
-        v[3] = csub(b, d);
-    } else if constexpr (RAD == 6) {
-        // pairs (r, r+3) first: even outputs are the 3-point DFT of the sums, odd outputs that of
-        // the differences times exp(SIGN 2 pi i r / 6)
-        const R c1 = (R)0.5, s1 = (R)SIGN * (R)0.86602540378443864676;
-        C a0 = cadd(v[0], v[3]), a1 = cadd(v[1], v[4]), a2 = cadd(v[2], v[5]);
-        C b0 = csub(v[0], v[3]), b1 = csub(v[1], v[4]), b2 = csub(v[2], v[5]);
-        b1 = cmul(b1, C{c1, s1});
-        b2 = cmul(b2, C{-c1, s1});
-        dft3<SIGN>(a0, a1, a2);
-        dft3<SIGN>(b0, b1, b2);
-        v[0] = a0;
-        v[2] = a1;
-        v[4] = a2;
-        v[1] = b0;
-        v[3] = b1;
-        v[5] = b2;
-    } else {
-        static_assert(RAD == 5 || RAD == 7, "radix");
-        // cos and sin of 2 pi m / RAD, m < RAD
-        constexpr double c5[5] = {1.0, 0.30901699437494745, -0.8090169943749473, -0.8090169943749476,
-                                  0.30901699437494723};
-        constexpr double s5[5] = {0.0, 0.9510565162951535, 0.5877852522924732, -0.587785252292473,
-                                  -0.9510565162951536};
-        constexpr double c7[7] = {1.0, 0.6234898018587336, -0.22252093395631434, -0.900968867902419,
-                                  -0.9009688679024191, -0.2225209339563146, 0.6234898018587334};
-        constexpr double s7[7] = {0.0, 0.7818314824680298, 0.9749279121818236, 0.43388373911755823,
-                                  -0.433883739117558, -0.9749279121818236, -0.7818314824680299};
-        C out[RAD];
-#pragma unroll
-        for (int q = 0; q < RAD; ++q) {
-            C acc = v[0];
-#pragma unroll
-            for (int r = 1; r < RAD; ++r) {
-                const int m = (r * q) % RAD;
-                const R cr = (R)(RAD == 5 ? c5[m] : c7[m]);
-                const R sr = (R)SIGN * (R)(RAD == 5 ? s5[m] : s7[m]);
-                acc = cadd(acc, cmul(v[r], C{cr, sr}));
-            }
-            out[q] = acc;
-        }
-#pragma unroll
-        for (int q = 0; q < RAD; ++q)
-            v[q] = out[q];
-    }
-}
-
-// One Stockham stage of radix RAD on nl lines of length N held in buf (map am), in place:
-// butterfly j of a line reads points j + r N/RAD, multiplies point r by w^(r (j mod Ns) N/(Ns RAD))
-// (w = exp(SIGN 2 pi i / N), tw[m] = exp(-2 pi i m / N)), applies the RAD-point DFT and writes
-// output q to (j div Ns) Ns RAD + (j mod Ns) + q Ns.  Whole lines are processed per round, so
-// each round reads all its points into registers before the barrier and writes after it.
-template <int RAD, int SIGN, int NT, int MB, typename C>
-__device__ __forceinline__ void fft_stage(C* buf, int nl, int N, int Ns, const C* tw, LineMap am)
-{
-    const int nb = N / RAD;
-    const int tstep = N / (Ns * RAD);
-    const int lpr = max(1, NT * MB / nb);
-    const SmallDiv dnb(nb), dns(Ns);
-    // an opaque copy of the thread index: keeps the compiler from hoisting every stage's index
-    // arithmetic out of the stage loop (which would hold all of it in registers at once)
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    for (int l0 = 0; l0 < nl; l0 += lpr) {
-        const int cnt = min(lpr, nl - l0) * nb;
-        C v[MB][RAD];
-        int dst[MB];
-#pragma unroll
-        for (int m = 0; m < MB; ++m) {
-            const int it = tid + m * NT;
-            dst[m] = -1;
-            if (it < cnt) {
-                const int lq = dnb.quot(it), l = l0 + lq, j = it - lq * nb;
-                const int k = j - dns.quot(j) * Ns;
-#pragma unroll
-                for (int r = 0; r < RAD; ++r) {
-                    C x = buf[am(l, j + r * nb)];
-                    if (r > 0 && k > 0) {
-                        C w = tw[r * k * tstep];
-                        if (SIGN > 0)
-                            w.y = -w.y;
-                        x = cmul(x, w);
-                    }
-                    v[m][r] = x;
-                }
-                dft<RAD, SIGN>(v[m]);
-                dst[m] = am(l, (j - k) * RAD + k);   // (j div Ns) Ns RAD + k, step Ns per output
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int m = 0; m < MB; ++m) {
-            if (dst[m] >= 0) {
-                const int it = tid + m * NT;
-                const int lq = dnb.quot(it), l = l0 + lq, j = it - lq * nb, k = j - dns.quot(j) * Ns;
-                const int o = (j - k) * RAD + k;
-#pragma unroll
-                for (int q = 0; q < RAD; ++q)
-                    buf[am(l, o + q * Ns)] = v[m][q];
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// FFT (SIGN -1 forward, +1 unnormalised inverse) of nl lines of length d.n, up to MB
-// butterflies per thread in one round.  All threads of the workgroup call it after a barrier;
-// it ends with one.
-template <int SIGN, int NT = kPlThreads, int MB = kPlMaxB, typename C>
-__device__ __forceinline__ void fft_lines(C* buf, int nl, const PlaneDim& d, const C* tw, LineMap am)
-{
-    int Ns = 1;
-    for (int s = 0; s < d.nr; ++s) {
-        switch (d.rad[s]) {
-        case 2: fft_stage<2, SIGN, NT, MB>(buf, nl, d.n, Ns, tw, am); break;
-        case 3: fft_stage<3, SIGN, NT, MB>(buf, nl, d.n, Ns, tw, am); break;
-        case 4: fft_stage<4, SIGN, NT, MB>(buf, nl, d.n, Ns, tw, am); break;
-        case 5: fft_stage<5, SIGN, NT, MB>(buf, nl, d.n, Ns, tw, am); break;
-        case 6: fft_stage<6, SIGN, NT, MB>(buf, nl, d.n, Ns, tw, am); break;
-        default: fft_stage<7, SIGN, NT, MB>(buf, nl, d.n, Ns, tw, am); break;
-        }
-        Ns *= d.rad[s];
-    }
-}
-
-// LDS fill: element i of n goes from src[sidx(i)] to dst[didx(i)].  Each thread issues
-// kPlLoads global loads before it stores any of them, so that many loads are in flight per
-// wave instead of one round trip per element.
-template <int NT, typename T, typename SI, typename DI>
-__device__ __forceinline__ void fill_lds(int n, const T* __restrict__ src, SI sidx, T* dst, DI didx)
-{
-    for (int i0 = threadIdx.x; i0 < n; i0 += kPlLoads * NT) {
-        T v[kPlLoads];
-#pragma unroll
-        for (int u = 0; u < kPlLoads; ++u) {
-            const int i = i0 + u * NT;
-            if (i < n)
-                v[u] = src[sidx(i)];
-        }
-#pragma unroll
-        for (int u = 0; u < kPlLoads; ++u) {
-            const int i = i0 + u * NT;
-            if (i < n)
-                dst[didx(i)] = v[u];
-        }
-    }
-}
-
 
 // Geometry and chunking shared by the passes.  Rows y = 2p and 2p + 1 form row pair p; the
 // spread and the interpolation work on chunks of Pc consecutive pairs, the y and x transforms
 // on chunks of kc consecutive kz columns.
 struct PlaneGeom {
     int nt;       // threads per workgroup of the row-chunk passes
+    int nty, ntx; // threads per workgroup of the y and the x pass
     int npad;     // slots (the plane shares are [5][npad])
     int K0, K1, K2;
     int kh;       // K2 / 2 + 1
@@ -282,7 +66,7 @@ struct PlaneGeom {
     int S;        // line stride of a pair (complex values): 2 kh
     int P;        // row pairs: ceil(K1 / 2)
     int Pc, nyc;  // pairs per row chunk, row chunks
-    int kc, nkc;  // columns per column chunk, column chunks
+    int kc, kcs, nkc;  // columns per column chunk (a power of two), its exponent, column chunks
     int kl;       // LDS line stride of a column chunk (kc made odd: whole-line strides put every
                   // point of a transform stage in one LDS bank)
     double klx, kly, klz;
@@ -349,6 +133,28 @@ __device__ __forceinline__ void entry_splines(const typename PlT<R>::R4& w, int 
         zz += zz < 0 ? K2 : 0;
         zi[tz] = 2 * zz;
     }
+}
+
+// Last stage of the z transform of nl complex lines in LDS, in place (a butterfly's outputs take
+// the places of its points).
+template <int SIGN, typename C>
+__device__ __forceinline__ void last_stage_rows(C* pl, int nl, int rad, const PlaneGeom& g, const C* tw)
+{
+    with_radix(rad, [&](auto rc_) {
+        constexpr int RAD = decltype(rc_)::value;
+        const int nb = g.K2 / RAD;
+        const SmallDiv dnb(nb);
+        for (int i0 = threadIdx.x; i0 < nl * nb; i0 += blockDim.x) {
+            const int i = opaque(i0), lq = dnb.quot(i), j = i - lq * nb;
+            C* line = pl + lq * g.S + j;
+            C v[RAD];
+            rooted_points<RAD, SIGN>(v, tw, j, [&](int r) { return line[r * nb]; });
+            dft<RAD, SIGN>(v);
+#pragma unroll
+            for (int q = 0; q < RAD; ++q)
+                line[q * nb] = v[q];
+        }
+    });
 }
 
 // Pass 1 (spread, z transform): workgroup (row chunk c, plane x).  The atoms whose support
@@ -500,68 +306,116 @@ __global__ __launch_bounds__(NT) void k_pme_spread_z(PlaneGeom g, PlaneDim dz,
         }
     }
     __syncthreads();
+    // z transform of the row pairs: the first stage reads the sums (fixed point or FP64), the
+    // complex lines replace them
     C* pl = reinterpret_cast<C*>(pl_smem);
-    if (FIX) {
-        // fixed point -> FP32 in place (value k keeps its index)
-        float f[kPlConvTotal / NT];
+    with_radix(dz.rad[0], [&](auto rc_) {
+        constexpr int RAD = decltype(rc_)::value;
+        const int nb = g.K2 / RAD;
+        const SmallDiv dnb(nb);
+        const int it = opaque(tid), lq = dnb.quot(it), j = it - lq * nb;
+        const bool act = it < rc.np * nb;   // the workgroup holds every butterfly of the stage
+        C v[RAD];
+        if (act) {
+            const double2* a = reinterpret_cast<const double2*>(acc) + lq * g.S + j;
 #pragma unroll
-        for (int m = 0; m < kPlConvTotal / NT; ++m) {
-            const int i = tid + m * NT;
-            f[m] = i < n2 ? (float)fixq_value(reinterpret_cast<const unsigned long long*>(acc)[i]) : 0.0f;
+            for (int r = 0; r < RAD; ++r) {
+                const double2 u = a[r * nb];
+                if constexpr (FIX)
+                    v[r] = C{(float)fixq_value((unsigned long long)__double_as_longlong(u.x)),
+                             (float)fixq_value((unsigned long long)__double_as_longlong(u.y))};
+                else
+                    v[r] = C{(R)u.x, (R)u.y};
+            }
+            dft<RAD, -1>(v);
         }
         __syncthreads();
-        float* fp = reinterpret_cast<float*>(pl_smem);
+        if (act) {
 #pragma unroll
-        for (int m = 0; m < kPlConvTotal / NT; ++m) {
-            const int i = tid + m * NT;
-            if (i < n2)
-                fp[i] = f[m];
+            for (int q = 0; q < RAD; ++q)
+                pl[lq * g.S + j * RAD + q] = v[q];
         }
-        __syncthreads();
-    }
-    fft_lines<-1, NT>(pl, rc.np, dz, tw_z, LineMap{g.S, 2, 1});
-    // separate the two rows of every pair into half spectra at [0, kh) and [kh, 2 kh)
-    {
-        const int lpr = max(1, NT * kPlSplit / g.kh);
-        const SmallDiv dkh(g.kh);
-        for (int p0 = 0; p0 < rc.np; p0 += lpr) {
-            const int cnt = min(lpr, rc.np - p0) * g.kh;
-            C a[kPlSplit], b[kPlSplit];
-#pragma unroll
-            for (int m = 0; m < kPlSplit; ++m) {
-                const int it = tid + m * NT;
-                if (it < cnt) {
-                    const int pq = dkh.quot(it), p = p0 + pq, k = it - pq * g.kh;
-                    const C z = pl[p * g.S + k];
-                    const C zr = pl[p * g.S + (k == 0 ? 0 : g.K2 - k)];
-                    // (z + conj zr) / 2 and (z - conj zr) / 2i
-                    a[m] = C{(R)0.5 * (z.x + zr.x), (R)0.5 * (z.y - zr.y)};
-                    b[m] = C{(R)0.5 * (z.y + zr.y), (R)0.5 * (zr.x - z.x)};
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int m = 0; m < kPlSplit; ++m) {
-                const int it = tid + m * NT;
-                if (it < cnt) {
-                    const int pq = dkh.quot(it), p = p0 + pq, k = it - pq * g.kh;
-                    pl[p * g.S + k] = a[m];
-                    pl[p * g.S + g.kh + k] = b[m];
-                }
-            }
-            __syncthreads();
-        }
-    }
+    });
+    __syncthreads();
+    mid_stages<-1>(pl, rc.np, dz, 1, tw_z, LineMap{g.S, 1});
+    last_stage_rows<-1>(pl, rc.np, dz.rad[dz.nr - 1], g, tw_z);
+    __syncthreads();
+    // the two rows of every pair separated into their half spectra: (z + conj zr) / 2 and
+    // (z - conj zr) / 2i with zr at K2 - k
     C* out = gout + ((size_t)x * g.K1 + rc.ya) * g.ks;
     const SmallDiv dkh(g.kh);
-    for (int i = tid; i < nyr * g.kh; i += NT) {
-        const int yl = dkh.quot(i), k = i - yl * g.kh;
-        out[yl * g.ks + k] = pl[(yl >> 1) * g.S + (yl & 1) * g.kh + k];
+    for (int i = tid; i < rc.np * g.kh; i += NT) {
+        const int p = dkh.quot(i), k = i - p * g.kh;
+        const C z = pl[p * g.S + k], zr = pl[p * g.S + (k == 0 ? 0 : g.K2 - k)];
+        out[(size_t)(2 * p) * g.ks + k] = C{(R)0.5 * (z.x + zr.x), (R)0.5 * (z.y - zr.y)};
+        if (2 * p + 1 < nyr)
+            out[(size_t)(2 * p + 1) * g.ks + k] = C{(R)0.5 * (z.y + zr.y), (R)0.5 * (zr.x - z.x)};
     }
 }
 
+// First and last stage of a column pass: thread (column col, butterfly j), the workgroup holding
+// every butterfly.  The first reads the butterfly's points from src (point stride ss) and leaves
+// its outputs in LDS; the last takes them from LDS to dst.  Offsets from the two bases stay below
+// 2^32 bytes (a column pass spans one grid), which leaves one address register per access.
+template <typename C> __device__ __forceinline__ C load_at(const C* base, unsigned byte_off)
+{
+    return *reinterpret_cast<const C*>(reinterpret_cast<const char*>(base) + byte_off);
+}
+template <typename C> __device__ __forceinline__ void store_at(C* base, unsigned byte_off, C v)
+{
+    *reinterpret_cast<C*>(reinterpret_cast<char*>(base) + byte_off) = v;
+}
+
+template <int SIGN, typename C>
+__device__ __forceinline__ void first_stage_cols(const C* __restrict__ src, unsigned ss, C* buf, int rad,
+                                                 const PlaneGeom& g, int N)
+{
+    with_radix(rad, [&](auto rc_) {
+        constexpr int RAD = decltype(rc_)::value;
+        const int nb = N / RAD, tid = opaque(threadIdx.x), col = tid & (g.kc - 1);
+        const int j = tid >> g.kcs;
+        if (j < nb) {
+            const unsigned off = (j * ss + col) * sizeof(C), step = nb * ss * sizeof(C);
+            C v[RAD];
+#pragma unroll
+            for (int r = 0; r < RAD; ++r)
+                v[r] = load_at(src, off + r * step);
+            dft<RAD, SIGN>(v);
+#pragma unroll
+            for (int q = 0; q < RAD; ++q)
+                buf[(j * RAD + q) * g.kl + col] = v[q];
+        }
+    });
+}
+
+template <int SIGN, typename C>
+__device__ __forceinline__ void last_stage_cols(const C* buf, C* __restrict__ dst, unsigned ds, int rad,
+                                                const PlaneGeom& g, int N, const C* tw)
+{
+    with_radix(rad, [&](auto rc_) {
+        constexpr int RAD = decltype(rc_)::value;
+        const int nb = N / RAD, tid = opaque(threadIdx.x), col = tid & (g.kc - 1);
+        const int j = tid >> g.kcs;
+        if (j < nb) {
+            C v[RAD];
+            const C* pt = buf + j * g.kl + col;
+            rooted_points<RAD, SIGN>(v, tw, j, [&](int r) { return pt[r * nb * g.kl]; });
+            dft<RAD, SIGN>(v);
+            const unsigned off = (j * ds + col) * sizeof(C), step = nb * ds * sizeof(C);
+#pragma unroll
+            for (int q = 0; q < RAD; ++q)
+                store_at(dst, off + q * step, v[q]);
+        }
+    });
+}
+
 // Passes 2 and 4 (y transform, SIGN -1 forward, +1 inverse): workgroup (plane x, column chunk):
-// the y-lines G[x][.][kz] for kz in the chunk, in place.
+// the y-lines G[x][.][kz] for kz in the chunk, in place.  A chunk is one 128-byte line of columns
+// (the padding columns of a row are transformed along; nothing reads them).
+// Bound by the grid's bytes through the caches: 42 MB in and out at 216^3 in FP32.  The stages that
+// all went through LDS (a fill, three stages and a store) took y + x + y 128 us there, 255 us in
+// FP64, and 69 / 91 us at 144^3; with the first and last stage in registers they take 71 and 122 us,
+// and 43 / 51 us.
 template <typename R, int SIGN>
 __global__ __launch_bounds__(kPlColThreads) void k_pme_ylines(PlaneGeom g, PlaneDim dy,
                                                            typename PlT<R>::C* __restrict__ gc,
@@ -573,37 +427,23 @@ __global__ __launch_bounds__(kPlColThreads) void k_pme_ylines(PlaneGeom g, Plane
     extern __shared__ __align__(16) double pl_smem[];
     if (use_done && sc->done)
         return;
-    const int tid = threadIdx.x;
     const int item = blockIdx.x;
     const int x = item / g.nkc, kz0 = (item - x * g.nkc) * g.kc;
-    const int ncol = min(g.kc, g.kh - kz0);
-    const SmallDiv dnc(ncol);
     C* buf = reinterpret_cast<C*>(pl_smem);
     C* tw = buf + g.K1 * g.kl;
-    for (int i = tid; i < g.K1; i += kPlColThreads)
-        tw[i] = roots_y[i];
     C* base = gc + (size_t)x * g.K1 * g.ks + kz0;
-    fill_lds<kPlColThreads>(
-        g.K1 * ncol, base,
-        [&](int i) {
-            const int y = dnc.quot(i);
-            return (size_t)y * g.ks + (i - y * ncol);
-        },
-        buf,
-        [&](int i) {
-            const int y = dnc.quot(i);
-            return y * g.kl + (i - y * ncol);
-        });
+    first_stage_cols<SIGN>(base, (unsigned)g.ks, buf, dy.rad[0], g, g.K1);
+    for (int i = threadIdx.x; i < g.K1; i += blockDim.x)
+        tw[i] = roots_y[i];
     __syncthreads();
-    fft_lines<SIGN, kPlColThreads, kPlColMaxB>(buf, ncol, dy, tw, LineMap{1, 2 * g.kl, g.kl});
-    for (int i = tid; i < g.K1 * ncol; i += kPlColThreads) {
-        const int y = dnc.quot(i), cc = i - y * ncol;
-        base[(size_t)y * g.ks + cc] = buf[y * g.kl + cc];
-    }
+    mid_stages<SIGN>(buf, g.kc, dy, 1, tw, LineMap{1, g.kl});
+    last_stage_cols<SIGN>(buf, base, (unsigned)g.ks, dy.rad[dy.nr - 1], g, g.K1, tw);
 }
 
 // Pass 3: workgroup (ky, column chunk): the x-lines of G for kz in the chunk: FFT, product with
-// the influence function theta (column-chunk layout), inverse FFT, in place.
+// the influence function theta (column-chunk layout), inverse FFT, in place.  The last stage of
+// the forward transform leaves X[j + q nb] in the thread of butterfly j, which is what the first
+// stage of the inverse with the same radix takes there, so the product is made in registers.
 template <typename R>
 __global__ __launch_bounds__(kPlColThreads) void k_pme_xconv(PlaneGeom g, PlaneDim dx,
                                                           typename PlT<R>::C* __restrict__ gc,
@@ -616,62 +456,48 @@ __global__ __launch_bounds__(kPlColThreads) void k_pme_xconv(PlaneGeom g, PlaneD
     extern __shared__ __align__(16) double pl_smem[];
     if (use_done && sc->done)
         return;
-    const int tid = threadIdx.x;
     const int item = blockIdx.x;
     const int ky = item / g.nkc, kz0 = (item - ky * g.nkc) * g.kc;
-    const int ncol = min(g.kc, g.kh - kz0);
-    const SmallDiv dnc(ncol);
     C* buf = reinterpret_cast<C*>(pl_smem);
     C* tw = buf + g.K0 * g.kl;
-    for (int i = tid; i < g.K0; i += kPlColThreads)
+    const unsigned xs = (unsigned)(g.K1 * g.ks);   // stride of x in G
+    C* base = gc + (size_t)ky * g.ks + kz0;
+    first_stage_cols<-1>(base, xs, buf, dx.rad[0], g, g.K0);
+    for (int i = threadIdx.x; i < g.K0; i += blockDim.x)
         tw[i] = roots_x[i];
-    const size_t xs = (size_t)g.K1 * g.ks;   // stride of x in G (and theta)
-    const size_t off = (size_t)ky * g.ks + kz0;
-    fill_lds<kPlColThreads>(
-        g.K0 * ncol, gc,
-        [&](int i) {
-            const int xx = dnc.quot(i);
-            return xx * xs + off + (i - xx * ncol);
-        },
-        buf,
-        [&](int i) {
-            const int xx = dnc.quot(i);
-            return xx * g.kl + (i - xx * ncol);
-        });
     __syncthreads();
-    const LineMap am{1, 2 * g.kl, g.kl};
-    fft_lines<-1, kPlColThreads, kPlColMaxB>(buf, ncol, dx, tw, am);
-    // product with the influence function (stored chunk by chunk: this workgroup's block is
-    // contiguous); its loads issued kPlLoads at a time
-    const R* th_blk = theta + (size_t)item * g.K0 * g.kc;
-    for (int i0 = tid; i0 < g.K0 * ncol; i0 += kPlLoads * kPlColThreads) {
-        R th[kPlLoads];
+    const LineMap am{1, g.kl};
+    mid_stages<-1>(buf, g.kc, dx, 1, tw, am);
+    const R* th = theta + (size_t)item * g.K0 * g.kc;
+    with_radix(dx.rad[dx.nr - 1], [&](auto rc_) {
+        constexpr int RAD = decltype(rc_)::value;
+        const int nb = g.K0 / RAD, tid = opaque(threadIdx.x), col = tid & (g.kc - 1), j = tid >> g.kcs;
+        C v[RAD];
+        if (j < nb) {   // the workgroup holds every butterfly of the stage
+            R f[RAD];
 #pragma unroll
-        for (int u = 0; u < kPlLoads; ++u) {
-            const int i = i0 + u * kPlColThreads;
-            if (i < g.K0 * ncol) {
-                const int kx = dnc.quot(i);
-                th[u] = th_blk[kx * g.kc + (i - kx * ncol)];
-            }
-        }
+            for (int q = 0; q < RAD; ++q)
+                f[q] = th[(j + q * nb) * g.kc + col];
+            const C* pt = buf + j * g.kl + col;
+            rooted_points<RAD, -1>(v, tw, j, [&](int r) { return pt[r * nb * g.kl]; });
+            dft<RAD, -1>(v);
 #pragma unroll
-        for (int u = 0; u < kPlLoads; ++u) {
-            const int i = i0 + u * kPlColThreads;
-            if (i < g.K0 * ncol) {
-                const int kx = dnc.quot(i), cc = i - kx * ncol;
-                C v = buf[kx * g.kl + cc];
-                v.x *= th[u];
-                v.y *= th[u];
-                buf[kx * g.kl + cc] = v;
+            for (int q = 0; q < RAD; ++q) {
+                v[q].x *= f[q];
+                v[q].y *= f[q];
             }
+            dft<RAD, +1>(v);
         }
-    }
+        __syncthreads();
+        if (j < nb) {
+#pragma unroll
+            for (int q = 0; q < RAD; ++q)
+                buf[(j * RAD + q) * g.kl + col] = v[q];
+        }
+    });
     __syncthreads();
-    fft_lines<+1, kPlColThreads, kPlColMaxB>(buf, ncol, dx, tw, am);
-    for (int i = tid; i < g.K0 * ncol; i += kPlColThreads) {
-        const int xx = dnc.quot(i), cc = i - xx * ncol;
-        gc[xx * xs + off + cc] = buf[xx * g.kl + cc];
-    }
+    mid_stages<+1>(buf, g.kc, dx, -1, tw, am);
+    last_stage_cols<+1>(buf, base, xs, dx.rad[0], g, g.K0, tw);
 }
 
 // Pass 5 (z transform back, interpolation): workgroup (row chunk c, plane x).  The potential
@@ -683,7 +509,7 @@ __global__ __launch_bounds__(kPlColThreads) void k_pme_xconv(PlaneGeom g, PlaneD
 // M_x M_y M'_z psi) over its 25 (y, z) points, t its weight index for the plane (the K/L
 // factors and the sign are applied by the combine).
 template <typename R, int NT>
-__global__ __launch_bounds__(NT) void k_pme_z_gather(PlaneGeom g, PlaneDim dz,
+__global__ __launch_bounds__(NT, sizeof(R) == 8 ? 4 : 1) void k_pme_z_gather(PlaneGeom g, PlaneDim dz,
                                                              const typename PlT<R>::C* __restrict__ gc,
                                                              const int* __restrict__ xy_start,
                                                              const int4* __restrict__ xb_rec,
@@ -707,62 +533,48 @@ __global__ __launch_bounds__(NT) void k_pme_z_gather(PlaneGeom g, PlaneDim dz,
     C* tw_z = pl + (g.Pc + 2) * g.S;
     for (int i = tid; i < g.K2; i += NT)
         tw_z[i] = roots_z[i];
-    const SmallDiv dkh(g.kh);
-    fill_lds<NT>(
-        nrows * g.kh, gc,
-        [&](int i) {
-            const int r = dkh.quot(i), k = i - r * g.kh;
-            int gy = rc.ya - 4 + r;
-            gy += gy < 0 ? g.K1 : 0;
-            return ((size_t)x * g.K1 + gy) * g.ks + k;
-        },
-        pl,
-        [&](int i) {
-            const int r = dkh.quot(i), k = i - r * g.kh;
-            return (r >> 1) * g.S + (r & 1) * g.kh + k;
-        });
-    if (nrows & 1)  // the last line holds one row only
-        for (int k = tid; k < g.kh; k += NT)
-            pl[(npl - 1) * g.S + g.kh + k] = C{(R)0, (R)0};
-    __syncthreads();
-    {
-        const int lpr = max(1, NT * kPlSplit / g.K2);
-        const SmallDiv dk2(g.K2);
-        for (int p0 = 0; p0 < npl; p0 += lpr) {
-            const int cnt = min(lpr, npl - p0) * g.K2;
-            C zv[kPlSplit];
+    // the first stage of the inverse along z reads the half spectra and forms the complex lines
+    with_radix(dz.rad[dz.nr - 1], [&](auto rc_) {
+        constexpr int RAD = decltype(rc_)::value;
+        const int nb = g.K2 / RAD;
+        const SmallDiv dnb(nb);
+        for (int i0 = tid; i0 < npl * nb; i0 += NT) {
+            const int i = opaque(i0), lq = dnb.quot(i), j = i - lq * nb;
+            int gy0 = rc.ya - 4 + 2 * lq, gy1 = gy0 + 1;
+            gy0 += gy0 < 0 ? g.K1 : 0;
+            gy1 += gy1 < 0 ? g.K1 : 0;
+            const bool two = 2 * lq + 1 < nrows;  // the last line may hold one row only
+            const C* ra = gc + ((size_t)x * g.K1 + gy0) * g.ks;
+            const C* rb = gc + ((size_t)x * g.K1 + (two ? gy1 : gy0)) * g.ks;
+            C v[RAD];
 #pragma unroll
-            for (int m = 0; m < kPlSplit; ++m) {
-                const int it = tid + m * NT;
-                if (it < cnt) {
-                    const int pq = dk2.quot(it), p = p0 + pq, k = it - pq * g.K2;
-                    const bool up = k >= g.kh;
-                    const int kk = up ? g.K2 - k : k;
-                    C a = pl[p * g.S + kk], b = pl[p * g.S + g.kh + kk];
-                    if (kk == 0 || 2 * kk == g.K2) {
-                        a.y = (R)0;
-                        b.y = (R)0;
-                    }
-                    if (up) {
-                        a.y = -a.y;
-                        b.y = -b.y;
-                    }
-                    zv[m] = C{a.x - b.y, a.y + b.x};
+            for (int r = 0; r < RAD; ++r) {
+                const int k = j + r * nb;
+                const bool up = k >= g.kh;
+                const int kk = up ? g.K2 - k : k;
+                C a = ra[kk], b = rb[kk];
+                if (!two)
+                    b.x = b.y = (R)0;
+                if (kk == 0 || 2 * kk == g.K2)
+                    a.y = b.y = (R)0;
+                if (up) {
+                    a.y = -a.y;
+                    b.y = -b.y;
                 }
+                v[r] = C{a.x - b.y, a.y + b.x};
+                if (sizeof(R) == 8 && r % kRootGroup == kRootGroup - 1)
+                    __builtin_amdgcn_sched_barrier(0);  // as in rooted_points: bounds the registers
             }
-            __syncthreads();
+            dft<RAD, +1>(v);
 #pragma unroll
-            for (int m = 0; m < kPlSplit; ++m) {
-                const int it = tid + m * NT;
-                if (it < cnt) {
-                    const int pq = dk2.quot(it), p = p0 + pq, k = it - pq * g.K2;
-                    pl[p * g.S + k] = zv[m];
-                }
-            }
-            __syncthreads();
+            for (int q = 0; q < RAD; ++q)
+                pl[lq * g.S + j * RAD + q] = v[q];
         }
-    }
-    fft_lines<+1, NT>(pl, npl, dz, tw_z, LineMap{g.S, 2, 1});
+    });
+    __syncthreads();
+    mid_stages<+1>(pl, npl, dz, -1, tw_z, LineMap{g.S, 1});
+    last_stage_rows<+1>(pl, npl, dz.rad[0], g, tw_z);
+    __syncthreads();
     // potential of local row r (global row ya - 4 + r), point z: component r mod 2 of
     // pl[(r div 2) S + z]
     const R* psi = reinterpret_cast<const R*>(pl_smem);
@@ -975,23 +787,43 @@ __global__ void k_plane_roots(int n, typename PlT<R>::C* __restrict__ out)
 static inline int nblk(size_t n, int b) { return (int)((n + b - 1) / b); }
 static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-// radices 6, 4, 3, 5, 7, 2 in that order; every stage must fit one round of butterflies
+static int min_radix(const PlaneDim& d) { return *std::min_element(d.rad, d.rad + d.nr); }
+
+// The radices of length n: as few as possible (at least two), and of those the split whose
+// smallest radix is largest (the fewest butterflies, so the fewest threads, in a stage); the two
+// largest at the ends, the others (at most 9) between them.  Returns false where a prime factor
+// above 7 is left or a stage would need more than 256 butterflies.
 static bool plane_factor(int n, PlaneDim& d)
 {
+    static const int radices[] = {18, 16, 15, 14, 12, 10, 9, 8, 7, 6, 5, 4, 3, 2};
     d.n = n;
     d.nr = 0;
-    int m = n;
-    for (int r : {6, 4, 3, 5, 7, 2})
-        while (m % r == 0) {
-            if (d.nr >= 12)
-                return false;
-            if (n / r > kPlColThreads * kPlMaxB)
-                return false;
-            d.rad[d.nr++] = r;
-            m /= r;
-        }
-    return m == 1 && n >= 2;
+    for (int nr = 2; nr <= 8 && d.nr == 0; ++nr) {
+        int cur[8], best = 0;
+        auto split = [&](auto&& self, int left, int at, int most) -> void {
+            if (at == nr) {
+                if (left == 1 && cur[nr - 1] > best && (nr < 3 || cur[2] <= 9)) {
+                    best = cur[nr - 1];  // non-increasing: the last is the smallest
+                    d.nr = nr;
+                    d.rad[0] = cur[0];
+                    d.rad[nr - 1] = cur[1];
+                    std::copy(cur + 2, cur + nr, d.rad + 1);
+                }
+                return;
+            }
+            for (int r : radices)
+                if (r <= most && left % r == 0) {
+                    cur[at] = r;
+                    self(self, left / r, at + 1, r);
+                }
+        };
+        split(split, n, 0, 18);
+    }
+    return d.nr > 0 && n / min_radix(d) <= 256;
 }
+
+// threads of a column pass: every butterfly of its widest stage for kc columns, in whole waves
+static int col_threads(const PlaneDim& d, int kc) { return cdiv(kc * (d.n / min_radix(d)), 64) * 64; }
 
 static size_t lds_spread(const PlaneGeom& g, size_t cs) { return 16 * (size_t)g.Pc * g.S + cs * g.K2; }
 static size_t lds_gather(const PlaneGeom& g, size_t cs) { return cs * ((size_t)(g.Pc + 2) * g.S + g.K2); }
@@ -1016,29 +848,41 @@ static PlaneGeom plane_geom(const amoeba_ctx* c)
     // limits; a grid that needs more than kPlLargeWG of them (two 512-thread workgroups fit a CU)
     // takes 256-thread workgroups on smaller chunks, so that more of them are resident at once
     // and the chip is not left with a partial last round (measured at 216^3)
+    PlaneDim dz;
+    plane_factor(g.K2, dz);
+    const int zb = dz.nr > 0 ? g.K2 / min_radix(dz) : 1;
+    auto one_round = [&]() { return g.Pc * zb <= g.nt; };  // the spread's first stage: a thread for every butterfly
     auto rows = [&](int target) {
         g.nyc = std::min(g.P, std::max(1, cdiv(target, g.K0)));
         g.Pc = cdiv(g.P, g.nyc);
-        while (g.Pc > 1 && (lds_spread(g, cs) > kPlLdsMax || lds_gather(g, cs) > kPlLdsMax ||
-                            2 * g.Pc * g.S > kPlConvTotal))
+        while (g.Pc > 1 && (lds_spread(g, cs) > kPlLdsMax || lds_gather(g, cs) > kPlLdsMax || !one_round()))
             g.Pc = cdiv(g.Pc, 2);
         g.nyc = cdiv(g.P, g.Pc);
     };
     g.nt = kPlThreads;
     rows(kPlTargetWG);
-    const bool large = g.K0 * g.nyc > kPlLargeWG;
-    if (large) {
+    if (g.K0 * g.nyc > kPlLargeWG) {
         g.nt = kPlThreadsLarge;
         rows(kPlTargetWGLarge);
+        if (!one_round()) {
+            g.nt = kPlThreads;
+            rows(kPlTargetWG);
+        }
     }
-    // column chunks likewise (on a large grid at most kPlColMaxKc columns, for the same reason)
-    g.nkc = std::min(g.kh, std::max(1, cdiv(kPlColTargetWG, std::min(g.K0, g.K1))));
-    g.kc = cdiv(g.kh, g.nkc);
-    if (large)
-        g.kc = std::min(g.kc, kPlColMaxKc);
-    g.kc = std::min(cdiv(g.kc, line) * line, g.ks);
-    while (g.kc > 1 && (lds_lines(g.K0, g.kc, cs) > kPlLdsMax || lds_lines(g.K1, g.kc, cs) > kPlLdsMax))
-        g.kc = cdiv(g.kc, 2);
+    // column chunks of one line, fewer columns where a pass would exceed the threads or the LDS of
+    // a workgroup (lengths far above those of the plane path's usual grids)
+    PlaneDim dx, dy;
+    plane_factor(g.K0, dx);  // (a length without a factorisation: not eligible, see plane_eligible)
+    plane_factor(g.K1, dy);
+    g.kc = line;
+    while (g.kc > 1 && (col_threads(dx, g.kc) > kPlColThreads || col_threads(dy, g.kc) > kPlColThreads ||
+                        lds_lines(g.K0, g.kc, cs) > kPlLdsMax || lds_lines(g.K1, g.kc, cs) > kPlLdsMax))
+        g.kc /= 2;
+    g.kcs = 0;
+    while ((1 << g.kcs) < g.kc)
+        ++g.kcs;
+    g.nty = col_threads(dy, g.kc);
+    g.ntx = col_threads(dx, g.kc);
     g.nkc = cdiv(g.kh, g.kc);
     g.kl = g.kc | 1;
     g.klx = c->K[0] / c->prm.box[0];
@@ -1065,9 +909,8 @@ bool plane_eligible(const amoeba_ctx* c)
     const PlaneGeom g = plane_geom(c);
     const size_t cs = c->mixed ? sizeof(float2) : sizeof(double2);
     return lds_spread(g, cs) <= kPlLdsMax && lds_gather(g, cs) <= kPlLdsMax &&
-           lds_lines(g.K0, g.kc, cs) <= kPlLdsMax && lds_lines(g.K1, g.kc, cs) <= kPlLdsMax &&
-           2 * g.Pc * g.S <= kPlConvTotal && g.kh <= g.nt * kPlSplit && g.K2 <= g.nt * kPlSplit &&
-           (size_t)g.K0 * g.K1 <= 65536;
+           g.Pc * (g.K2 / min_radix(d)) <= g.nt && lds_lines(g.K0, g.kc, cs) <= kPlLdsMax &&
+           lds_lines(g.K1, g.kc, cs) <= kPlLdsMax && g.nty <= kPlColThreads && g.ntx <= kPlColThreads && (size_t)g.K0 * g.K1 <= 65536;
 }
 
 int plane_setup(amoeba_ctx* c)
@@ -1137,7 +980,7 @@ template <typename R> static void plane_field_t(amoeba_ctx* c, bool use_done, in
     const int ud = use_done ? 1 : 0;
     const C* const* roots = (const C* const*)c->pl_roots;
     C* gc = (C*)c->grid_c;
-    const dim3 nt(g.nt), ntc(kPlColThreads);
+    const dim3 nt(g.nt);
     const bool small = g.nt == kPlThreads;
     constexpr bool FIX = std::is_same<R, float>::value;
     if (parts & 1) {
@@ -1154,11 +997,11 @@ template <typename R> static void plane_field_t(amoeba_ctx* c, bool use_done, in
         return;
     {
         StageTimer tm(c, perm ? AMOEBA_T_PERM : AMOEBA_T_FFT);
-        hipLaunchKernelGGL((k_pme_ylines<R, -1>), dim3(g.K0 * g.nkc), ntc, lds_lines(g.K1, g.kc, cs), st, g, d[1], gc,
+        hipLaunchKernelGGL((k_pme_ylines<R, -1>), dim3(g.K0 * g.nkc), dim3(g.nty), lds_lines(g.K1, g.kc, cs), st, g, d[1], gc,
                            roots[1], c->sc, ud);
-        hipLaunchKernelGGL(k_pme_xconv<R>, dim3(g.K1 * g.nkc), ntc, lds_lines(g.K0, g.kc, cs), st, g, d[0], gc,
+        hipLaunchKernelGGL(k_pme_xconv<R>, dim3(g.K1 * g.nkc), dim3(g.ntx), lds_lines(g.K0, g.kc, cs), st, g, d[0], gc,
                            (const R*)c->theta_pl, roots[0], c->sc, ud);
-        hipLaunchKernelGGL((k_pme_ylines<R, 1>), dim3(g.K0 * g.nkc), ntc, lds_lines(g.K1, g.kc, cs), st, g, d[1], gc,
+        hipLaunchKernelGGL((k_pme_ylines<R, 1>), dim3(g.K0 * g.nkc), dim3(g.nty), lds_lines(g.K1, g.kc, cs), st, g, d[1], gc,
                            roots[1], c->sc, ud);
     }
     {
