@@ -167,6 +167,13 @@ __global__ void k_gather_mpole(int npad, const int* __restrict__ perm, const dou
 
 static inline int nblk(size_t n, int b) { return (int)((n + b - 1) / b); }
 
+// multipoles of the caller into mp_d (and mp_f)
+void launch_gather_mpole(amoeba_ctx* c, const double* q, const double* dip, const double* quad, int* flags)
+{
+    hipLaunchKernelGGL(k_gather_mpole, dim3(nblk(c->npad, 256)), dim3(256), 0, c->stream, c->npad, c->perm, q, dip,
+                       quad, c->mp_d, c->mixed ? c->mp_f : nullptr, flags);
+}
+
 int sort_params(amoeba_ctx* c);
 
 int read_flags(amoeba_ctx* c, int* out)
@@ -541,8 +548,7 @@ static int perm_field_parts(amoeba_ctx* c, const double* pos, const double* q, c
         flags = c->flags;
         hipMemsetAsync(flags, 0, sizeof(int), st);
     }
-    hipLaunchKernelGGL(k_gather_mpole, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->perm, q, dip, quad,
-                       c->mp_d, c->mixed ? c->mp_f : nullptr, flags);
+    launch_gather_mpole(c, q, dip, quad, flags);
     if (pme_use_planes(c) && !c->timing) {
         // the multipole tiles (VALU bound) on the second stream beside the reciprocal passes
         hipEventRecord(c->ev_fork, st);
@@ -924,22 +930,9 @@ int amoeba_polarization_gradient(amoeba_ctx* c, const double* pos, const double*
     int rc = begin_config(c, pos, "amoeba_polarization_gradient");
     if (rc)
         return rc;
-    if (!c->mp_d) {
-        if ((rc = ctx_alloc(c, (void**)&c->mp_d, sizeof(double4) * 3 * c->npad)))
-            return rc;
-        if (c->mixed && (rc = ctx_alloc(c, (void**)&c->mp_f, sizeof(float4) * 3 * c->npad)))
-            return rc;
-    }
-    hipStream_t st = c->stream;
-    hipMemsetAsync(c->flags, 0, sizeof(int), st);
-    hipLaunchKernelGGL(k_gather_mpole, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->perm, q, dip, quad,
-                       c->mp_d, c->mixed ? c->mp_f : nullptr, c->flags);
-    launch_gather_vec_checked(c, mu, c->v_mu);
-    if ((rc = polar_gradient_slot(c)))
+    hipMemsetAsync(c->flags, 0, sizeof(int), c->stream);
+    if ((rc = polar_gradient(c, q, dip, quad, mu, grad_out)))
         return rc;
-    if (c->mixed)
-        launch_check_overflow(c, c->ereal);   // the fixed-point pair sums
-    launch_scatter(c, c->v_q, grad_out);
     int f = 0;
     if ((rc = read_flags(c, &f)))
         return rc;

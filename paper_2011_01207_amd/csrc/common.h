@@ -258,7 +258,9 @@ struct amoeba_ctx {
     double4* mp_d = nullptr;               // [npad*3] (q,dx,dy,dz),(Txx,Txy,Txz,Tyy),(Tyz,Tzz,0,0)
     float4* mp_f = nullptr;                // same in FP32 (mixed mode)
     void* f_src = nullptr;                 // [npad*4] (R4) multipoles + dipoles of the gradient tiles
-    void* f_psi = nullptr;                 // [K0*K1*K2] (R) grid potential of the multipoles (gradient)
+    void* f_psi = nullptr;                 // [K0*K1*K2] (R) grid potential of the multipoles (gradient, brick path)
+    void* f_grid = nullptr;                // a second half grid of the plane path (gradient)
+    double4* f_part = nullptr;             // [5][npad] reciprocal gradient shares of an atom's five x-planes
 
     amoeba::PcgScalars* sc = nullptr;      // device scalars
     amoeba::PcgScalars* sc_host = nullptr; // pinned mirror [2] (one per in-flight PCG iteration)
@@ -375,7 +377,7 @@ int next_coef_mode(const amoeba_ctx* c);  // the next dipole product: 0 evaluate
 void launch_real_reduce(amoeba_ctx* c, double* ereal, hipStream_t st = nullptr, bool use_done = false);
 void launch_perm_tiles(amoeba_ctx* c, hipStream_t st = nullptr);
 void launch_perm_assemble(amoeba_ctx* c, double* out_slot, const double* scales);  // scales in slot order
-void launch_force_tiles(amoeba_ctx* c, const void* src, double* out);  // real-space gradient pair sums
+void launch_force_tiles(amoeba_ctx* c, const void* src, double* out, hipStream_t st);  // real-space gradient pair sums
 
 // pme.hip
 int pme_setup(amoeba_ctx* c);
@@ -393,18 +395,23 @@ int plane_bin_atoms(amoeba_ctx* c);
 void plane_dipole_field(amoeba_ctx* c, bool use_done, int parts);  // 1 spread, 2 the rest, 3 all
 void plane_perm_field(amoeba_ctx* c);                             // permanent multipoles, all passes
 void plane_gather(amoeba_ctx* c, double* out);          // E_rec from the plane shares
+size_t plane_grid_bytes(const amoeba_ctx* c);
+bool plane_force_fits(const amoeba_ctx* c);
+void plane_force(amoeba_ctx* c, const void* src, void* grid1, double4* part);  // reciprocal gradient shares
 int plane_combine(amoeba_ctx* c, bool use_done, bool dot_pq, bool reduced);  // PCG product; returns its partial count
 bool pme_use_planes(const amoeba_ctx* c);
 void launch_gather(amoeba_ctx* c, double* out);       // E_rec at atoms from the potential grid
 int pme_brick_potential(amoeba_ctx* c, bool perm);    // psi of the multipoles (perm) or of pv, brick path
 
 // force.hip
-int polar_gradient_slot(amoeba_ctx* c);               // dE_pol/dr (slot order) into v_q
+int polar_gradient(amoeba_ctx* c, const double* q, const double* dip, const double* quad, const double* mu,
+                   double* grad_out);                  // dE_pol/dr, everything in caller order
 
 // api.hip
 int read_flags(amoeba_ctx* c, int* out);
 int check_vec_finite(amoeba_ctx* c, const double* v, size_t n, const char* what);
 void launch_check_overflow(amoeba_ctx* c, const double* v_slot);  // |v| < kFixRange, flag on the device
+void launch_gather_mpole(amoeba_ctx* c, const double* q, const double* dip, const double* quad, int* flags);
 int begin_config(amoeba_ctx* c, const double* pos, const char* who);
 
 // guess.hip

@@ -15,6 +15,15 @@
 //       dE_pol,rec/dr_m = C sum_k [ dQ_mu/dr_m (psi_mu + psi_p) + dQ_p/dr_m psi_mu ],
 //     where dQ_mu/dr_m needs the second and dQ_p/dr_m the third B-spline derivatives.
 // The dipole self terms do not depend on the positions.
+// The grid potentials come from the plane passes (plane.hip), both grids transformed together and
+// interpolated by k_pme_z_force, with the pair sums beside them on the second stream; a grid
+// outside the plane path (or the brick path asked for, or no room for the planes' workspace) uses
+// the brick spread, rocFFT and a thread per atom over its 125 points.  At 288,000 atoms (mixed, two
+// configurations) a gradient with its mask refresh took 3.26 ms on the brick path (the per-atom
+// interpolation 0.65 ms of a call, the brick bins and spreads 0.27, rocFFT 0.2) and takes 1.19 ms on
+// the planes; 23,559 atoms in FP64 0.82 and 0.42 ms.
+#include <algorithm>
+
 #include "common.h"
 #include "spline.h"
 
@@ -34,6 +43,53 @@ __global__ void k_force_src(int npad, const double4* __restrict__ mp, const doub
         out[4 * (size_t)s + k] = R4T{(RT)m.x, (RT)m.y, (RT)m.z, (RT)m.w};
     }
     out[4 * (size_t)s + 3] = R4T{(RT)mu[3 * (size_t)s], (RT)mu[3 * (size_t)s + 1], (RT)mu[3 * (size_t)s + 2], (RT)0};
+}
+
+// Inputs of the gradient in slot order, one pass: FP64 multipole records (md) and dipoles (mu_s),
+// and the ForceKind records (src: multipoles and dipoles, R4), which the tiles and the plane
+// spreads read.  Flags non-finite values and a quadrupole that is not traceless.
+template <typename R4T>
+__global__ void k_force_gather(int npad, const int* __restrict__ perm, const double* __restrict__ q,
+                               const double* __restrict__ dip, const double* __restrict__ quad,
+                               const double* __restrict__ mu, double4* __restrict__ md, double* __restrict__ mu_s,
+                               R4T* __restrict__ src, int* __restrict__ flags)
+{
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= npad)
+        return;
+    using RT = decltype(src->x);
+    const int a = perm[s];
+    double v[13] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    if (a >= 0) {
+        v[0] = q[a];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            v[1 + c] = dip[3 * (size_t)a + c];
+            v[10 + c] = mu[3 * (size_t)a + c];
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c)
+            v[4 + c] = quad[6 * (size_t)a + c];
+        bool bad = false;
+#pragma unroll
+        for (int c = 0; c < 13; ++c)
+            bad = bad || !isfinite(v[c]);
+        if (bad)
+            atomicOr(flags, kFlagNonFinite);
+        const double tr = v[4] + v[7] + v[9], sc = fabs(v[4]) + fabs(v[7]) + fabs(v[9]);
+        if (fabs(tr) > 1e-10 * (1.0 + sc))
+            atomicOr(flags, kFlagBadCsr);  // reported as "quadrupole not traceless"
+    }
+    md[3 * (size_t)s] = make_double4(v[0], v[1], v[2], v[3]);
+    md[3 * (size_t)s + 1] = make_double4(v[4], v[5], v[6], v[7]);
+    md[3 * (size_t)s + 2] = make_double4(v[8], v[9], 0.0, 0.0);
+    src[4 * (size_t)s] = R4T{(RT)v[0], (RT)v[1], (RT)v[2], (RT)v[3]};
+    src[4 * (size_t)s + 1] = R4T{(RT)v[4], (RT)v[5], (RT)v[6], (RT)v[7]};
+    src[4 * (size_t)s + 2] = R4T{(RT)v[8], (RT)v[9], (RT)0, (RT)0};
+    src[4 * (size_t)s + 3] = R4T{(RT)v[10], (RT)v[11], (RT)v[12], (RT)0};
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        mu_s[3 * (size_t)s + c] = v[10 + c];
 }
 
 // grad_r of w = mu . E_mp(r) for the multipole (q, d, Theta) of slot j (FP64).
@@ -214,20 +270,104 @@ __global__ void k_force_recip(int npad, const int* __restrict__ perm, const doub
         grad[3 * (size_t)s + c] = kCoulomb * (acc[c] - real[3 * (size_t)s + c] - corr[3 * (size_t)s + c]);
 }
 
+// The gradient in caller order from its parts: grad = C (sum of the five plane shares, in order,
+// - real - corr).  With fixed-point pair sums (range) their range is checked here.
+__global__ __launch_bounds__(256) void k_force_finish(int npad, const int* __restrict__ perm,
+                                                      const double4* __restrict__ part,
+                                                      const double* __restrict__ real,
+                                                      const double* __restrict__ corr, int range,
+                                                      double* __restrict__ grad, int* __restrict__ flags)
+{
+    const int s = blockIdx.x * 256 + threadIdx.x;
+    int f = 0;
+    const int a = s < npad ? perm[s] : -1;
+    if (a >= 0) {
+        double4 v[5];
+#pragma unroll
+        for (int t = 0; t < 5; ++t)
+            v[t] = part[(size_t)t * npad + s];
+        const double rec[3] = {(((v[0].x + v[1].x) + v[2].x) + v[3].x) + v[4].x,
+                               (((v[0].y + v[1].y) + v[2].y) + v[3].y) + v[4].y,
+                               (((v[0].z + v[1].z) + v[2].z) + v[3].z) + v[4].z};
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double r = real[3 * (size_t)s + c];
+            if (range && !(fabs(r) < kFixRange))
+                f |= isfinite(r) ? kFlagOverflow : kFlagNonFinite;
+            grad[3 * (size_t)a + c] = kCoulomb * (rec[c] - r - corr[3 * (size_t)s + c]);
+        }
+    }
+    if (f)
+        atomicOr(flags, f);
+}
+
 static inline int nblk(size_t n, int b) { return (int)((n + b - 1) / b); }
 
-// dE_pol/dr in slot order into c->v_q, for the multipoles in mp_d/mp_f and the dipoles in v_mu
-// (both gathered by the caller).  Uses the brick spread and rocFFT for the two grid potentials.
-int polar_gradient_slot(amoeba_ctx* c)
+static void launch_force_scaled(amoeba_ctx* c, hipStream_t st)
+{
+    const double3 box = make_double3(c->prm.box[0], c->prm.box[1], c->prm.box[2]);
+    hipLaunchKernelGGL(k_force_scaled, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->perm, c->pos_s,
+                       c->par_d, (const double4*)c->mp_d, c->v_mu, c->sc_ptr, c->sc_j, c->sc_s, box,
+                       make_double3(1.0 / box.x, 1.0 / box.y, 1.0 / box.z), c->prm.cutoff * c->prm.cutoff, c->erec);
+}
+
+// The plane path's workspace of the gradient: a second half grid and FP64 shares (an FP64
+// context's dipole shares serve).  False where the workspace cap leaves no room for it.
+static bool force_planes_ready(amoeba_ctx* c)
+{
+    if (!pme_use_planes(c) || !plane_force_fits(c))
+        return false;
+    if (!c->f_grid) {
+        const size_t part = c->mixed ? sizeof(double4) * 5 * (size_t)c->npad : 0, grid = plane_grid_bytes(c);
+        const int64_t cap = c->prm.max_workspace_bytes;
+        if (cap > 0 && c->ws_bytes - c->coef_bytes + (int64_t)(part + grid) > cap)
+            return false;
+        if ((part && !c->f_part && ctx_alloc(c, (void**)&c->f_part, part)) || ctx_alloc(c, &c->f_grid, grid)) {
+            c->err.clear();
+            return false;
+        }
+        if (!c->mixed)
+            c->f_part = (double4*)c->rec_part;
+    }
+    return true;
+}
+
+// dE_pol/dr in caller order for multipoles and dipoles given in caller order, on the plane path:
+// the pair sums and the scaled-pair correction on the second stream beside the grid passes.
+static void gradient_planes(amoeba_ctx* c, const double* q, const double* dip, const double* quad, const double* mu,
+                            double* grad_out)
+{
+    hipStream_t st = c->stream;
+    const dim3 g(nblk(c->npad, 256)), b(256);
+    if (c->mixed)
+        hipLaunchKernelGGL(k_force_gather<float4>, g, b, 0, st, c->npad, c->perm, q, dip, quad, mu, c->mp_d, c->v_mu,
+                           (float4*)c->f_src, c->flags);
+    else
+        hipLaunchKernelGGL(k_force_gather<double4>, g, b, 0, st, c->npad, c->perm, q, dip, quad, mu, c->mp_d, c->v_mu,
+                           (double4*)c->f_src, c->flags);
+    hipEventRecord(c->ev_fork, st);
+    hipStreamWaitEvent(c->stream2, c->ev_fork, 0);
+    launch_force_tiles(c, c->f_src, c->ereal, c->stream2);
+    launch_force_scaled(c, c->stream2);
+    hipEventRecord(c->ev_join, c->stream2);
+    plane_force(c, c->f_src, c->f_grid, c->f_part);
+    hipStreamWaitEvent(st, c->ev_join, 0);
+    hipLaunchKernelGGL(k_force_finish, g, b, 0, st, c->npad, c->perm, c->f_part, c->ereal, c->erec, (int)c->mixed,
+                       grad_out, c->flags);
+}
+
+// The same on the brick path: brick spread and rocFFT for the two grid potentials, a thread per
+// atom for the interpolation.
+static int gradient_bricks(amoeba_ctx* c, const double* q, const double* dip, const double* quad, const double* mu,
+                           double* grad_out)
 {
     hipStream_t st = c->stream;
     int rc;
     const size_t rs = c->mixed ? sizeof(float) : sizeof(double);
-    if (!c->f_src) {
-        if ((rc = ctx_alloc(c, &c->f_src, 4 * 4 * rs * (size_t)c->npad)) ||
-            (rc = ctx_alloc(c, &c->f_psi, rs * c->ngrid)))
-            return rc;
-    }
+    if (!c->f_psi && (rc = ctx_alloc(c, &c->f_psi, rs * c->ngrid)))
+        return rc;
+    launch_gather_mpole(c, q, dip, quad, c->flags);
+    launch_gather_vec_checked(c, mu, c->v_mu);
     // sources: ForceKind records (multipoles + dipoles) and the pair kernels' dipole copy
     if (c->mixed)
         hipLaunchKernelGGL(k_force_src<float4>, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->mp_d,
@@ -236,16 +376,9 @@ int polar_gradient_slot(amoeba_ctx* c)
         hipLaunchKernelGGL(k_force_src<double4>, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->mp_d,
                            c->v_mu, (double4*)c->f_src);
     launch_set_direction(c, c->v_mu);
-    // real space: sum_j G_ij into ereal
-    launch_force_tiles(c, c->f_src, c->ereal);
-    // scaled pairs: into erec
-    {
-        double3 box = make_double3(c->prm.box[0], c->prm.box[1], c->prm.box[2]);
-        hipLaunchKernelGGL(k_force_scaled, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->perm, c->pos_s,
-                           c->par_d, (const double4*)c->mp_d, c->v_mu, c->sc_ptr, c->sc_j, c->sc_s, box,
-                           make_double3(1.0 / box.x, 1.0 / box.y, 1.0 / box.z), c->prm.cutoff * c->prm.cutoff,
-                           c->erec);
-    }
+    // real space: sum_j G_ij into ereal; scaled pairs: into erec
+    launch_force_tiles(c, c->f_src, c->ereal, st);
+    launch_force_scaled(c, st);
     // grid potentials: psi_p (multipoles) kept in f_psi, then psi_mu (dipoles) in grid_r
     if ((rc = pme_brick_potential(c, true)))
         return rc;
@@ -262,6 +395,30 @@ int polar_gradient_slot(amoeba_ctx* c)
         hipLaunchKernelGGL(k_force_recip<double>, dim3(nblk(c->npad, 128)), dim3(128), 0, st, c->npad, c->perm,
                            c->pos_s, kl, K, (const double*)c->grid_r, (const double*)c->f_psi,
                            (const double4*)c->mp_d, c->v_mu, c->ereal, c->erec, c->v_q);
+    if (c->mixed)
+        launch_check_overflow(c, c->ereal);   // the fixed-point pair sums
+    launch_scatter(c, c->v_q, grad_out);
+    return AMOEBA_OK;
+}
+
+// dE_pol/dr (caller order) of multipoles and dipoles in caller order; input and range checks go
+// to the context's flag word.
+int polar_gradient(amoeba_ctx* c, const double* q, const double* dip, const double* quad, const double* mu,
+                   double* grad_out)
+{
+    int rc;
+    if (!c->mp_d) {
+        if ((rc = ctx_alloc(c, (void**)&c->mp_d, sizeof(double4) * 3 * c->npad)))
+            return rc;
+        if (c->mixed && (rc = ctx_alloc(c, (void**)&c->mp_f, sizeof(float4) * 3 * c->npad)))
+            return rc;
+    }
+    if (!c->f_src &&
+        (rc = ctx_alloc(c, &c->f_src, 4 * 4 * (c->mixed ? sizeof(float) : sizeof(double)) * (size_t)c->npad)))
+        return rc;
+    if (!force_planes_ready(c))
+        return gradient_bricks(c, q, dip, quad, mu, grad_out);
+    gradient_planes(c, q, dip, quad, mu, grad_out);
     return AMOEBA_OK;
 }
 

@@ -66,6 +66,7 @@ struct PlaneGeom {
     int S;        // line stride of a pair (complex values): 2 kh
     int P;        // row pairs: ceil(K1 / 2)
     int Pc, nyc;  // pairs per row chunk, row chunks
+    int Pf, nyf;  // the same of the gradient's interpolation (one line per row)
     int kc, kcs, nkc;  // columns per column chunk (a power of two), its exponent, column chunks
     int kl;       // LDS line stride of a column chunk (kc made odd: whole-line strides put every
                   // point of a transform stage in one LDS bank)
@@ -107,10 +108,10 @@ template <int NR> struct BinRanges {
 // Row chunk c of the grid: pairs [p0, p0 + np), rows [ya, yb).
 struct RowChunk {
     int np, ya, yb;
-    __device__ __forceinline__ RowChunk(const PlaneGeom& g, int c)
+    __device__ __forceinline__ RowChunk(const PlaneGeom& g, int c, int pairs)
     {
-        const int p0 = c * g.Pc;
-        np = min(g.Pc, g.P - p0);
+        const int p0 = c * pairs;
+        np = min(pairs, g.P - p0);
         ya = 2 * p0;
         yb = min(g.K1, 2 * (p0 + np));
     }
@@ -161,7 +162,8 @@ __device__ __forceinline__ void last_stage_rows(C* pl, int nl, int rad, const Pl
 // meets the chunk's rows of plane x have fx in x..x+4 and fy in [ya, yb + 4) (mod K); they add
 // p_x M' M M + p_y M M' M + p_z M M M' (derivatives scaled by K/L) at their in-chunk points,
 // or with PERM their permanent multipoles, q M M M + d . grad(M M M) + Theta : grad grad (M M M) / 3
-// (src then holds three R4 per atom: (q, d), (Txx, Txy, Txz, Tyy), (Tyz, Tzz, 0, 0)).
+// (src then holds three R4 per atom: (q, d), (Txx, Txy, Txz, Tyy), (Tyz, Tzz, 0, 0)); sstride R4
+// from one atom's record to the next.
 // Then every row pair is transformed along z, separated into the two rows' half spectra, and
 // the rows are written to G[x][y][0, kh).
 template <typename R, bool FIX, bool PERM, int NT>
@@ -170,6 +172,7 @@ __global__ __launch_bounds__(NT) void k_pme_spread_z(PlaneGeom g, PlaneDim dz,
                                                              const int4* __restrict__ xb_rec,
                                                              const typename PlT<R>::R4* __restrict__ xb_w,
                                                              const typename PlT<R>::R4* __restrict__ src,
+                                                             int sstride,
                                                              const typename PlT<R>::C* __restrict__ roots_z,
                                                              typename PlT<R>::C* __restrict__ gout,
                                                              const PcgScalars* __restrict__ sc, int use_done)
@@ -182,7 +185,7 @@ __global__ __launch_bounds__(NT) void k_pme_spread_z(PlaneGeom g, PlaneDim dz,
     const int tid = threadIdx.x;
     const int item = xcd_remap(blockIdx.x, gridDim.x);
     const int c = item / g.K0, x = item - c * g.K0;
-    const RowChunk rc(g, c);
+    const RowChunk rc(g, c, g.Pc);
     const int n2 = 2 * rc.np * g.S;                    // doubles of the chunk's accumulation
     double* acc = pl_smem;
     C* tw_z = reinterpret_cast<C*>(pl_smem + 2 * g.Pc * g.S);
@@ -230,7 +233,7 @@ __global__ __launch_bounds__(NT) void k_pme_spread_z(PlaneGeom g, PlaneDim dz,
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int k = 0; k < (PERM ? 3 : 1); ++k)
-                m[u][k] = src[(PERM ? 3 : 1) * (size_t)rec[u].x + k];
+                m[u][k] = src[sstride * (size_t)rec[u].x + k];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             if (!ok[u])
@@ -411,7 +414,8 @@ __device__ __forceinline__ void last_stage_cols(const C* buf, C* __restrict__ ds
 
 // Passes 2 and 4 (y transform, SIGN -1 forward, +1 inverse): workgroup (plane x, column chunk):
 // the y-lines G[x][.][kz] for kz in the chunk, in place.  A chunk is one 128-byte line of columns
-// (the padding columns of a row are transformed along; nothing reads them).
+// (the padding columns of a row are transformed along; nothing reads them).  The y index of the
+// launch selects the grid (the gradient transforms two at once).
 // Bound by the grid's bytes through the caches: 42 MB in and out at 216^3 in FP32.  The stages that
 // all went through LDS (a fill, three stages and a store) took y + x + y 128 us there, 255 us in
 // FP64, and 69 / 91 us at 144^3; with the first and last stage in registers they take 71 and 122 us,
@@ -419,6 +423,7 @@ __device__ __forceinline__ void last_stage_cols(const C* buf, C* __restrict__ ds
 template <typename R, int SIGN>
 __global__ __launch_bounds__(kPlColThreads) void k_pme_ylines(PlaneGeom g, PlaneDim dy,
                                                            typename PlT<R>::C* __restrict__ gc,
+                                                           typename PlT<R>::C* __restrict__ gc1,
                                                            const typename PlT<R>::C* __restrict__ roots_y,
                                                            const PcgScalars* __restrict__ sc, int use_done)
 {
@@ -431,7 +436,7 @@ __global__ __launch_bounds__(kPlColThreads) void k_pme_ylines(PlaneGeom g, Plane
     const int x = item / g.nkc, kz0 = (item - x * g.nkc) * g.kc;
     C* buf = reinterpret_cast<C*>(pl_smem);
     C* tw = buf + g.K1 * g.kl;
-    C* base = gc + (size_t)x * g.K1 * g.ks + kz0;
+    C* base = (blockIdx.y ? gc1 : gc) + (size_t)x * g.K1 * g.ks + kz0;
     first_stage_cols<SIGN>(base, (unsigned)g.ks, buf, dy.rad[0], g, g.K1);
     for (int i = threadIdx.x; i < g.K1; i += blockDim.x)
         tw[i] = roots_y[i];
@@ -447,6 +452,7 @@ __global__ __launch_bounds__(kPlColThreads) void k_pme_ylines(PlaneGeom g, Plane
 template <typename R>
 __global__ __launch_bounds__(kPlColThreads) void k_pme_xconv(PlaneGeom g, PlaneDim dx,
                                                           typename PlT<R>::C* __restrict__ gc,
+                                                          typename PlT<R>::C* __restrict__ gc1,
                                                           const R* __restrict__ theta,
                                                           const typename PlT<R>::C* __restrict__ roots_x,
                                                           const PcgScalars* __restrict__ sc, int use_done)
@@ -461,7 +467,7 @@ __global__ __launch_bounds__(kPlColThreads) void k_pme_xconv(PlaneGeom g, PlaneD
     C* buf = reinterpret_cast<C*>(pl_smem);
     C* tw = buf + g.K0 * g.kl;
     const unsigned xs = (unsigned)(g.K1 * g.ks);   // stride of x in G
-    C* base = gc + (size_t)ky * g.ks + kz0;
+    C* base = (blockIdx.y ? gc1 : gc) + (size_t)ky * g.ks + kz0;
     first_stage_cols<-1>(base, xs, buf, dx.rad[0], g, g.K0);
     for (int i = threadIdx.x; i < g.K0; i += blockDim.x)
         tw[i] = roots_x[i];
@@ -527,7 +533,7 @@ __global__ __launch_bounds__(NT, sizeof(R) == 8 ? 4 : 1) void k_pme_z_gather(Pla
     const int tid = threadIdx.x;
     const int item = xcd_remap(blockIdx.x, gridDim.x);
     const int c = item / g.K0, x = item - c * g.K0;
-    const RowChunk rc(g, c);
+    const RowChunk rc(g, c, g.Pc);
     const int nrows = rc.yb - rc.ya + 4, npl = (nrows + 1) / 2;
     C* pl = reinterpret_cast<C*>(pl_smem);
     C* tw_z = pl + (g.Pc + 2) * g.S;
@@ -630,6 +636,193 @@ __global__ __launch_bounds__(NT, sizeof(R) == 8 ? 4 : 1) void k_pme_z_gather(Pla
             const R tx0 = pick5(x0, tq[u]), tx1 = pick5(x1, tq[u]);
             part[(size_t)tq[u] * g.npad + rec[u].x] = R4{tx1 * ax, tx0 * ay, tx0 * az, (R)0};
         }
+    }
+}
+
+// Weights of the gradient's interpolation: B-spline values and derivatives up to the third, the
+// k-th times scale^k (polynomial pieces as in spline5; the third derivatives are linear).
+__device__ __forceinline__ void spline5_third(double w, double scale, double (&m0)[5], double (&m1)[5],
+                                              double (&m2)[5], double (&m3)[5])
+{
+    spline5<double, true>(w, m0, m1, m2);
+    const double v = 1.0 - w;
+    m3[0] = w;
+    m3[1] = 1.0 - 4.0 * w;
+    m3[2] = 6.0 * w - 3.0;
+    m3[3] = 4.0 * v - 1.0;
+    m3[4] = -v;
+    const double s2 = scale * scale;
+#pragma unroll
+    for (int t = 0; t < 5; ++t) {
+        m1[t] *= scale;
+        m2[t] *= s2;
+        m3[t] *= s2 * scale;
+    }
+}
+
+// Pass 5 of the polarization gradient: workgroup (row chunk c, plane x) of two transformed grids,
+// the potentials psi_p of the multipoles (gp) and psi_m of the dipoles (gm).  Each row is one
+// complex line, psi_p in the real and psi_m in the imaginary part, so that a point's two
+// potentials are one LDS read.  Then every atom with fx in x..x+4 and fy in [ya, yb) adds up its
+// share from plane x of
+//   sum_k psi_a(k) (H mu) + psi_m(k) (q grad W + H d + 1/3 sum_bc Theta_bc d_a d_b d_c W),
+//   H_ab = d_a d_b W, psi_a = psi_m + psi_p,
+// in FP64 (weights, sums and the contraction with the multipoles), into part[t npad + s].
+// Bound by FP64 issue (about 550 instructions per atom and plane) beside the two grids' bytes: 79 us
+// at 288,000 atoms beside the pair tiles, 16 us at 23,559 atoms in FP64.
+template <typename R, int NT>
+__global__ __launch_bounds__(NT) void k_pme_z_force(PlaneGeom g, PlaneDim dz,
+                                                    const typename PlT<R>::C* __restrict__ gp,
+                                                    const typename PlT<R>::C* __restrict__ gm,
+                                                    const int* __restrict__ xy_start,
+                                                    const int4* __restrict__ xb_rec,
+                                                    const double4* __restrict__ pos_s,
+                                                    const typename PlT<R>::C* __restrict__ roots_z,
+                                                    const double4* __restrict__ mp, const double* __restrict__ mu,
+                                                    double4* __restrict__ part)
+{
+    using C = typename PlT<R>::C;
+    extern __shared__ __align__(16) double pl_smem[];
+    const int tid = threadIdx.x;
+    const int item = xcd_remap(blockIdx.x, gridDim.x);
+    const int c = item / g.K0, x = item - c * g.K0;
+    const RowChunk rc(g, c, g.Pf);
+    const int nrows = rc.yb - rc.ya + 4;
+    C* pl = reinterpret_cast<C*>(pl_smem);
+    C* tw_z = pl + (2 * g.Pf + 4) * g.S;
+    for (int i = tid; i < g.K2; i += NT)
+        tw_z[i] = roots_z[i];
+    with_radix(dz.rad[dz.nr - 1], [&](auto rc_) {
+        constexpr int RAD = decltype(rc_)::value;
+        const int nb = g.K2 / RAD;
+        const SmallDiv dnb(nb);
+        for (int i0 = tid; i0 < nrows * nb; i0 += NT) {
+            const int i = opaque(i0), r = dnb.quot(i), j = i - r * nb;
+            int gy = rc.ya - 4 + r;
+            gy += gy < 0 ? g.K1 : 0;
+            const size_t row = ((size_t)x * g.K1 + gy) * g.ks;
+            C v[RAD];
+#pragma unroll
+            for (int q = 0; q < RAD; ++q) {
+                const int k = j + q * nb;
+                const bool up = k >= g.kh;
+                const int kk = up ? g.K2 - k : k;
+                C a = gp[row + kk], b = gm[row + kk];
+                if (kk == 0 || 2 * kk == g.K2)
+                    a.y = b.y = (R)0;
+                if (up) {
+                    a.y = -a.y;
+                    b.y = -b.y;
+                }
+                v[q] = C{a.x - b.y, a.y + b.x};
+                if (q % kRootGroup == kRootGroup - 1)
+                    __builtin_amdgcn_sched_barrier(0);  // as in rooted_points: bounds the registers
+            }
+            dft<RAD, +1>(v);
+#pragma unroll
+            for (int q = 0; q < RAD; ++q)
+                pl[r * g.S + j * RAD + q] = v[q];
+        }
+    });
+    __syncthreads();
+    mid_stages<+1>(pl, nrows, dz, -1, tw_z, LineMap{g.S, 1});
+    last_stage_rows<+1>(pl, nrows, dz.rad[0], g, tw_z);
+    __syncthreads();
+    BinRanges<5> br;
+    br.pre[0] = 0;
+#pragma unroll
+    for (int t = 0; t < 5; ++t) {
+        int bx = x + t;
+        bx -= bx >= g.K0 ? g.K0 : 0;
+        const int* st = xy_start + (size_t)bx * g.K1;
+        br.lo[t] = st[rc.ya];
+        br.tq[t] = t;
+        br.pre[t + 1] = br.pre[t] + st[rc.yb] - br.lo[t];
+    }
+    const int yorg = rc.ya - 4;
+    for (int i = tid; i < br.total(); i += NT) {
+        int t;
+        const int e = br.entry(i, t);
+        const int4 rec = xb_rec[e];
+        const int s = rec.x;
+        const double4 p = pos_s[s];
+        double y0[5], y1[5], y2[5], y3[5], z0[5], z1[5], z2[5], z3[5];
+        int f;
+        double w;
+        grid_coord(p.z, g.klz, g.K2, f, w);
+        spline5_third(w, g.klz, z0, z1, z2, z3);
+        grid_coord(p.y, g.kly, g.K1, f, w);
+        spline5_third(w, g.kly, y0, y1, y2, y3);
+        int zi[5];
+#pragma unroll
+        for (int tz = 0; tz < 5; ++tz) {
+            zi[tz] = rec.w - tz;
+            zi[tz] += zi[tz] < 0 ? g.K2 : 0;
+        }
+        // plane sums: a_bc (psi_a, b + c <= 2), m_bc (psi_m, b + c <= 3) with b y- and c z-derivatives
+        double a00 = 0, a01 = 0, a02 = 0, a10 = 0, a11 = 0, a20 = 0;
+        double m00 = 0, m01 = 0, m02 = 0, m03 = 0, m10 = 0, m11 = 0, m12 = 0, m20 = 0, m21 = 0, m30 = 0;
+#pragma unroll
+        for (int ty = 0; ty < 5; ++ty) {
+            const C* row = pl + (rec.z - ty - yorg) * g.S;   // rows in [0, nrows): fy lies in [ya, yb)
+            double sa0 = 0, sa1 = 0, sa2 = 0, sm0 = 0, sm1 = 0, sm2 = 0, sm3 = 0;
+#pragma unroll
+            for (int tz = 0; tz < 5; ++tz) {
+                const C u = row[zi[tz]];
+                const double pm = (double)u.y, pa = (double)u.x + pm;
+                sa0 = fma(z0[tz], pa, sa0);
+                sa1 = fma(z1[tz], pa, sa1);
+                sa2 = fma(z2[tz], pa, sa2);
+                sm0 = fma(z0[tz], pm, sm0);
+                sm1 = fma(z1[tz], pm, sm1);
+                sm2 = fma(z2[tz], pm, sm2);
+                sm3 = fma(z3[tz], pm, sm3);
+            }
+            a00 = fma(y0[ty], sa0, a00);
+            a01 = fma(y0[ty], sa1, a01);
+            a02 = fma(y0[ty], sa2, a02);
+            a10 = fma(y1[ty], sa0, a10);
+            a11 = fma(y1[ty], sa1, a11);
+            a20 = fma(y2[ty], sa0, a20);
+            m00 = fma(y0[ty], sm0, m00);
+            m01 = fma(y0[ty], sm1, m01);
+            m02 = fma(y0[ty], sm2, m02);
+            m03 = fma(y0[ty], sm3, m03);
+            m10 = fma(y1[ty], sm0, m10);
+            m11 = fma(y1[ty], sm1, m11);
+            m12 = fma(y1[ty], sm2, m12);
+            m20 = fma(y2[ty], sm0, m20);
+            m21 = fma(y2[ty], sm1, m21);
+            m30 = fma(y3[ty], sm0, m30);
+        }
+        double X0, X1, X2, X3;
+        {
+            double x0[5], x1[5], x2[5], x3[5];
+            grid_coord(p.x, g.klx, g.K0, f, w);
+            spline5_third(w, g.klx, x0, x1, x2, x3);
+            X0 = pick5(x0, t);
+            X1 = pick5(x1, t);
+            X2 = pick5(x2, t);
+            X3 = pick5(x3, t);
+        }
+        const double ux = mu[3 * (size_t)s], uy = mu[3 * (size_t)s + 1], uz = mu[3 * (size_t)s + 2];
+        const double4 q0 = mp[3 * (size_t)s], q1 = mp[3 * (size_t)s + 1], q2 = mp[3 * (size_t)s + 2];
+        const double q = q0.x, dx = q0.y, dy = q0.z, dz_ = q0.w;
+        const double third = 1.0 / 3.0;
+        const double txx = third * q1.x, txy = 2.0 * third * q1.y, txz = 2.0 * third * q1.z, tyy = third * q1.w,
+                     tyz = 2.0 * third * q2.x, tzz = third * q2.y;
+        // second derivatives of psi_a and of psi_m on this plane
+        const double hxx = X2 * a00, hxy = X1 * a10, hxz = X1 * a01, hyy = X0 * a20, hyz = X0 * a11, hzz = X0 * a02;
+        const double kxx = X2 * m00, kxy = X1 * m10, kxz = X1 * m01, kyy = X0 * m20, kyz = X0 * m11, kzz = X0 * m02;
+        double4 o;
+        o.x = hxx * ux + hxy * uy + hxz * uz + q * X1 * m00 + kxx * dx + kxy * dy + kxz * dz_ + txx * X3 * m00 +
+              X2 * (txy * m10 + txz * m01) + X1 * (tyy * m20 + tyz * m11 + tzz * m02);
+        o.y = hxy * ux + hyy * uy + hyz * uz + q * X0 * m10 + kxy * dx + kyy * dy + kyz * dz_ + txx * X2 * m10 +
+              X1 * (txy * m20 + txz * m11) + X0 * (tyy * m30 + tyz * m21 + tzz * m12);
+        o.z = hxz * ux + hyz * uy + hzz * uz + q * X0 * m01 + kxz * dx + kyz * dy + kzz * dz_ + txx * X2 * m01 +
+              X1 * (txy * m11 + txz * m02) + X0 * (tyy * m21 + tyz * m12 + tzz * m03);
+        o.w = 0.0;
+        part[(size_t)t * g.npad + s] = o;
     }
 }
 
@@ -827,6 +1020,7 @@ static int col_threads(const PlaneDim& d, int kc) { return cdiv(kc * (d.n / min_
 
 static size_t lds_spread(const PlaneGeom& g, size_t cs) { return 16 * (size_t)g.Pc * g.S + cs * g.K2; }
 static size_t lds_gather(const PlaneGeom& g, size_t cs) { return cs * ((size_t)(g.Pc + 2) * g.S + g.K2); }
+static size_t lds_force(const PlaneGeom& g, size_t cs) { return cs * ((size_t)(2 * g.Pf + 4) * g.S + g.K2); }
 static size_t lds_lines(int N, int kc, size_t cs) { return cs * ((size_t)N * (kc | 1) + N); }
 
 static PlaneGeom plane_geom(const amoeba_ctx* c)
@@ -869,6 +1063,11 @@ static PlaneGeom plane_geom(const amoeba_ctx* c)
             rows(kPlTargetWG);
         }
     }
+    // the gradient's interpolation holds a line per row: row chunks of at most half the pairs
+    g.Pf = cdiv(g.Pc, 2);
+    while (g.Pf > 1 && lds_force(g, cs) > kPlLdsMax)
+        g.Pf = cdiv(g.Pf, 2);
+    g.nyf = cdiv(g.P, g.Pf);
     // column chunks of one line, fewer columns where a pass would exceed the threads or the LDS of
     // a workgroup (lengths far above those of the plane path's usual grids)
     PlaneDim dx, dy;
@@ -911,6 +1110,12 @@ bool plane_eligible(const amoeba_ctx* c)
     return lds_spread(g, cs) <= kPlLdsMax && lds_gather(g, cs) <= kPlLdsMax &&
            g.Pc * (g.K2 / min_radix(d)) <= g.nt && lds_lines(g.K0, g.kc, cs) <= kPlLdsMax &&
            lds_lines(g.K1, g.kc, cs) <= kPlLdsMax && g.nty <= kPlColThreads && g.ntx <= kPlColThreads && (size_t)g.K0 * g.K1 <= 65536;
+}
+
+// Whether the gradient's interpolation fits a workgroup's LDS (a line per row and the halo).
+bool plane_force_fits(const amoeba_ctx* c)
+{
+    return lds_force(plane_geom(c), c->mixed ? sizeof(float2) : sizeof(double2)) <= kPlLdsMax;
 }
 
 int plane_setup(amoeba_ctx* c)
@@ -965,51 +1170,104 @@ int plane_bin_atoms(amoeba_ctx* c)
     return AMOEBA_OK;
 }
 
+// The passes of one reciprocal field, for the two entry points below and the gradient.
+template <typename R> struct PlanePasses {
+    using C = typename PlT<R>::C;
+    using R4 = typename PlT<R>::R4;
+    static constexpr bool FIX = std::is_same<R, float>::value;
+    amoeba_ctx* c;
+    PlaneGeom g;
+    PlaneDim d[3];
+    const C* const* roots;
+    explicit PlanePasses(amoeba_ctx* ctx) : c(ctx), g(plane_geom(ctx)), roots((const C* const*)ctx->pl_roots)
+    {
+        for (int a = 0; a < 3; ++a)
+            plane_factor(c->K[a], d[a]);
+    }
+    bool small() const { return g.nt == kPlThreads; }
+    void spread(const R4* src, int sstride, bool perm, C* gc, int ud) const
+    {
+        auto k = perm ? (small() ? k_pme_spread_z<R, FIX, true, kPlThreads>
+                                 : k_pme_spread_z<R, FIX, true, kPlThreadsLarge>)
+                      : (small() ? k_pme_spread_z<R, FIX, false, kPlThreads>
+                                 : k_pme_spread_z<R, FIX, false, kPlThreadsLarge>);
+        hipLaunchKernelGGL(k, dim3(g.K0 * g.nyc), dim3(g.nt), lds_spread(g, sizeof(C)), c->stream, g, d[2],
+                           c->xb_start, c->xb_rec, (const R4*)c->xb_w, src, sstride, roots[2], gc, c->sc, ud);
+    }
+    // y, x with the influence function and y back, of gc (and gc1 when given)
+    void transforms(C* gc, C* gc1, int ud) const
+    {
+        const int ng = gc1 ? 2 : 1;
+        const size_t ly = lds_lines(g.K1, g.kc, sizeof(C)), lx = lds_lines(g.K0, g.kc, sizeof(C));
+        hipLaunchKernelGGL((k_pme_ylines<R, -1>), dim3(g.K0 * g.nkc, ng), dim3(g.nty), ly, c->stream, g, d[1], gc,
+                           gc1, roots[1], c->sc, ud);
+        hipLaunchKernelGGL(k_pme_xconv<R>, dim3(g.K1 * g.nkc, ng), dim3(g.ntx), lx, c->stream, g, d[0], gc, gc1,
+                           (const R*)c->theta_pl, roots[0], c->sc, ud);
+        hipLaunchKernelGGL((k_pme_ylines<R, 1>), dim3(g.K0 * g.nkc, ng), dim3(g.nty), ly, c->stream, g, d[1], gc,
+                           gc1, roots[1], c->sc, ud);
+    }
+    void gather(const C* gc, int ud) const
+    {
+        auto k = small() ? k_pme_z_gather<R, kPlThreads> : k_pme_z_gather<R, kPlThreadsLarge>;
+        hipLaunchKernelGGL(k, dim3(g.K0 * g.nyc), dim3(g.nt), lds_gather(g, sizeof(C)), c->stream, g, d[2], gc,
+                           c->xb_start, c->xb_rec, (const R4*)c->xb_w, roots[2], (R4*)c->rec_part, c->sc, ud);
+    }
+};
+
 // part 1: the spread pass; part 2: the transforms and the interpolation; 3: both.  perm: spread
 // the permanent multipoles (mp) instead of the direction, all stages timed as AMOEBA_T_PERM.
 template <typename R> static void plane_field_t(amoeba_ctx* c, bool use_done, int parts, bool perm)
 {
-    using C = typename PlT<R>::C;
-    using R4 = typename PlT<R>::R4;
-    const PlaneGeom g = plane_geom(c);
-    PlaneDim d[3];
-    for (int a = 0; a < 3; ++a)
-        plane_factor(c->K[a], d[a]);
-    const size_t cs = sizeof(C);
-    hipStream_t st = c->stream;
+    using P = PlanePasses<R>;
+    const P p(c);
     const int ud = use_done ? 1 : 0;
-    const C* const* roots = (const C* const*)c->pl_roots;
-    C* gc = (C*)c->grid_c;
-    const dim3 nt(g.nt);
-    const bool small = g.nt == kPlThreads;
-    constexpr bool FIX = std::is_same<R, float>::value;
+    typename P::C* gc = (typename P::C*)c->grid_c;
     if (parts & 1) {
         StageTimer tm(c, perm ? AMOEBA_T_PERM : AMOEBA_T_SPREAD);
-        const R4* src = perm ? (c->mixed ? (const R4*)c->mp_f : (const R4*)c->mp_d)
-                             : (c->mixed ? (const R4*)c->pv_f : (const R4*)c->pv_d);
-        auto k = perm ? (small ? k_pme_spread_z<R, FIX, true, kPlThreads> : k_pme_spread_z<R, FIX, true, kPlThreadsLarge>)
-                      : (small ? k_pme_spread_z<R, FIX, false, kPlThreads>
-                               : k_pme_spread_z<R, FIX, false, kPlThreadsLarge>);
-        hipLaunchKernelGGL(k, dim3(g.K0 * g.nyc), nt, lds_spread(g, cs), st, g, d[2], c->xb_start, c->xb_rec,
-                           (const R4*)c->xb_w, src, roots[2], gc, c->sc, perm ? 0 : ud);
+        const void* src = perm ? (c->mixed ? (const void*)c->mp_f : (const void*)c->mp_d)
+                               : (c->mixed ? (const void*)c->pv_f : (const void*)c->pv_d);
+        p.spread((const typename P::R4*)src, perm ? 3 : 1, perm, gc, perm ? 0 : ud);
     }
     if (!(parts & 2))
         return;
     {
         StageTimer tm(c, perm ? AMOEBA_T_PERM : AMOEBA_T_FFT);
-        hipLaunchKernelGGL((k_pme_ylines<R, -1>), dim3(g.K0 * g.nkc), dim3(g.nty), lds_lines(g.K1, g.kc, cs), st, g, d[1], gc,
-                           roots[1], c->sc, ud);
-        hipLaunchKernelGGL(k_pme_xconv<R>, dim3(g.K1 * g.nkc), dim3(g.ntx), lds_lines(g.K0, g.kc, cs), st, g, d[0], gc,
-                           (const R*)c->theta_pl, roots[0], c->sc, ud);
-        hipLaunchKernelGGL((k_pme_ylines<R, 1>), dim3(g.K0 * g.nkc), dim3(g.nty), lds_lines(g.K1, g.kc, cs), st, g, d[1], gc,
-                           roots[1], c->sc, ud);
+        p.transforms(gc, nullptr, ud);
     }
-    {
-        StageTimer tm(c, perm ? AMOEBA_T_PERM : AMOEBA_T_GATHER);
-        auto k = small ? k_pme_z_gather<R, kPlThreads> : k_pme_z_gather<R, kPlThreadsLarge>;
-        hipLaunchKernelGGL(k, dim3(g.K0 * g.nyc), nt, lds_gather(g, cs), st, g, d[2], (const C*)gc, c->xb_start,
-                           c->xb_rec, (const R4*)c->xb_w, roots[2], (R4*)c->rec_part, c->sc, ud);
-    }
+    StageTimer tm(c, perm ? AMOEBA_T_PERM : AMOEBA_T_GATHER);
+    p.gather(gc, ud);
+}
+
+// Complex values of one half grid of the plane path (a second one is the gradient's workspace).
+size_t plane_grid_bytes(const amoeba_ctx* c)
+{
+    return (size_t)c->K[0] * c->K[1] * plane_row_stride(c) * 2 * (c->mixed ? sizeof(float) : sizeof(double));
+}
+
+// Reciprocal shares of the polarization gradient (part[5][npad], FP64): both potentials, then
+// their interpolation.  src: [npad][4] (R4) multipoles and dipoles (the ForceKind records); grid1:
+// a second half grid.
+template <typename R> static void plane_force_t(amoeba_ctx* c, const void* src, void* grid1, double4* part)
+{
+    using P = PlanePasses<R>;
+    using C = typename P::C;
+    const P p(c);
+    const typename P::R4* s4 = (const typename P::R4*)src;
+    C *gp = (C*)c->grid_c, *gm = (C*)grid1;
+    p.spread(s4, 4, true, gp, 0);
+    p.spread(s4 + 3, 4, false, gm, 0);
+    p.transforms(gp, gm, 0);
+    hipLaunchKernelGGL((k_pme_z_force<R, kPlThreadsLarge>), dim3(p.g.K0 * p.g.nyf), dim3(kPlThreadsLarge),
+                       lds_force(p.g, sizeof(C)), c->stream, p.g, p.d[2], (const C*)gp, (const C*)gm, c->xb_start,
+                       c->xb_rec, c->pos_s, p.roots[2], (const double4*)c->mp_d, c->v_mu, part);
+}
+
+void plane_force(amoeba_ctx* c, const void* src, void* grid1, double4* part)
+{
+    if (c->mixed)
+        plane_force_t<float>(c, src, grid1, part);
+    else
+        plane_force_t<double>(c, src, grid1, part);
 }
 
 void plane_dipole_field(amoeba_ctx* c, bool use_done, int parts)

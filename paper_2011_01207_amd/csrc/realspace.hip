@@ -266,10 +266,11 @@ __device__ __forceinline__ double fma_r(double a, double b, double c) { return f
 template <typename R> struct DipoleKind {
     using R4 = typename V4<R>::T;
     static constexpr int NV = 1;
+    static constexpr int kMinWaves = 1;  // waves per SIMD the registers have to leave room for
     // the j-field is linear in the i dipole (d[0].xyz) and the i-field in the j dipole, and
     // nothing else of the pair uses them, so with integer sums both are held times 2^38 and
     // both fields come out scaled
-    static constexpr bool kScaledJ = true;
+    static constexpr bool kScaledJ = true, kScaleJSrc = true;
     __device__ static void scale_i(R4* d, R f)
     {
         d[0].x *= f;
@@ -329,7 +330,7 @@ template <typename R> struct MultipoleKind {
     // the j-field is linear in the i multipoles (everything but the Thole factor d[2].z) and
     // the i-field in the j multipoles, which nothing else of the pair uses: held times 2^38
     // with integer sums, as for the dipoles
-    static constexpr bool kScaledJ = true;
+    static constexpr bool kScaledJ = true, kScaleJSrc = true;
     static constexpr bool kParamsInSrc = false;
     __device__ static void scale_i(R4* d, R f)
     {
@@ -345,6 +346,7 @@ template <typename R> struct MultipoleKind {
         d[2].y *= f;
     }
     static constexpr int NV = 3;
+    static constexpr int kMinWaves = 1;
     __device__ static void load(const R4* src, size_t s, R a, R4* d)
     {
         d[0] = src[3 * s];
@@ -468,10 +470,31 @@ __device__ __forceinline__ void force_pair(T rx, T ry, T rz, T aij, T wij, const
 
 template <typename R> struct ForceKind {
     using R4 = typename V4<R>::T;
-    static constexpr bool kScaledJ = false;
+    // every term of G holds one i factor (a multipole or the dipole) and one j factor, so scaling
+    // the i sources alone scales both sums
+    static constexpr bool kScaledJ = true, kScaleJSrc = false;
     static constexpr bool kParamsInSrc = false;
-    __device__ static void scale_i(R4*, R) {}
+    __device__ static void scale_i(R4* d, R f)
+    {
+        d[0].x *= f;
+        d[0].y *= f;
+        d[0].z *= f;
+        d[0].w *= f;
+        d[1].x *= f;
+        d[1].y *= f;
+        d[1].z *= f;
+        d[1].w *= f;
+        d[2].x *= f;
+        d[2].y *= f;
+        d[3].x *= f;
+        d[3].y *= f;
+        d[3].z *= f;
+    }
     static constexpr int NV = 4;
+    // FP32: 128 registers (the FP64 branch of near-coincident pairs, rarely taken, spills instead),
+    // so that the four workgroups whose LDS fits a CU run at once (288,000 atoms: gradient of two
+    // configurations 1.25 -> 1.19 ms)
+    static constexpr int kMinWaves = sizeof(R) == 4 ? 4 : 1;
     __device__ static void load(const R4* src, size_t s, R a, R4* d)
     {
         d[0] = src[4 * s];
@@ -489,7 +512,7 @@ template <typename R> struct ForceKind {
         const R aij = di[2].z < dj[2].z ? di[2].z : dj[2].z;
         const R wij = ip.w * jp.w;
         R G[3];
-        if (sizeof(R) == 4 && dx * dx + dy * dy + dz * dz < kCloseR2) {
+        if (__builtin_expect(sizeof(R) == 4 && dx * dx + dy * dy + dz * dz < kCloseR2, 0)) {
             // FP32 cannot resolve B_n' of a near-coincident pair (see close_pair_series): such a
             // pair is evaluated in FP64 from the same displacement
             double Gd[3];
@@ -519,7 +542,7 @@ template <typename R> struct ForceKind {
 // evaluated as with kCoefCompute (the store did not fit); record and replay agree on which.
 // ------------------------------------------------------------------------------------------
 template <typename R, bool FIX, class K, bool MI, int CM = kCoefCompute>
-__global__ __launch_bounds__(256) void k_block_tiles(int nb, const int* __restrict__ blk_tile0,
+__global__ __launch_bounds__(256, K::kMinWaves) void k_block_tiles(int nb, const int* __restrict__ blk_tile0,
                                                      const int* __restrict__ tile_np,
                                                      const int* __restrict__ tile_j,
                                                      const unsigned long long* __restrict__ tile_mask,
@@ -630,7 +653,7 @@ __global__ __launch_bounds__(256) void k_block_tiles(int nb, const int* __restri
             // with integer sums the i-field of a row is linear in the j sources, so they are held
             // times 2^38 as the i sources are, and a row's i-field goes to the accumulator
             // pre-scaled too
-            if constexpr (SJ)
+            if constexpr (SJ && K::kScaleJSrc)
                 K::scale_i(d, (R)kFixQScaleF);
 #pragma unroll
             for (int v = 0; v < NV; ++v)
@@ -951,17 +974,17 @@ template <bool MI> static void perm_tiles(amoeba_ctx* c, hipStream_t st)
                            (const int*)nullptr, 0ll, (double2*)nullptr);
 }
 
-template <bool MI> static void force_tiles(amoeba_ctx* c, const void* src)
+template <bool MI> static void force_tiles(amoeba_ctx* c, const void* src, hipStream_t st)
 {
     if (c->mixed)
         hipLaunchKernelGGL((k_block_tiles<float, true, ForceKind<float>, MI>), dim3(c->nb), dim3(256), 0,
-                           c->stream, c->nb, c->blk_tile0, c->tile_np, c->tile_j, c->tile_mask, c->tile_walk,
+                           st, c->nb, c->blk_tile0, c->tile_np, c->tile_j, c->tile_mask, c->tile_walk,
                            c->jrel_f, c->off_f,
                            c->par_f, (const float4*)src, make_ewald<float>(c), c->eipart, (float*)c->jbuf, c->sc, 0,
                            (const int*)nullptr, 0ll, (float2*)nullptr);
     else
         hipLaunchKernelGGL((k_block_tiles<double, false, ForceKind<double>, MI>), dim3(c->nb), dim3(256), 0,
-                           c->stream, c->nb, c->blk_tile0, c->tile_np, c->tile_j, c->tile_mask, c->tile_walk,
+                           st, c->nb, c->blk_tile0, c->tile_np, c->tile_j, c->tile_mask, c->tile_walk,
                            c->jrel_d, c->off_d,
                            c->par_d, (const double4*)src, make_ewald<double>(c), c->eipart, (double*)c->jbuf, c->sc,
                            0, (const int*)nullptr, 0ll, (double2*)nullptr);
@@ -969,16 +992,16 @@ template <bool MI> static void force_tiles(amoeba_ctx* c, const void* src)
 
 // Real-space pair sums of the polarization gradient, sum_j G_ij per slot, into out (FP64 N x 3);
 // src: [npad][4] (R4) multipoles and dipoles in the ForceKind layout.
-void launch_force_tiles(amoeba_ctx* c, const void* src, double* out)
+void launch_force_tiles(amoeba_ctx* c, const void* src, double* out, hipStream_t st)
 {
     if (c->ntiles > 0) {
         if (c->skip_mimg)
-            force_tiles<false>(c, src);
+            force_tiles<false>(c, src, st);
         else
-            force_tiles<true>(c, src);
-        launch_real_reduce(c, out, c->stream);
+            force_tiles<true>(c, src, st);
+        launch_real_reduce(c, out, st);
     } else {
-        hipMemsetAsync(out, 0, sizeof(double) * 3 * (size_t)c->npad, c->stream);
+        hipMemsetAsync(out, 0, sizeof(double) * 3 * (size_t)c->npad, st);
     }
 }
 

@@ -71,3 +71,46 @@ def test_gradient_error_paths():
         assert ei.value.status == amoeba.AMOEBA_E_LIST
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("grid", [(24, 24, 24), (20, 21, 28), (10, 12, 14), (28, 15, 35), (125, 14, 27)],
+                         ids=lambda g: "x".join(map(str, g)))
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_gradient_of_the_plane_path_matches_bricks_and_oracle(grid, prec):
+    """The grid passes of the plane path against the brick path of the same context: odd edges,
+    the smallest sizes, and transforms of three stages."""
+    s = synth.water648()
+    s.grid = grid
+    print(f"[gpu] gradient planes/bricks grid={grid} {prec}", flush=True)
+    mu = 0.05 * np.random.default_rng(3).standard_normal((s.n, 3))
+    g_ref = O.polar_gradient(s, mu, "spme")
+    ctx, t = amoeba.context_for(s, precision=prec, device=DEV)
+    try:
+        m = torch.tensor(mu, device=DEV)
+        g = ctx.polarization_gradient(t["pos"], t["q"], t["dip"], t["quad"], m).cpu().numpy()
+        ctx.set_pme_path("bricks")
+        g_b = ctx.polarization_gradient(t["pos"], t["q"], t["dip"], t["quad"], m).cpu().numpy()
+    finally:
+        ctx.close()
+    assert_fields(g, g_ref, BAR[prec], what="gradient on planes")
+    assert_fields(g, g_b, BAR[prec], what="planes vs bricks")
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_gradient_under_a_workspace_cap_takes_the_brick_path(prec):
+    """A cap that leaves room for the brick path's buffers and not for the planes'."""
+    s = synth.water648()
+    mu = torch.tensor(0.05 * np.random.default_rng(3).standard_normal((s.n, 3)), device=DEV)
+    out, held = [], 0
+    for capped in (False, True):
+        npad, grid = (s.n + 63) // 64 * 64, 24 ** 3
+        need = (96 + 128) * npad + 8 * grid if prec == "fp64" else (96 + 48 + 64) * npad + 4 * grid
+        kw = {"max_workspace_bytes": held + need + 64} if capped else {}
+        ctx, t = amoeba.context_for(s, precision=prec, device=DEV, **kw)
+        try:
+            held = ctx.info()["workspace_bytes"]
+            out.append(ctx.polarization_gradient(t["pos"], t["q"], t["dip"], t["quad"], mu).cpu().numpy())
+            assert ctx.info()["workspace_bytes"] - held > need or capped
+        finally:
+            ctx.close()
+    assert_fields(out[1], out[0], BAR[prec], what="capped vs uncapped")
