@@ -6,6 +6,7 @@
 #include <rocfft/rocfft.h>
 
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -127,6 +128,8 @@ struct RedScratch {
     double* part;
 };
 
+struct PlanePlan;  // plane.hip
+
 struct DeviceBuf {
     void* p = nullptr;
     size_t bytes = 0;
@@ -214,6 +217,7 @@ struct amoeba_ctx {
     void* sp_w = nullptr;          // [npad][32] (R) B-spline weights m0, m1 per dimension
     // dipole reciprocal field by x-planes (plane.hip), used when the grid fits (plane_ok)
     bool plane_ok = false;
+    mutable std::shared_ptr<amoeba::PlanePlan> plane_plan;  // geometry of the plane passes, made on first use
     int pme_path = 0;              // amoeba_pme_path requested by the caller
     bool rec_plane = false;        // the last reciprocal field came from the plane path
     bool brick_bins_stale = true;  // brick bins and spline table not built for the current positions
@@ -373,6 +377,7 @@ void coef_invalidate(amoeba_ctx* c);      // pair coefficients must be recorded 
 int coef_reserve(amoeba_ctx* c);          // size the coefficient store (host has synchronized)
 void coef_release(amoeba_ctx* c);         // free it (other allocations come first under the cap)
 bool coef_store_on(const amoeba_ctx* c);  // the requested mode uses the store
+int begin_coef_mode(amoeba_ctx* c, bool* use_done);  // the mode of the product being enqueued
 int next_coef_mode(const amoeba_ctx* c);  // the next dipole product: 0 evaluates, 1 records, 2 replays
 void launch_real_reduce(amoeba_ctx* c, double* ereal, hipStream_t st = nullptr, bool use_done = false);
 void launch_perm_tiles(amoeba_ctx* c, hipStream_t st = nullptr);
@@ -400,6 +405,9 @@ bool plane_force_fits(const amoeba_ctx* c);
 void plane_force(amoeba_ctx* c, const void* src, void* grid1, double4* part);  // reciprocal gradient shares
 int plane_combine(amoeba_ctx* c, bool use_done, bool dot_pq, bool reduced);  // PCG product; returns its partial count
 bool pme_use_planes(const amoeba_ctx* c);
+bool plane_small_system(const amoeba_ctx* c);
+bool plane_small_product(const amoeba_ctx* c);          // a small system's product (plane.hip)
+void plane_small_product_fields(amoeba_ctx* c, bool use_done);
 void launch_gather(amoeba_ctx* c, double* out);       // E_rec at atoms from the potential grid
 int pme_brick_potential(amoeba_ctx* c, bool perm);    // psi of the multipoles (perm) or of pv, brick path
 
@@ -432,5 +440,6 @@ int pcg_start(amoeba_ctx* c, bool have_guess, double* rms_debye);   // r0, z0, p
 int pcg_start_from(amoeba_ctx* c, const double* q0);                // same, A mu0 given
 int pcg_run(amoeba_ctx* c, int max_iter, int start_matvecs, double* mu_out, double* e_pol);
 int matvec_slot(amoeba_ctx* c, bool use_done, bool dot, hipEvent_t fork_ev = nullptr);  // q = A p
+double self_coefficient(const amoeba_ctx* c);                       // Ewald self field: 4 beta^3 / (3 sqrt(pi))
 
 }  // namespace amoeba

@@ -270,6 +270,164 @@ __global__ __launch_bounds__(256) void k_direction(int npad, int n, const double
     }
 }
 
+// The rest of a small system's iteration in one workgroup of 1024 threads, kSmallSlots slots each:
+// the combine of k_plane_combine (MODE 2) with p.Ap, k_update and k_direction, with the residual and
+// the product in registers between them.  Three launches of about 4 us, each waiting for the one
+// before, become one of 8 us at 648 atoms.  Beyond 2,048 slots one CU's share of the vectors costs
+// more than the launches saved (22 us at 3,810 atoms with four slots a thread).
+constexpr int kSmallSlots = 2;
+constexpr int kSmallMaxSlots = 1024 * kSmallSlots;
+
+template <int NV> __device__ __forceinline__ void block_sum_1024(double (&v)[NV])
+{
+    __shared__ double sh[NV][16];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+            v[k] += __shfl_xor(v[k], off);
+    __syncthreads();
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+            sh[k][w] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        double t = 0.0;
+#pragma unroll
+        for (int m = 0; m < 16; ++m)
+            t += sh[k][m];
+        v[k] = t;
+    }
+}
+
+template <typename R4T>
+__global__ __launch_bounds__(1024) void k_pcg_small(int npad, int n, double3 kl, double self,
+                                                    const int* __restrict__ perm, const R4T* __restrict__ part,
+                                                    const double* __restrict__ alpha,
+                                                    const double* __restrict__ alpha_inv,
+                                                    const double* __restrict__ ereal, double* __restrict__ mu,
+                                                    double* __restrict__ r, double* __restrict__ p,
+                                                    R4T* __restrict__ pv, PcgScalars* __restrict__ sc,
+                                                    PcgScalars* __restrict__ pub, int* __restrict__ range_flags)
+{
+    const int tid = threadIdx.x, it = sc->iters, seq = sc->seq, done = sc->done;
+    const double rz_old = sc->rzb[it & 1], tol = sc->tol;
+    __syncthreads();
+    if (done) {
+        if (tid == 0) {
+            sc->seq = seq + 1;
+            pub[seq & 1] = *sc;
+        }
+        return;
+    }
+    double q[kSmallSlots][3], pp[kSmallSlots][3], rv[kSmallSlots][3];
+    double pq[1] = {0.0};
+    bool out_of_range = false;
+#pragma unroll
+    for (int u = 0; u < kSmallSlots; ++u) {
+        const int s = tid + u * 1024;
+        if (s >= npad)
+            continue;
+        double e[3] = {0.0, 0.0, 0.0};
+        const bool real = perm[s] >= 0;
+#pragma unroll
+        for (int t = 0; t < 5; ++t) {
+            const R4T v = part[(size_t)t * npad + s];
+            e[0] += (double)v.x;
+            e[1] += (double)v.y;
+            e[2] += (double)v.z;
+        }
+        e[0] = -e[0] * kl.x;
+        e[1] = -e[1] * kl.y;
+        e[2] = -e[2] * kl.z;
+        const double ainv = alpha_inv[s];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const size_t i = 3 * (size_t)s + c;
+            const double pa = p[i];
+            pp[u][c] = pa;
+            q[u][c] = real ? pa * ainv - (ereal[i] + e[c] + self * pa) : 0.0;
+            pq[0] += pa * q[u][c];
+            out_of_range |= !(fabs(q[u][c]) < kFixRange);
+        }
+    }
+    block_sum_1024<1>(pq);
+    if (!(pq[0] > 0.0) || !isfinite(pq[0])) {
+        if (tid == 0) {
+            sc->pq = pq[0];
+            sc->done = 1;
+            sc->status = 2;
+            sc->seq = seq + 1;
+            pub[seq & 1] = *sc;
+        }
+        return;
+    }
+    const double g = rz_old / pq[0];
+    double acc[2] = {0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < kSmallSlots; ++u) {
+        const int s = tid + u * 1024;
+        if (s >= npad)
+            continue;
+        const double al = alpha[s];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const size_t i = 3 * (size_t)s + c;
+            mu[i] += g * pp[u][c];
+            rv[u][c] = r[i] - g * q[u][c];
+            const double zv = al * rv[u][c];
+            r[i] = rv[u][c];
+            acc[0] += rv[u][c] * zv;
+            acc[1] += zv * zv;
+        }
+    }
+    block_sum_1024<2>(acc);
+    const double rms = kDebye * sqrt(acc[1] / n);
+    const bool conv = rms < tol, bad = !isfinite(acc[0]);
+    const double beta = acc[0] / rz_old;
+    if (tid == 0) {
+        sc->pq = pq[0];
+        sc->gamma = g;
+        sc->rms = rms;
+        sc->rms_sum += rms;
+        sc->zz = acc[1];
+        sc->iters = it + 1;
+        if (conv) {
+            sc->done = 1;
+            sc->status = 1;
+        } else if (bad) {
+            sc->done = 1;
+            sc->status = 2;
+        } else {
+            sc->rzb[(it + 1) & 1] = acc[0];
+            sc->beta = beta;
+        }
+        sc->seq = seq + 1;
+        pub[seq & 1] = *sc;
+    }
+    if (range_flags && __syncthreads_or(out_of_range) && tid == 0)
+        atomicOr(range_flags, kFlagOverflow);
+    if (conv || bad)
+        return;
+#pragma unroll
+    for (int u = 0; u < kSmallSlots; ++u) {
+        const int s = tid + u * 1024;
+        if (s >= npad)
+            continue;
+        const double al = alpha[s];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const size_t i = 3 * (size_t)s + c;
+            const double v = al * rv[u][c] + beta * pp[u][c];
+            p[i] = v;
+            Comp<R4T>::set(pv, i, v);
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void k_epol(int npad, const double* __restrict__ mu, const double* __restrict__ e,
                                               double* __restrict__ part)
 {
@@ -292,6 +450,12 @@ __global__ __launch_bounds__(256) void k_epol_finalize(int nparts, const double*
 }
 
 static inline int nblk(size_t n, int b) { return (int)((n + b - 1) / b); }
+
+double self_coefficient(const amoeba_ctx* c)
+{
+    const double b = c->prm.ewald_alpha;
+    return 4.0 * b * b * b / (3.0 * sqrt(kPi));
+}
 
 void launch_gather_vec(amoeba_ctx* c, const double* src_caller, double* dst_slot)
 {
@@ -331,10 +495,18 @@ static double* part_vec(amoeba_ctx* c) { return c->red.part + ((size_t)c->npq_ca
 // while the reciprocal transforms and the interpolation (latency bound) run on the context
 // stream, so that the two share the CUs; the combine waits for both.  Stage timing keeps
 // everything on the context stream so that each stage is timed alone.
+// A small system's product (plane_small_product) is launch bound: it takes four launches on the
+// context stream instead.
 // fork_ev: an event already recorded at the current end of the context stream (the PCG loop's
 // per-iteration event), used as the fork point instead of recording another one.
 int matvec_slot(amoeba_ctx* c, bool use_done, bool dot, hipEvent_t fork_ev)
 {
+    if (plane_small_product(c)) {
+        c->rec_plane = true;
+        plane_small_product_fields(c, use_done);
+        launch_matvec_combine(c, use_done, dot, true);
+        return AMOEBA_OK;
+    }
     if (pme_use_planes(c) && !c->timing) {
         c->rec_plane = true;
         if (!fork_ev) {
@@ -374,6 +546,28 @@ static void launch_init_residual(amoeba_ctx* c, const double* q, int it)
 
 static int enqueue_iteration_direct(amoeba_ctx* c, hipEvent_t fork_ev)
 {
+    if (c->npad <= kSmallMaxSlots && plane_small_system(c)) {
+        // the same sums in the same order with stage timers as without
+        c->rec_plane = true;
+        if (plane_small_product(c)) {
+            plane_small_product_fields(c, true);
+        } else {
+            launch_mutual_tiles(c, true, c->stream);
+            plane_dipole_field(c, true, 3);
+            launch_real_reduce(c, c->ereal, c->stream, true);
+        }
+        StageTimer tm(c, AMOEBA_T_PCG);
+        const double3 kl = make_double3(c->K[0] / c->prm.box[0], c->K[1] / c->prm.box[1], c->K[2] / c->prm.box[2]);
+        if (c->mixed)
+            hipLaunchKernelGGL(k_pcg_small<float4>, dim3(1), dim3(1024), 0, c->stream, c->npad, c->n, kl,
+                               self_coefficient(c), c->perm, (const float4*)c->rec_part, c->alpha_s, c->alpha_inv_s,
+                               c->ereal, c->v_mu, c->v_r, c->v_p, c->pv_f, c->sc, c->sc_host_dev, c->flags);
+        else
+            hipLaunchKernelGGL(k_pcg_small<double4>, dim3(1), dim3(1024), 0, c->stream, c->npad, c->n, kl,
+                               self_coefficient(c), c->perm, (const double4*)c->rec_part, c->alpha_s, c->alpha_inv_s,
+                               c->ereal, c->v_mu, c->v_r, c->v_p, c->pv_d, c->sc, c->sc_host_dev, (int*)nullptr);
+        return AMOEBA_OK;
+    }
     int rc = matvec_slot(c, true, true, fork_ev);
     if (rc)
         return rc;

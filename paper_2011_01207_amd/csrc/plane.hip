@@ -34,6 +34,7 @@
 #include "plane_fft.h"
 #include "reduce.h"
 #include "spline.h"
+#include "tiles.h"
 
 namespace amoeba {
 
@@ -46,6 +47,7 @@ constexpr int kPlThreadsLarge = 256;    // the same on large grids, in smaller r
 constexpr int kPlLargeWG = 1024;        // row-chunk workgroups of 512 threads above which a grid is large
 constexpr int kPlTargetWGLarge = 3456;  // row-chunk workgroups the chunking aims at on a large grid
 constexpr int kPlColThreads = 512;      // threads per workgroup of the column passes at most
+constexpr int kPlYxyThreads = 1024;     // threads per workgroup of the one-launch y-x-y pass at most
 constexpr size_t kPlLdsMax = 64 * 1024; // LDS of one workgroup
 constexpr int kPlTargetWG = 432;        // workgroups per row-chunk pass the chunking aims at
 // Wave priority of the transform and interpolation passes: they run beside the real-space tiles
@@ -167,23 +169,16 @@ __device__ __forceinline__ void last_stage_rows(C* pl, int nl, int rad, const Pl
 // Then every row pair is transformed along z, separated into the two rows' half spectra, and
 // the rows are written to G[x][y][0, kh).
 template <typename R, bool FIX, bool PERM, int NT>
-__global__ __launch_bounds__(NT) void k_pme_spread_z(PlaneGeom g, PlaneDim dz,
-                                                             const int* __restrict__ xy_start,
-                                                             const int4* __restrict__ xb_rec,
-                                                             const typename PlT<R>::R4* __restrict__ xb_w,
-                                                             const typename PlT<R>::R4* __restrict__ src,
-                                                             int sstride,
-                                                             const typename PlT<R>::C* __restrict__ roots_z,
-                                                             typename PlT<R>::C* __restrict__ gout,
-                                                             const PcgScalars* __restrict__ sc, int use_done)
+__device__ __forceinline__ void spread_z(double* pl_smem, int item, const PlaneGeom& g, const PlaneDim& dz,
+                                         const int* __restrict__ xy_start, const int4* __restrict__ xb_rec,
+                                         const typename PlT<R>::R4* __restrict__ xb_w,
+                                         const typename PlT<R>::R4* __restrict__ src, int sstride,
+                                         const typename PlT<R>::C* __restrict__ roots_z,
+                                         typename PlT<R>::C* __restrict__ gout)
 {
     using C = typename PlT<R>::C;
     using R4 = typename PlT<R>::R4;
-    extern __shared__ __align__(16) double pl_smem[];
-    if (use_done && sc->done)
-        return;
     const int tid = threadIdx.x;
-    const int item = xcd_remap(blockIdx.x, gridDim.x);
     const int c = item / g.K0, x = item - c * g.K0;
     const RowChunk rc(g, c, g.Pc);
     const int n2 = 2 * rc.np * g.S;                    // doubles of the chunk's accumulation
@@ -356,6 +351,71 @@ __global__ __launch_bounds__(NT) void k_pme_spread_z(PlaneGeom g, PlaneDim dz,
     }
 }
 
+template <typename R, bool FIX, bool PERM, int NT>
+__global__ __launch_bounds__(NT) void k_pme_spread_z(PlaneGeom g, PlaneDim dz, const int* __restrict__ xy_start,
+                                                     const int4* __restrict__ xb_rec,
+                                                     const typename PlT<R>::R4* __restrict__ xb_w,
+                                                     const typename PlT<R>::R4* __restrict__ src, int sstride,
+                                                     const typename PlT<R>::C* __restrict__ roots_z,
+                                                     typename PlT<R>::C* __restrict__ gout,
+                                                     const PcgScalars* __restrict__ sc, int use_done)
+{
+    extern __shared__ __align__(16) double pl_smem[];
+    if (use_done && sc->done)
+        return;
+    spread_z<R, FIX, PERM, NT>(pl_smem, xcd_remap(blockIdx.x, gridDim.x), g, dz, xy_start, xb_rec, xb_w, src, sstride,
+                               roots_z, gout);
+}
+
+// A small system's dipole product starts with one launch for the two halves that need nothing of
+// each other: workgroups 0 .. nb - 1 take a block's tiles (eight waves each, so that a wave walks
+// about one tile), the others a row chunk of the spread.
+template <typename R> struct HeadTiles {
+    using R4 = typename PlT<R>::R4;
+    int nb;
+    const int *blk_tile0, *tile_np, *tile_j;
+    const unsigned long long* tile_mask;
+    const uint16_t* tile_walk;
+    const R4 *jrel, *off, *par;
+    EwaldArgs<R> ew;
+    double* eipart;
+    R* jbuf;
+    const int* coef_row0;
+    long long coef_cap_rows;
+    typename V2<R>::T* coef;
+    int use_done;
+};
+constexpr int kHeadWaves = kPlThreads / 64;
+
+template <typename R, bool MI, int CM>
+__global__ __launch_bounds__(kPlThreads) void k_product_head(HeadTiles<R> t, PlaneGeom g, PlaneDim dz,
+                                                             const int* __restrict__ xy_start,
+                                                             const int4* __restrict__ xb_rec,
+                                                             const typename PlT<R>::R4* __restrict__ xb_w,
+                                                             const typename PlT<R>::R4* __restrict__ src,
+                                                             const typename PlT<R>::C* __restrict__ roots_z,
+                                                             typename PlT<R>::C* __restrict__ gout,
+                                                             const PcgScalars* __restrict__ sc, int use_done)
+{
+    constexpr bool FIX = std::is_same<R, float>::value;
+    extern __shared__ __align__(16) double pl_smem[];
+    const int b = blockIdx.x;
+    if (b < t.nb) {
+        if (t.use_done && sc->done)
+            return;
+        using L = TileLds<R, FIX, DipoleKind<R>, kHeadWaves>;
+        block_tiles<R, FIX, DipoleKind<R>, MI, CM, kHeadWaves>(*reinterpret_cast<L*>(pl_smem), b, t.blk_tile0,
+                                                               t.tile_np, t.tile_j, t.tile_mask, t.tile_walk, t.jrel,
+                                                               t.off, t.par, src, t.ew, t.eipart, t.jbuf, t.coef_row0,
+                                                               t.coef_cap_rows, t.coef);
+    } else {
+        if (use_done && sc->done)
+            return;
+        spread_z<R, FIX, false, kPlThreads>(pl_smem, xcd_remap(b - t.nb, gridDim.x - t.nb), g, dz, xy_start, xb_rec,
+                                            xb_w, src, 1, roots_z, gout);
+    }
+}
+
 // First and last stage of a column pass: thread (column col, butterfly j), the workgroup holding
 // every butterfly.  The first reads the butterfly's points from src (point stride ss) and leaves
 // its outputs in LDS; the last takes them from LDS to dst.  Offsets from the two bases stay below
@@ -504,6 +564,129 @@ __global__ __launch_bounds__(kPlColThreads) void k_pme_xconv(PlaneGeom g, PlaneD
     __syncthreads();
     mid_stages<+1>(buf, g.kc, dx, -1, tw, am);
     last_stage_cols<+1>(buf, base, xs, dx.rad[0], g, g.K0, tw);
+}
+
+// Passes 2 to 4 in one launch for a small grid: workgroup kz (and grid, the y index of the launch)
+// holds that column's K0 x K1 points in LDS, one butterfly per thread in every stage.  A stage whose
+// outputs take other places than its points has a barrier between its reads and its writes; the
+// last stage of a transform replaces its own points.
+template <int SIGN, bool LAST, int W, typename C, typename IN, typename OUT>
+__device__ __forceinline__ void yxy_stage(int rad, int N, int nl, const C* tw, IN in, OUT out)
+{
+    // LAST: roots on the way in, outputs to j + q N/RAD; else outputs to j RAD + q.  Thread index:
+    // W = 0 butterflies fastest (lines are rows of the plane), 1 lines fastest (columns).
+    with_radix(rad, [&](auto rc_) {
+        constexpr int RAD = decltype(rc_)::value;
+        const int nb = N / RAD, it = opaque(threadIdx.x);
+        const SmallDiv dv(W == 0 ? nb : nl);
+        const int hi = dv.quot(it), lo = it - hi * (W == 0 ? nb : nl);
+        const int l = W == 0 ? hi : lo, j = W == 0 ? lo : hi;
+        const bool act = it < nl * nb;
+        C v[RAD];
+        if (act) {
+            if constexpr (LAST) {
+                rooted_points<RAD, SIGN>(v, tw, j, [&](int r) { return in(l, j + r * nb); });
+            } else {
+#pragma unroll
+                for (int r = 0; r < RAD; ++r)
+                    v[r] = in(l, j + r * nb);
+            }
+            dft<RAD, SIGN>(v);
+        }
+        if constexpr (!LAST)
+            __syncthreads();
+        if (act) {
+#pragma unroll
+            for (int q = 0; q < RAD; ++q)
+                out(l, LAST ? j + q * nb : j * RAD + q, v[q]);
+        }
+    });
+    __syncthreads();
+}
+
+template <typename R> struct RealReduceArgs {
+    int npad;  // 0: none
+    const double* eipart;
+    const R* jbuf;
+    const int *rev_ptr, *rev_idx;
+    double* ereal;
+};
+
+template <typename R>
+__global__ __launch_bounds__(kPlYxyThreads) void k_pme_yxy(PlaneGeom g, PlaneDim dy, PlaneDim dx,
+                                                  typename PlT<R>::C* __restrict__ gc,
+                                                  typename PlT<R>::C* __restrict__ gc1,
+                                                  const R* __restrict__ theta,
+                                                  const typename PlT<R>::C* __restrict__ roots_y,
+                                                  const typename PlT<R>::C* __restrict__ roots_x,
+                                                  RealReduceArgs<R> rr,
+                                                  const PcgScalars* __restrict__ sc, int use_done)
+{
+    using C = typename PlT<R>::C;
+    extern __shared__ __align__(16) double pl_smem[];
+    if (use_done && sc->done)
+        return;
+    const int kz = blockIdx.x, tid = threadIdx.x;
+    if (kz >= g.kh) {  // the workgroups beyond the columns: the real-space reduction of a product
+        const int s = (kz - g.kh) * blockDim.x + tid;
+        if (s < rr.npad)
+            real_reduce<R>(s, rr.eipart, rr.jbuf, rr.rev_ptr, rr.rev_idx, rr.ereal);
+        return;
+    }
+    C* base = (blockIdx.y ? gc1 : gc) + kz;
+    C* buf = reinterpret_cast<C*>(pl_smem);
+    const int lp = g.K1 | 1;
+    C* tw_y = buf + g.K0 * lp;
+    C* tw_x = tw_y + g.K1;
+    auto mem = [&](int x, int y) -> C& { return buf[x * lp + y]; };
+    auto at = [&](int x, int y) { return mem(x, y); };
+    auto to = [&](int x, int y, C v) { mem(x, y) = v; };
+    auto at_t = [&](int y, int x) { return mem(x, y); };
+    auto to_t = [&](int y, int x, C v) { mem(x, y) = v; };
+    auto global = [&](int x, int y) { return (unsigned)((x * g.K1 + y) * g.ks) * (unsigned)sizeof(C); };
+    for (int i = tid; i < g.K1 + g.K0; i += blockDim.x)
+        tw_y[i] = i < g.K1 ? roots_y[i] : roots_x[i - g.K1];
+    // y forward, from the grid
+    yxy_stage<-1, false, 0>(dy.rad[0], g.K1, g.K0, tw_y, [&](int x, int y) { return load_at(base, global(x, y)); }, to);
+    yxy_stage<-1, true, 0>(dy.rad[1], g.K1, g.K0, tw_y, at, to);
+    // x forward, the influence function and the first stage back in registers (as in k_pme_xconv)
+    yxy_stage<-1, false, 1>(dx.rad[0], g.K0, g.K1, tw_x, at_t, to_t);
+    const R* th = theta + (size_t)(kz >> g.kcs) * g.K0 * g.kc + (kz & (g.kc - 1));
+    const unsigned ths = (unsigned)(g.nkc * g.K0 * g.kc);
+    with_radix(dx.rad[1], [&](auto rc_) {
+        constexpr int RAD = decltype(rc_)::value;
+        const int nb = g.K0 / RAD, it = opaque(tid);
+        const SmallDiv dv(g.K1);
+        const int j = dv.quot(it), y = it - j * g.K1;
+        const bool act = it < g.K1 * nb;
+        C v[RAD];
+        if (act) {
+            R f[RAD];
+#pragma unroll
+            for (int q = 0; q < RAD; ++q)
+                f[q] = th[y * ths + (j + q * nb) * g.kc];
+            rooted_points<RAD, -1>(v, tw_x, j, [&](int r) { return mem(j + r * nb, y); });
+            dft<RAD, -1>(v);
+#pragma unroll
+            for (int q = 0; q < RAD; ++q) {
+                v[q].x *= f[q];
+                v[q].y *= f[q];
+            }
+            dft<RAD, +1>(v);
+        }
+        __syncthreads();
+        if (act) {
+#pragma unroll
+            for (int q = 0; q < RAD; ++q)
+                mem(j * RAD + q, y) = v[q];
+        }
+    });
+    __syncthreads();
+    yxy_stage<+1, true, 1>(dx.rad[0], g.K0, g.K1, tw_x, at_t, to_t);
+    // y back, to the grid
+    yxy_stage<+1, false, 0>(dy.rad[1], g.K1, g.K0, tw_y, at, to);
+    yxy_stage<+1, true, 0>(dy.rad[0], g.K1, g.K0, tw_y, at,
+                           [&](int x, int y, C v) { store_at(base, global(x, y), v); });
 }
 
 // Pass 5 (z transform back, interpolation): workgroup (row chunk c, plane x).  The potential
@@ -1023,7 +1206,30 @@ static size_t lds_gather(const PlaneGeom& g, size_t cs) { return cs * ((size_t)(
 static size_t lds_force(const PlaneGeom& g, size_t cs) { return cs * ((size_t)(2 * g.Pf + 4) * g.S + g.K2); }
 static size_t lds_lines(int N, int kc, size_t cs) { return cs * ((size_t)N * (kc | 1) + N); }
 
-static PlaneGeom plane_geom(const amoeba_ctx* c)
+// Threads of the one-launch y-x-y pass, 0 where it does not serve the grid: a column of at most
+// kPlYxyPoints points, both lengths of two stages, one butterfly per thread.  The pass reads 8 or 16
+// bytes of each 128-byte line, so it gains only where launches cost more than bytes: y + x + y 14.2
+// against 9.5 us at 24^3, 14.8 / 11.9 at 36^3, 15.4 / 15.2 at 48^3 and 17.0 / 24.2 at 64^3 in FP32
+// (15.2 / 10.1, 15.4 / 13.2, 18.3 / 19.4, 23.4 / 30.7 in FP64); at 48^3 the launches saved decide.
+constexpr int kPlYxyPoints = 2304;
+static size_t lds_yxy(const PlaneGeom& g, size_t cs) { return cs * ((size_t)g.K0 * (g.K1 | 1) + g.K0 + g.K1); }
+static int yxy_threads(const PlaneGeom& g, const PlaneDim& dy, const PlaneDim& dx, size_t cs)
+{
+    if (g.K0 * g.K1 > kPlYxyPoints || dy.nr != 2 || dx.nr != 2 || lds_yxy(g, cs) > kPlLdsMax)
+        return 0;
+    const int nt = std::max(g.K0 * (g.K1 / min_radix(dy)), g.K1 * (g.K0 / min_radix(dx)));
+    return nt <= kPlYxyThreads ? cdiv(nt, 64) * 64 : 0;
+}
+
+// Geometry and factorisations of a context's grid, worked out once.
+struct PlanePlan {
+    PlaneGeom g;
+    PlaneDim d[3];
+    bool factors;  // every length has a factorisation (else g is not filled)
+    int yxy;       // threads of the one-launch y-x-y pass, 0: the three passes
+};
+
+static PlaneGeom make_geom(const amoeba_ctx* c, const PlaneDim (&d)[3])
 {
     PlaneGeom g;
     g.npad = c->npad;
@@ -1042,9 +1248,7 @@ static PlaneGeom plane_geom(const amoeba_ctx* c)
     // limits; a grid that needs more than kPlLargeWG of them (two 512-thread workgroups fit a CU)
     // takes 256-thread workgroups on smaller chunks, so that more of them are resident at once
     // and the chip is not left with a partial last round (measured at 216^3)
-    PlaneDim dz;
-    plane_factor(g.K2, dz);
-    const int zb = dz.nr > 0 ? g.K2 / min_radix(dz) : 1;
+    const int zb = g.K2 / min_radix(d[2]);
     auto one_round = [&]() { return g.Pc * zb <= g.nt; };  // the spread's first stage: a thread for every butterfly
     auto rows = [&](int target) {
         g.nyc = std::min(g.P, std::max(1, cdiv(target, g.K0)));
@@ -1070,18 +1274,15 @@ static PlaneGeom plane_geom(const amoeba_ctx* c)
     g.nyf = cdiv(g.P, g.Pf);
     // column chunks of one line, fewer columns where a pass would exceed the threads or the LDS of
     // a workgroup (lengths far above those of the plane path's usual grids)
-    PlaneDim dx, dy;
-    plane_factor(g.K0, dx);  // (a length without a factorisation: not eligible, see plane_eligible)
-    plane_factor(g.K1, dy);
     g.kc = line;
-    while (g.kc > 1 && (col_threads(dx, g.kc) > kPlColThreads || col_threads(dy, g.kc) > kPlColThreads ||
+    while (g.kc > 1 && (col_threads(d[0], g.kc) > kPlColThreads || col_threads(d[1], g.kc) > kPlColThreads ||
                         lds_lines(g.K0, g.kc, cs) > kPlLdsMax || lds_lines(g.K1, g.kc, cs) > kPlLdsMax))
         g.kc /= 2;
     g.kcs = 0;
     while ((1 << g.kcs) < g.kc)
         ++g.kcs;
-    g.nty = col_threads(dy, g.kc);
-    g.ntx = col_threads(dx, g.kc);
+    g.nty = col_threads(d[1], g.kc);
+    g.ntx = col_threads(d[0], g.kc);
     g.nkc = cdiv(g.kh, g.kc);
     g.kl = g.kc | 1;
     g.klx = c->K[0] / c->prm.box[0];
@@ -1090,32 +1291,48 @@ static PlaneGeom plane_geom(const amoeba_ctx* c)
     return g;
 }
 
-int plane_row_stride(const amoeba_ctx* c) { return plane_geom(c).ks; }
+static const PlanePlan& plane_plan(const amoeba_ctx* c)
+{
+    if (!c->plane_plan) {
+        auto p = std::make_shared<PlanePlan>();
+        p->factors = true;
+        p->yxy = 0;
+        for (int a = 0; a < 3; ++a)
+            p->factors = plane_factor(c->K[a], p->d[a]) && p->factors;
+        if (p->factors) {
+            p->g = make_geom(c, p->d);
+            p->yxy = yxy_threads(p->g, p->d[1], p->d[0], c->mixed ? sizeof(float2) : sizeof(double2));
+        }
+        c->plane_plan = p;
+    }
+    return *c->plane_plan;
+}
+
+int plane_row_stride(const amoeba_ctx* c) { return plane_plan(c).g.ks; }
 
 void plane_column_chunks(const amoeba_ctx* c, int* kc, int* nkc)
 {
-    const PlaneGeom g = plane_geom(c);
+    const PlaneGeom& g = plane_plan(c).g;
     *kc = g.kc;
     *nkc = g.nkc;
 }
 
 bool plane_eligible(const amoeba_ctx* c)
 {
-    PlaneDim d;
-    for (int a = 0; a < 3; ++a)
-        if (!plane_factor(c->K[a], d))
-            return false;
-    const PlaneGeom g = plane_geom(c);
+    const PlanePlan& p = plane_plan(c);
+    if (!p.factors)
+        return false;
+    const PlaneGeom& g = p.g;
     const size_t cs = c->mixed ? sizeof(float2) : sizeof(double2);
     return lds_spread(g, cs) <= kPlLdsMax && lds_gather(g, cs) <= kPlLdsMax &&
-           g.Pc * (g.K2 / min_radix(d)) <= g.nt && lds_lines(g.K0, g.kc, cs) <= kPlLdsMax &&
+           g.Pc * (g.K2 / min_radix(p.d[2])) <= g.nt && lds_lines(g.K0, g.kc, cs) <= kPlLdsMax &&
            lds_lines(g.K1, g.kc, cs) <= kPlLdsMax && g.nty <= kPlColThreads && g.ntx <= kPlColThreads && (size_t)g.K0 * g.K1 <= 65536;
 }
 
 // Whether the gradient's interpolation fits a workgroup's LDS (a line per row and the halo).
 bool plane_force_fits(const amoeba_ctx* c)
 {
-    return lds_force(plane_geom(c), c->mixed ? sizeof(float2) : sizeof(double2)) <= kPlLdsMax;
+    return lds_force(plane_plan(c).g, c->mixed ? sizeof(float2) : sizeof(double2)) <= kPlLdsMax;
 }
 
 int plane_setup(amoeba_ctx* c)
@@ -1176,13 +1393,14 @@ template <typename R> struct PlanePasses {
     using R4 = typename PlT<R>::R4;
     static constexpr bool FIX = std::is_same<R, float>::value;
     amoeba_ctx* c;
-    PlaneGeom g;
-    PlaneDim d[3];
+    const PlaneGeom& g;
+    const PlaneDim (&d)[3];
+    const int yxy;
     const C* const* roots;
-    explicit PlanePasses(amoeba_ctx* ctx) : c(ctx), g(plane_geom(ctx)), roots((const C* const*)ctx->pl_roots)
+    explicit PlanePasses(amoeba_ctx* ctx)
+        : c(ctx), g(plane_plan(ctx).g), d(plane_plan(ctx).d), yxy(plane_plan(ctx).yxy),
+          roots((const C* const*)ctx->pl_roots)
     {
-        for (int a = 0; a < 3; ++a)
-            plane_factor(c->K[a], d[a]);
     }
     bool small() const { return g.nt == kPlThreads; }
     void spread(const R4* src, int sstride, bool perm, C* gc, int ud) const
@@ -1194,10 +1412,19 @@ template <typename R> struct PlanePasses {
         hipLaunchKernelGGL(k, dim3(g.K0 * g.nyc), dim3(g.nt), lds_spread(g, sizeof(C)), c->stream, g, d[2],
                            c->xb_start, c->xb_rec, (const R4*)c->xb_w, src, sstride, roots[2], gc, c->sc, ud);
     }
-    // y, x with the influence function and y back, of gc (and gc1 when given)
-    void transforms(C* gc, C* gc1, int ud) const
+    // y, x with the influence function and y back, of gc (and gc1 when given); reduce: the
+    // real-space reduction of a small system's product in the same launch
+    void transforms(C* gc, C* gc1, int ud, bool reduce = false) const
     {
         const int ng = gc1 ? 2 : 1;
+        if (const int nt = yxy) {
+            const RealReduceArgs<R> rr{reduce ? c->npad : 0, c->eipart, (const R*)c->jbuf, c->rev_ptr, c->rev_idx,
+                                       c->ereal};
+            hipLaunchKernelGGL(k_pme_yxy<R>, dim3(g.kh + (reduce ? cdiv(c->npad, nt) : 0), ng), dim3(nt),
+                               lds_yxy(g, sizeof(C)), c->stream, g, d[1], d[0], gc, gc1, (const R*)c->theta_pl,
+                               roots[1], roots[0], rr, c->sc, ud);
+            return;
+        }
         const size_t ly = lds_lines(g.K1, g.kc, sizeof(C)), lx = lds_lines(g.K0, g.kc, sizeof(C));
         hipLaunchKernelGGL((k_pme_ylines<R, -1>), dim3(g.K0 * g.nkc, ng), dim3(g.nty), ly, c->stream, g, d[1], gc,
                            gc1, roots[1], c->sc, ud);
@@ -1236,6 +1463,72 @@ template <typename R> static void plane_field_t(amoeba_ctx* c, bool use_done, in
     }
     StageTimer tm(c, perm ? AMOEBA_T_PERM : AMOEBA_T_GATHER);
     p.gather(gc, ud);
+}
+
+// A small system: its grid takes the one-launch transforms and its row passes the 512-thread
+// workgroups.  Its dipole product is enqueued as one launch for tiles and spread and one for the
+// transforms and the real-space reduction, on the context stream, unless stage timers want the
+// stages by themselves.
+bool plane_small_system(const amoeba_ctx* c)
+{
+    return pme_use_planes(c) && c->ntiles > 0 && plane_plan(c).g.nt == kPlThreads && plane_plan(c).yxy > 0;
+}
+bool plane_small_product(const amoeba_ctx* c) { return plane_small_system(c) && !c->timing && !c->timing_live; }
+
+template <typename R, bool MI, int CM>
+static void head_launch(amoeba_ctx* c, const PlanePasses<R>& p, const HeadTiles<R>& t, const typename PlT<R>::R4* pv,
+                        int ud)
+{
+    using C = typename PlT<R>::C;
+    constexpr bool FIX = std::is_same<R, float>::value;
+    const size_t lds = std::max(lds_spread(p.g, sizeof(C)), sizeof(TileLds<R, FIX, DipoleKind<R>, kHeadWaves>));
+    hipLaunchKernelGGL((k_product_head<R, MI, CM>), dim3(c->nb + p.g.K0 * p.g.nyc), dim3(kPlThreads), lds, c->stream,
+                       t, p.g, p.d[2], c->xb_start, c->xb_rec, (const typename PlT<R>::R4*)c->xb_w, pv, p.roots[2],
+                       (C*)c->grid_c, c->sc, ud);
+}
+
+template <typename R, int CM>
+static void head_launch_mi(amoeba_ctx* c, const PlanePasses<R>& p, const HeadTiles<R>& t,
+                           const typename PlT<R>::R4* pv, int ud)
+{
+    if (c->skip_mimg)
+        head_launch<R, false, CM>(c, p, t, pv, ud);
+    else
+        head_launch<R, true, CM>(c, p, t, pv, ud);
+}
+
+// The product up to its combine: E_real in ereal, the reciprocal shares in rec_part.
+template <typename R> static void small_product_t(amoeba_ctx* c, bool use_done)
+{
+    using C = typename PlT<R>::C;
+    using R4 = typename PlT<R>::R4;
+    const PlanePasses<R> p(c);
+    const int ud = use_done ? 1 : 0;
+    bool tiles_done = use_done;
+    const int cm = begin_coef_mode(c, &tiles_done);
+    const bool f = c->mixed;
+    const R4* pv = f ? (const R4*)c->pv_f : (const R4*)c->pv_d;
+    const HeadTiles<R> t{c->nb, c->blk_tile0, c->tile_np, c->tile_j, c->tile_mask, c->tile_walk,
+                         f ? (const R4*)c->jrel_f : (const R4*)c->jrel_d,
+                         f ? (const R4*)c->off_f : (const R4*)c->off_d,
+                         f ? (const R4*)c->par_f : (const R4*)c->par_d, make_ewald<R>(c), c->eipart, (R*)c->jbuf,
+                         c->coef_row0, (long long)c->coef_cap_rows, (typename V2<R>::T*)c->coef, tiles_done ? 1 : 0};
+    if (cm == kCoefReplay)
+        head_launch_mi<R, kCoefReplay>(c, p, t, pv, ud);
+    else if (cm == kCoefRecord)
+        head_launch_mi<R, kCoefRecord>(c, p, t, pv, ud);
+    else
+        head_launch_mi<R, kCoefCompute>(c, p, t, pv, ud);
+    p.transforms((C*)c->grid_c, nullptr, ud, true);
+    p.gather((const C*)c->grid_c, ud);
+}
+
+void plane_small_product_fields(amoeba_ctx* c, bool use_done)
+{
+    if (c->mixed)
+        small_product_t<float>(c, use_done);
+    else
+        small_product_t<double>(c, use_done);
 }
 
 // Complex values of one half grid of the plane path (a second one is the gradient's workspace).
@@ -1306,8 +1599,7 @@ int plane_combine(amoeba_ctx* c, bool use_done, bool dot_pq, bool reduced)
 {
     StageTimer tm(c, AMOEBA_T_GATHER);
     double3 kl = make_double3(c->K[0] / c->prm.box[0], c->K[1] / c->prm.box[1], c->K[2] / c->prm.box[2]);
-    const double b = c->prm.ewald_alpha;
-    const double self = 4.0 * b * b * b / (3.0 * sqrt(kPi));
+    const double self = self_coefficient(c);
     const int nwg = nblk(c->npad, 256);
     if (c->mixed) {
         auto k = reduced ? k_plane_combine<float, 2> : k_plane_combine<float, 1>;
