@@ -19,6 +19,7 @@ constexpr double kFixScale = 1099511627776.0;    // 2^40: fixed-point fraction b
 constexpr double kFixInv = 1.0 / 1099511627776.0;
 constexpr double kCoulomb = 332.0637133;         // kcal*A/(mol e^2)
 constexpr double kDebye = 4.80320;               // D per e*A
+constexpr int kSmallWaves = 8;                   // waves that share a block's tiles in a small system
 constexpr int kBrick = 8;                        // PME spread brick edge (grid points)
 constexpr int kMaxFiltered = 2048;               // filtered j-atoms per block (list build)
 constexpr int kRedBlocks = 512;                  // workgroups of the deterministic reductions
@@ -378,6 +379,11 @@ int coef_reserve(amoeba_ctx* c);          // size the coefficient store (host ha
 void coef_release(amoeba_ctx* c);         // free it (other allocations come first under the cap)
 bool coef_store_on(const amoeba_ctx* c);  // the requested mode uses the store
 int begin_coef_mode(amoeba_ctx* c, bool* use_done);  // the mode of the product being enqueued
+// Blocks of a small system at most: above, the overlap of the two streams is worth more than the
+// launches (a PCG iteration with two streams / in single launches, mixed: 75.6 / 65.3 us at 13,500
+// atoms, 76.7 / 73.2 at 23,559, 79.8 / 79.4 at 30,000, 83.4 / 88.7 at 42,000; FP64: 84.0 / 77.1,
+// 87.1 / 93.5, 90.6 / 99.9).
+inline int small_blocks(const amoeba_ctx* c) { return c->mixed ? 400 : 256; }
 int next_coef_mode(const amoeba_ctx* c);  // the next dipole product: 0 evaluates, 1 records, 2 replays
 void launch_real_reduce(amoeba_ctx* c, double* ereal, hipStream_t st = nullptr, bool use_done = false);
 void launch_perm_tiles(amoeba_ctx* c, hipStream_t st = nullptr);

@@ -386,6 +386,7 @@ template <typename R> struct HeadTiles {
     int use_done;
 };
 constexpr int kHeadWaves = kPlThreads / 64;
+static_assert(kHeadWaves == kSmallWaves, "a workgroup of the spread holds the waves of a small system's block");
 
 template <typename R, bool MI, int CM>
 __global__ __launch_bounds__(kPlThreads) void k_product_head(HeadTiles<R> t, PlaneGeom g, PlaneDim dz,
@@ -472,6 +473,22 @@ __device__ __forceinline__ void last_stage_cols(const C* buf, C* __restrict__ ds
     });
 }
 
+// The real-space reduction of a product, taken by the workgroups of a transform launch beyond its
+// own (small systems).
+template <typename R> struct RealReduceArgs {
+    int npad;  // 0: none
+    const double* eipart;
+    const R* jbuf;
+    const int *rev_ptr, *rev_idx;
+    double* ereal;
+    __device__ __forceinline__ void run(int wg) const
+    {
+        const int s = wg * blockDim.x + threadIdx.x;
+        if (s < npad)
+            real_reduce<R>(s, eipart, jbuf, rev_ptr, rev_idx, ereal);
+    }
+};
+
 // Passes 2 and 4 (y transform, SIGN -1 forward, +1 inverse): workgroup (plane x, column chunk):
 // the y-lines G[x][.][kz] for kz in the chunk, in place.  A chunk is one 128-byte line of columns
 // (the padding columns of a row are transformed along; nothing reads them).  The y index of the
@@ -485,6 +502,7 @@ __global__ __launch_bounds__(kPlColThreads) void k_pme_ylines(PlaneGeom g, Plane
                                                            typename PlT<R>::C* __restrict__ gc,
                                                            typename PlT<R>::C* __restrict__ gc1,
                                                            const typename PlT<R>::C* __restrict__ roots_y,
+                                                           RealReduceArgs<R> rr,
                                                            const PcgScalars* __restrict__ sc, int use_done)
 {
     __builtin_amdgcn_s_setprio(kPlPassPrio);
@@ -493,6 +511,10 @@ __global__ __launch_bounds__(kPlColThreads) void k_pme_ylines(PlaneGeom g, Plane
     if (use_done && sc->done)
         return;
     const int item = blockIdx.x;
+    if (item >= g.K0 * g.nkc) {
+        rr.run(item - g.K0 * g.nkc);
+        return;
+    }
     const int x = item / g.nkc, kz0 = (item - x * g.nkc) * g.kc;
     C* buf = reinterpret_cast<C*>(pl_smem);
     C* tw = buf + g.K1 * g.kl;
@@ -604,14 +626,6 @@ __device__ __forceinline__ void yxy_stage(int rad, int N, int nl, const C* tw, I
     __syncthreads();
 }
 
-template <typename R> struct RealReduceArgs {
-    int npad;  // 0: none
-    const double* eipart;
-    const R* jbuf;
-    const int *rev_ptr, *rev_idx;
-    double* ereal;
-};
-
 template <typename R>
 __global__ __launch_bounds__(kPlYxyThreads) void k_pme_yxy(PlaneGeom g, PlaneDim dy, PlaneDim dx,
                                                   typename PlT<R>::C* __restrict__ gc,
@@ -627,10 +641,8 @@ __global__ __launch_bounds__(kPlYxyThreads) void k_pme_yxy(PlaneGeom g, PlaneDim
     if (use_done && sc->done)
         return;
     const int kz = blockIdx.x, tid = threadIdx.x;
-    if (kz >= g.kh) {  // the workgroups beyond the columns: the real-space reduction of a product
-        const int s = (kz - g.kh) * blockDim.x + tid;
-        if (s < rr.npad)
-            real_reduce<R>(s, rr.eipart, rr.jbuf, rr.rev_ptr, rr.rev_idx, rr.ereal);
+    if (kz >= g.kh) {
+        rr.run(kz - g.kh);
         return;
     }
     C* base = (blockIdx.y ? gc1 : gc) + kz;
@@ -1417,21 +1429,21 @@ template <typename R> struct PlanePasses {
     void transforms(C* gc, C* gc1, int ud, bool reduce = false) const
     {
         const int ng = gc1 ? 2 : 1;
+        const RealReduceArgs<R> rr{reduce ? c->npad : 0, c->eipart, (const R*)c->jbuf, c->rev_ptr, c->rev_idx,
+                                   c->ereal};
         if (const int nt = yxy) {
-            const RealReduceArgs<R> rr{reduce ? c->npad : 0, c->eipart, (const R*)c->jbuf, c->rev_ptr, c->rev_idx,
-                                       c->ereal};
             hipLaunchKernelGGL(k_pme_yxy<R>, dim3(g.kh + (reduce ? cdiv(c->npad, nt) : 0), ng), dim3(nt),
                                lds_yxy(g, sizeof(C)), c->stream, g, d[1], d[0], gc, gc1, (const R*)c->theta_pl,
                                roots[1], roots[0], rr, c->sc, ud);
             return;
         }
         const size_t ly = lds_lines(g.K1, g.kc, sizeof(C)), lx = lds_lines(g.K0, g.kc, sizeof(C));
-        hipLaunchKernelGGL((k_pme_ylines<R, -1>), dim3(g.K0 * g.nkc, ng), dim3(g.nty), ly, c->stream, g, d[1], gc,
-                           gc1, roots[1], c->sc, ud);
+        hipLaunchKernelGGL((k_pme_ylines<R, -1>), dim3(g.K0 * g.nkc + (reduce ? cdiv(c->npad, g.nty) : 0), ng),
+                           dim3(g.nty), ly, c->stream, g, d[1], gc, gc1, roots[1], rr, c->sc, ud);
         hipLaunchKernelGGL(k_pme_xconv<R>, dim3(g.K1 * g.nkc, ng), dim3(g.ntx), lx, c->stream, g, d[0], gc, gc1,
                            (const R*)c->theta_pl, roots[0], c->sc, ud);
         hipLaunchKernelGGL((k_pme_ylines<R, 1>), dim3(g.K0 * g.nkc, ng), dim3(g.nty), ly, c->stream, g, d[1], gc,
-                           gc1, roots[1], c->sc, ud);
+                           gc1, roots[1], RealReduceArgs<R>{}, c->sc, ud);
     }
     void gather(const C* gc, int ud) const
     {
@@ -1465,13 +1477,12 @@ template <typename R> static void plane_field_t(amoeba_ctx* c, bool use_done, in
     p.gather(gc, ud);
 }
 
-// A small system: its grid takes the one-launch transforms and its row passes the 512-thread
-// workgroups.  Its dipole product is enqueued as one launch for tiles and spread and one for the
-// transforms and the real-space reduction, on the context stream, unless stage timers want the
-// stages by themselves.
+// A small system: at most small_blocks() blocks, row passes of the 512-thread workgroups.  Its dipole
+// product is enqueued as one launch for tiles and spread, with the real-space reduction beside the
+// transforms, on the context stream, unless stage timers want the stages by themselves.
 bool plane_small_system(const amoeba_ctx* c)
 {
-    return pme_use_planes(c) && c->ntiles > 0 && plane_plan(c).g.nt == kPlThreads && plane_plan(c).yxy > 0;
+    return pme_use_planes(c) && c->ntiles > 0 && c->nb <= small_blocks(c) && plane_plan(c).g.nt == kPlThreads;
 }
 bool plane_small_product(const amoeba_ctx* c) { return plane_small_system(c) && !c->timing && !c->timing_live; }
 

@@ -29,14 +29,15 @@
 //   multipole field at i from j:   q_j B1' r - B1' d_j + B2' (d_j.r) r
 //                                  + (1/3) B3' (Theta_j:rr) r - (2/3) B2' Theta_j r
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "tiles.h"
 
 namespace amoeba {
 
-template <typename R, bool FIX, class K, bool MI, int CM = kCoefCompute>
-__global__ __launch_bounds__(256, K::kMinWaves) void k_block_tiles(const int* __restrict__ blk_tile0,
+template <typename R, bool FIX, class K, bool MI, int CM, int W>
+__global__ __launch_bounds__(64 * W, K::kMinWaves) void k_block_tiles(const int* __restrict__ blk_tile0,
                                                      const int* __restrict__ tile_np,
                                                      const int* __restrict__ tile_j,
                                                      const unsigned long long* __restrict__ tile_mask,
@@ -50,10 +51,10 @@ __global__ __launch_bounds__(256, K::kMinWaves) void k_block_tiles(const int* __
                                                      const int* __restrict__ coef_row0, long long coef_cap_rows,
                                                      typename V2<R>::T* __restrict__ coef)
 {
-    __shared__ TileLds<R, FIX, K, kWavesPerWG> L;
+    __shared__ TileLds<R, FIX, K, W> L;
     if (use_done && sc->done)
         return;
-    block_tiles<R, FIX, K, MI, CM, kWavesPerWG>(L, blockIdx.x, blk_tile0, tile_np, tile_j, tile_mask, tile_walk, jrel,
+    block_tiles<R, FIX, K, MI, CM, W>(L, blockIdx.x, blk_tile0, tile_np, tile_j, tile_mask, tile_walk, jrel,
                                                 off, par, src, ew, eipart, jbuf, coef_row0, coef_cap_rows, coef);
 }
 
@@ -71,28 +72,39 @@ __global__ void k_real_reduce(int npad, const double* __restrict__ eipart, const
         real_reduce<R>(s, eipart, jbuf, rev_ptr, rev_idx, ereal);
 }
 
-template <typename R, bool FIX, bool MI, int CM>
+// Waves per block: four where the blocks fill the chip (a block's tiles share its staged i data and
+// one row of accumulators), eight for a small system, whose blocks leave the chip idle and whose
+// time is the longest wave's.
+template <typename F> static void with_waves(const amoeba_ctx* c, F&& f)
+{
+    if (c->nb <= small_blocks(c))
+        f(std::integral_constant<int, kSmallWaves>{});
+    else
+        f(std::integral_constant<int, kWavesPerWG>{});
+}
+
+template <typename R, bool FIX, bool MI, int CM, int W>
 static void dipole_tiles(amoeba_ctx* c, bool use_done, hipStream_t st, const typename V4<R>::T* jrel,
                          const typename V4<R>::T* off, const typename V4<R>::T* par, const typename V4<R>::T* pv)
 {
-    hipLaunchKernelGGL((k_block_tiles<R, FIX, DipoleKind<R>, MI, CM>), dim3(c->nb), dim3(256), 0, st,
+    hipLaunchKernelGGL((k_block_tiles<R, FIX, DipoleKind<R>, MI, CM, W>), dim3(c->nb), dim3(64 * W), 0, st,
                        c->blk_tile0, c->tile_np, c->tile_j, c->tile_mask, c->tile_walk, jrel, off, par, pv,
                        make_ewald<R>(c),
                        c->eipart, (R*)c->jbuf, c->sc, (int)use_done, c->coef_row0, (long long)c->coef_cap_rows,
                        (typename V2<R>::T*)c->coef);
 }
 
-template <typename R, bool FIX, bool MI>
+template <typename R, bool FIX, bool MI, int W>
 static void dipole_tiles_cm(amoeba_ctx* c, int cm, bool use_done, hipStream_t st, const typename V4<R>::T* jrel,
                             const typename V4<R>::T* off, const typename V4<R>::T* par,
                             const typename V4<R>::T* pv)
 {
     if (cm == kCoefReplay)
-        dipole_tiles<R, FIX, MI, kCoefReplay>(c, use_done, st, jrel, off, par, pv);
+        dipole_tiles<R, FIX, MI, kCoefReplay, W>(c, use_done, st, jrel, off, par, pv);
     else if (cm == kCoefRecord)
-        dipole_tiles<R, FIX, MI, kCoefRecord>(c, use_done, st, jrel, off, par, pv);
+        dipole_tiles<R, FIX, MI, kCoefRecord, W>(c, use_done, st, jrel, off, par, pv);
     else
-        dipole_tiles<R, FIX, MI, kCoefCompute>(c, use_done, st, jrel, off, par, pv);
+        dipole_tiles<R, FIX, MI, kCoefCompute, W>(c, use_done, st, jrel, off, par, pv);
 }
 
 // Whether the dipole products use the store.  AUTO: in FP64, where the pair functions cost far
@@ -133,10 +145,14 @@ template <bool MI> static void mutual_tiles(amoeba_ctx* c, bool use_done, hipStr
         return;
     StageTimer tm(c, AMOEBA_T_REAL, st);
     const int cm = begin_coef_mode(c, &use_done);
-    if (c->mixed)
-        dipole_tiles_cm<float, true, MI>(c, cm, use_done, st, c->jrel_f, c->off_f, c->par_f, c->pv_f);
-    else
-        dipole_tiles_cm<double, false, MI>(c, cm, use_done, st, c->jrel_d, c->off_d, c->par_d, c->pv_d);
+    auto go = [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        if (c->mixed)
+            dipole_tiles_cm<float, true, MI, W>(c, cm, use_done, st, c->jrel_f, c->off_f, c->par_f, c->pv_f);
+        else
+            dipole_tiles_cm<double, false, MI, W>(c, cm, use_done, st, c->jrel_d, c->off_d, c->par_d, c->pv_d);
+    };
+    with_waves(c, go);
 }
 
 void coef_invalidate(amoeba_ctx* c) { c->coef_ready = false; }
@@ -208,35 +224,33 @@ void launch_real_reduce(amoeba_ctx* c, double* ereal, hipStream_t st, bool use_d
                            c->eipart, (const double*)c->jbuf, c->rev_ptr, c->rev_idx, ereal, c->sc, (int)use_done);
 }
 
-template <bool MI> static void perm_tiles(amoeba_ctx* c, hipStream_t st)
+template <bool MI, int W> static void perm_tiles(amoeba_ctx* c, hipStream_t st)
 {
-    if (c->ntiles == 0)
-        return;
     StageTimer tm(c, AMOEBA_T_PERM, st);
     if (c->mixed)
-        hipLaunchKernelGGL((k_block_tiles<float, true, MultipoleKind<float>, MI>), dim3(c->nb), dim3(256), 0,
+        hipLaunchKernelGGL((k_block_tiles<float, true, MultipoleKind<float>, MI, kCoefCompute, W>), dim3(c->nb), dim3(64 * W), 0,
                            st, c->blk_tile0, c->tile_np, c->tile_j, c->tile_mask, c->tile_walk, c->jrel_f,
                            c->off_f, c->par_f,
                            (const float4*)c->mp_f, make_ewald<float>(c), c->eipart, (float*)c->jbuf, c->sc, 0,
                            (const int*)nullptr, 0ll, (float2*)nullptr);
     else
-        hipLaunchKernelGGL((k_block_tiles<double, false, MultipoleKind<double>, MI>), dim3(c->nb), dim3(256), 0,
+        hipLaunchKernelGGL((k_block_tiles<double, false, MultipoleKind<double>, MI, kCoefCompute, W>), dim3(c->nb), dim3(64 * W), 0,
                            st, c->blk_tile0, c->tile_np, c->tile_j, c->tile_mask, c->tile_walk, c->jrel_d,
                            c->off_d, c->par_d,
                            (const double4*)c->mp_d, make_ewald<double>(c), c->eipart, (double*)c->jbuf, c->sc, 0,
                            (const int*)nullptr, 0ll, (double2*)nullptr);
 }
 
-template <bool MI> static void force_tiles(amoeba_ctx* c, const void* src, hipStream_t st)
+template <bool MI, int W> static void force_tiles(amoeba_ctx* c, const void* src, hipStream_t st)
 {
     if (c->mixed)
-        hipLaunchKernelGGL((k_block_tiles<float, true, ForceKind<float>, MI>), dim3(c->nb), dim3(256), 0,
+        hipLaunchKernelGGL((k_block_tiles<float, true, ForceKind<float>, MI, kCoefCompute, W>), dim3(c->nb), dim3(64 * W), 0,
                            st, c->blk_tile0, c->tile_np, c->tile_j, c->tile_mask, c->tile_walk,
                            c->jrel_f, c->off_f,
                            c->par_f, (const float4*)src, make_ewald<float>(c), c->eipart, (float*)c->jbuf, c->sc, 0,
                            (const int*)nullptr, 0ll, (float2*)nullptr);
     else
-        hipLaunchKernelGGL((k_block_tiles<double, false, ForceKind<double>, MI>), dim3(c->nb), dim3(256), 0,
+        hipLaunchKernelGGL((k_block_tiles<double, false, ForceKind<double>, MI, kCoefCompute, W>), dim3(c->nb), dim3(64 * W), 0,
                            st, c->blk_tile0, c->tile_np, c->tile_j, c->tile_mask, c->tile_walk,
                            c->jrel_d, c->off_d,
                            c->par_d, (const double4*)src, make_ewald<double>(c), c->eipart, (double*)c->jbuf, c->sc,
@@ -248,10 +262,13 @@ template <bool MI> static void force_tiles(amoeba_ctx* c, const void* src, hipSt
 void launch_force_tiles(amoeba_ctx* c, const void* src, double* out, hipStream_t st)
 {
     if (c->ntiles > 0) {
-        if (c->skip_mimg)
-            force_tiles<false>(c, src, st);
-        else
-            force_tiles<true>(c, src, st);
+        with_waves(c, [&](auto waves) {
+            constexpr int W = decltype(waves)::value;
+            if (c->skip_mimg)
+                force_tiles<false, W>(c, src, st);
+            else
+                force_tiles<true, W>(c, src, st);
+        });
         launch_real_reduce(c, out, st);
     } else {
         hipMemsetAsync(out, 0, sizeof(double) * 3 * (size_t)c->npad, st);
@@ -264,10 +281,13 @@ void launch_perm_tiles(amoeba_ctx* c, hipStream_t st)
         return;
     if (!st)
         st = c->stream;
-    if (c->skip_mimg)
-        perm_tiles<false>(c, st);
-    else
-        perm_tiles<true>(c, st);
+    with_waves(c, [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        if (c->skip_mimg)
+            perm_tiles<false, W>(c, st);
+        else
+            perm_tiles<true, W>(c, st);
+    });
     launch_real_reduce(c, c->ereal, st);
 }
 
