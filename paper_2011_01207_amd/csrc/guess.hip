@@ -6,8 +6,7 @@
 // real-space dipole field of the pair kernel (the same tiles and precision as a PCG product)
 // and c the Ewald self coefficient.  Invariant features: alpha, Thole a, |v_k| in Debye, the
 // three cosines between the bases, and three Gaussian-weighted neighbour counts over the
-// in-cutoff pairs of the tile list.  Network: SiLU MLP NFEAT -> 64 -> 64 -> NBASIS on the
-// vector ALU in FP32, mu0 = sum_k (s_k + y_k) v_k with s = (1, 1, 1).
+// in-cutoff pairs of the tile list.  Network: SiLU MLP NFEAT -> 64 -> 64 -> NBASIS in FP32, mu0 = sum_k (s_k + y_k) v_k with s = (1, 1, 1).
 //
 // Delta kind, for a configuration that follows a solved one (converged dipoles mu_ref and
 // permanent field E_ref of that one, held by the context in caller order): v0 = mu_ref,
@@ -15,14 +14,14 @@
 // The untrained network returns mu_ref, the previous-step guess; trained, it adds the local
 // response to the change of the permanent field, with no real-space product and no tile walk.
 //
-// Weights are read at addresses that are the same for every lane, so they come through the
-// scalar unit and stay in the scalar cache; activations live in vector registers.  Training
-// sums every gradient over a fixed grid of one-wave workgroups in a fixed order and then over
-// the workgroups in index order, so gradients, losses and updates are bitwise reproducible.
+// Both dense layers, forward and backward, and the weight gradients are matrix products on the
+// matrix cores in FP32.  Training gives every tile of 16 samples to a fixed wave and sums waves and
+// workgroups in a fixed order, so gradients, losses and updates are bitwise reproducible.
 #include <algorithm>
 #include <cmath>
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -58,13 +57,14 @@ constexpr int kOffMean = kNP;
 constexpr int kOffInv = kNP + kNF;
 static_assert(kOffB3 + kNB == kNP, "parameter layout");
 static_assert(kNP + 2 * kNF == kNM, "model layout");
-constexpr int kGuessWG = 512;          // workgroups of the gradient kernel (at most)
+constexpr int kGuessWG = 256;          // workgroups of the gradient kernel (at most)
 
 // Scratch of amoeba_guess_gradient_noalloc: per-workgroup gradient and loss partials, the loss
-// and the flag word, for batches of at most kScratchWG chunks of 64 samples, in one file-scope
+// and the flag word, for batches of at most AMOEBA_GUESS_NOALLOC_MAX_BATCH samples, in one file-scope
 // device array (each device holds its own copy until the process ends).  Host code never uses
 // the array's name as an address: guess_scratch_init looks up each device's address once.
-constexpr int kScratchWG = 128;
+constexpr int kScratchWG = 128;  // 64 samples to a workgroup (guess_grad)
+static_assert(kScratchWG * 64 >= AMOEBA_GUESS_NOALLOC_MAX_BATCH, "scratch partials");
 constexpr size_t kScratchPart = sizeof(float) * (size_t)kNP * kScratchWG;
 constexpr size_t kScratchLoss = kScratchPart;
 constexpr size_t kScratchScal = kScratchLoss + sizeof(double) * kScratchWG;
@@ -272,35 +272,20 @@ __global__ void k_guess_features(int npad, const int* __restrict__ perm, const d
 }
 
 // ------------------------------------------------------------------------------------------
-// Network forward for one sample: layer 1 keeps a1 and h1 in registers; layer 2 runs over its
-// units one at a time (the unit index only addresses weights), feeding the output layer.
-// ------------------------------------------------------------------------------------------
-__device__ __forceinline__ void mlp_layer1(const float* __restrict__ w, const float (&x)[kNF], float (&a1)[kH],
-                                           float (&h1)[kH])
+// Sum over the 16 lanes of a row (lanes with the same lane / 16), in every lane: data-parallel
+// additions with the neighbour, the neighbouring pair, and the mirrored half row and row (the
+// partial sums are uniform in the halves that they mirror).
+__device__ __forceinline__ float row_sum(float x)
 {
-    float xh[kNF];
-#pragma unroll
-    for (int f = 0; f < kNF; ++f)
-        xh[f] = (x[f] - w[kOffMean + f]) * w[kOffInv + f];
-#pragma unroll
-    for (int k = 0; k < kH; ++k) {
-        float a = w[kOffB1 + k];
-#pragma unroll
-        for (int f = 0; f < kNF; ++f)
-            a = fmaf(w[k * kNF + f], xh[f], a);
-        a1[k] = a;
-        h1[k] = a * sigm(a);
-    }
-}
-
-__device__ __forceinline__ float mlp_unit2(const float* __restrict__ w, int k, const float (&h1)[kH])
-{
-    const float* row = w + kOffW2 + k * kH;
-    float a = w[kOffB2 + k];
-#pragma unroll
-    for (int j = 0; j < kH; ++j)
-        a = fmaf(row[j], h1[j], a);
-    return a;
+    auto add = [](float v, auto ctrl) {
+        constexpr int C = decltype(ctrl)::value;
+        return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), C, 0xf, 0xf, true));
+    };
+    x = add(x, std::integral_constant<int, 0xb1>{});   // quad_perm [1, 0, 3, 2]
+    x = add(x, std::integral_constant<int, 0x4e>{});   // quad_perm [2, 3, 0, 1]
+    x = add(x, std::integral_constant<int, 0x141>{});  // row_half_mirror
+    x = add(x, std::integral_constant<int, 0x140>{});  // row_mirror
+    return x;
 }
 
 // Inference over many samples (the whole box per configuration): the two dense layers are
@@ -311,7 +296,7 @@ __device__ __forceinline__ float mlp_unit2(const float* __restrict__ w, int k, c
 // registers).  Its output goes through LDS to become the A operand of layer 2 (B = W2^T, read
 // from LDS, which keeps the register count at three waves per SIMD).  The output layer and the
 // basis combination run on the vector units, each lane summing its units and the 16 lanes of a
-// group adding their partial sums.  The next tile's inputs are loaded during the current one.
+// group adding their partial sums (row_sum).  The next tile's inputs are loaded during the current one.
 typedef float mfma_f4 __attribute__((ext_vector_type(4)));
 constexpr int kFwdTile = 16;        // samples per tile (one wave)
 constexpr int kFwdMaxWG = 768;      // workgroups at most (grid-stride over the tiles; measured)
@@ -437,12 +422,10 @@ __global__ __launch_bounds__(256) void k_guess_forward(int64_t n, const float* _
                     y[v][c] = fmaf(w3l[c][nt], h, y[v][c]);
             }
 #pragma unroll
-        for (int off = 1; off < 16; off <<= 1)
+        for (int v = 0; v < 4; ++v)
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-#pragma unroll
-                for (int c = 0; c < kNB; ++c)
-                    y[v][c] += __shfl_xor(y[v][c], off);
+            for (int c = 0; c < kNB; ++c)
+                y[v][c] = row_sum(y[v][c]);
         // lane lr < 12 of group lg writes component oc of sample 4 lg + ov (phantom slots: 0)
         const int64_t a = a0 + 4 * lg + ov;
         if (lr < 4 * kNB && a < n) {
@@ -474,223 +457,427 @@ static unsigned forward_grid(int64_t n)
 }
 
 // ------------------------------------------------------------------------------------------
-// Loss and gradient.  One wave per workgroup, chunks of 64 samples, chunk q handled by
-// workgroup q mod G.  Phase 1 (lane = sample): forward, dL/dmu0, backward deltas, written to
-// LDS by rows.  Phase 2 (lane = hidden unit h): the workgroup's gradient of every parameter
-// that belongs to unit h, summed over the chunk's samples in order, kept in registers across
-// chunks.  Samples past the batch end contribute exactly zero.
+// Loss and gradient on the matrix cores (FP32 16x16x4, layouts as in k_guess_forward).  Workgroups
+// of four waves; tile q of 16 samples belongs to wave q mod (4 G) of the launch.  A wave keeps a
+// layer's values where its product leaves them, lane (lr, lg) holding samples 4 lg .. 4 lg + 3 of unit
+// 16 nt + lr:
+//   forward   a1 = x W1^T, a2 = h1 W2^T          (h1 through LDS to become an A operand)
+//   backward  d2 = (d3 W3) silu'(a2), d1 = (d2 W2) silu'(a1)            (d2 through LDS)
+//   weights   gW2 += d2^T h1, gW1 += d1^T x: the sum runs over samples, so register v of the layer
+//             values is an operand as it stands (k index lg = sample 4 lg + v), with no transposition
+// and the rest (output layer, biases, loss) on the vector units.  The weight gradients stay in 96
+// registers over the wave's tiles; at the end the waves of the workgroup add theirs in LDS, in wave
+// order, and the workgroup writes one partial.  Samples past the batch end contribute exactly zero.
+// 220 matrix instructions (12 us for 65,536 samples) and about 700 vector ones to a tile.  One wave
+// to a SIMD: the gradients and a tile's layers need 348 registers (two waves in 256 spilled: 53 us).
+// For 65,536 samples 48 us; one wave per workgroup on the vector units, a sample to a lane, took
+// 209 us.
 // ------------------------------------------------------------------------------------------
-constexpr int kRow = kH + 4;     // LDS row stride of the per-sample activations (16-byte rows)
+constexpr int kGradWaves = 4;
+constexpr int kPadA = kH + 4;    // LDS row strides that keep the operand reads free of bank conflicts:
+constexpr int kPadB = kH + 16;   // [16 nt + lr][4 s + lg] and [4 s + lg][16 nt + lr]
 
-__global__ __launch_bounds__(64) void k_guess_grad(int64_t n_batch, int64_t n_rows, const int* __restrict__ idx,
-                                                   const float* __restrict__ w, const float* __restrict__ feat,
-                                                   const float* __restrict__ basis, GuessOffsets so,
-                                                   const float* __restrict__ target, float lscale,
-                                                   float* __restrict__ part, double* __restrict__ lossp,
-                                                   int* __restrict__ flags)
+struct GradWeights {
+    float w2a[kH][kPadA];                    // W2, read as the B operand of h1 W2^T
+    float w2b[kH][kPadB];                    // W2, read as the B operand of d2 W2
+    float w1[kH][12], w3[kNB][kH], b1[kH], b2[kH];  // kept here rather than in registers
+    float h[kGradWaves][kFwdTile][kPadA];    // a wave's h1, then its d2
+};
+constexpr int kGradSums = kGradWaves / 2;
+static_assert(kGradWaves == 4 && kFwdTile * kGradWaves == 64, "the sums written out, and the scratch array's size");
+union GradLds {
+    GradWeights w;
+    float sum[kGradSums][kNP];               // at the end: sums of the waves' gradients
+};
+
+__device__ __forceinline__ void wave_sync()
 {
-    __shared__ __align__(16) float s_x[kBlock][12];
-    __shared__ __align__(16) float s_h1[kBlock][kRow];
-    __shared__ __align__(16) float s_d1[kBlock][kRow];
-    __shared__ __align__(16) float s_h2[kBlock][kRow];
-    __shared__ __align__(16) float s_d2[kBlock][kRow];   // holds silu'(a2) until delta2 replaces it
-    __shared__ __align__(16) float s_d3[kBlock][4];
-    const int lane = threadIdx.x;
-    const int64_t nchunk = (n_batch + kBlock - 1) / kBlock;
-    float gW1[kNF], gW2[kH], gW3[kNB], gb1 = 0.f, gb2 = 0.f, gb3 = 0.f;
-#pragma unroll
-    for (int f = 0; f < kNF; ++f)
-        gW1[f] = 0.f;
-#pragma unroll
-    for (int j = 0; j < kH; ++j)
-        gW2[j] = 0.f;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__global__ __launch_bounds__(64 * kGradWaves) void k_guess_grad(int64_t n_batch, int64_t n_rows,
+                                                                const int* __restrict__ idx,
+                                                                const float* __restrict__ w,
+                                                                const float* __restrict__ feat,
+                                                                const float* __restrict__ basis, GuessOffsets so,
+                                                                const float* __restrict__ target, float lscale,
+                                                                float* __restrict__ part, double* __restrict__ lossp,
+                                                                int* __restrict__ flags)
+{
+    static_assert(kH == 64 && kNF <= 12 && kNB == 3, "tile shapes of the matrix-core gradient");
+    __shared__ GradLds lds;
+    __shared__ double s_loss[kGradWaves];
+    GradWeights& L = lds.w;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lr = lane & 15, lg = lane >> 4;
+    for (int i = tid; i < kH * kH; i += 64 * kGradWaves) {
+        const float v = w[kOffW2 + i];
+        L.w2a[i / kH][i % kH] = v;
+        L.w2b[i / kH][i % kH] = v;
+    }
+    for (int i = tid; i < kH * 12; i += 64 * kGradWaves)
+        L.w1[i / 12][i % 12] = i % 12 < kNF ? w[(i / 12) * kNF + i % 12] : 0.0f;
+    if (tid < kNB * kH)
+        L.w3[tid / kH][tid % kH] = w[kOffW3 + tid];
+    if (tid < kH) {
+        L.b1[tid] = w[kOffB1 + tid];
+        L.b2[tid] = w[kOffB2 + tid];
+    }
+    float mean[3], inv[3], bias3[kNB];
+    const float mean_x = lr < kNF ? w[kOffMean + lr] : 0.0f, inv_x = lr < kNF ? w[kOffInv + lr] : 0.0f;
 #pragma unroll
     for (int c = 0; c < kNB; ++c)
-        gW3[c] = 0.f;
-    double lacc = 0.0;
-    for (int64_t q = blockIdx.x; q < nchunk; q += gridDim.x) {
-        // ---- phase 1: lane = sample
-        const int64_t b = q * kBlock + lane;
-        int64_t row = -1;
-        if (b < n_batch) {
-            row = idx ? (int64_t)idx[b] : b;
-            if (row < 0 || row >= n_rows) {
-                atomicOr(flags, kFlagBadIndex);
-                row = -1;
-            }
-        }
-        float x[kNF], v[kNB][3], tg[3];
-        if (row >= 0) {
+        bias3[c] = w[kOffB3 + c];
 #pragma unroll
-            for (int f = 0; f < kNF; ++f)
-                x[f] = feat[row * kNF + f];
+    for (int s3 = 0; s3 < 3; ++s3) {
+        const int f = 4 * s3 + lg;
+        mean[s3] = f < kNF ? w[kOffMean + f] : 0.0f;
+        inv[s3] = f < kNF ? w[kOffInv + f] : 0.0f;
+    }
+    const mfma_f4 zero{0.0f, 0.0f, 0.0f, 0.0f};
+    mfma_f4 gW2[4][4], gW1[4];
+    float gW3[kNB][4], gb1[4], gb2[4], gb3[kNB];
 #pragma unroll
-            for (int k = 0; k < kNB; ++k)
+    for (int a = 0; a < 4; ++a) {
+        gW1[a] = zero;
+        gb1[a] = gb2[a] = 0.0f;
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    v[k][c] = basis[row * kNB * 3 + k * 3 + c];
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-                tg[c] = target[row * 3 + c];
-        } else {
-#pragma unroll
-            for (int f = 0; f < kNF; ++f)
-                x[f] = w[kOffMean + f];
-#pragma unroll
-            for (int k = 0; k < kNB; ++k)
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    v[k][c] = 0.f;
-            tg[0] = tg[1] = tg[2] = 0.f;
-        }
-        float a1[kH], h1[kH];
-        mlp_layer1(w, x, a1, h1);
-#pragma unroll
-        for (int f = 0; f < kNF; ++f)
-            s_x[lane][f] = (x[f] - w[kOffMean + f]) * w[kOffInv + f];
-#pragma unroll
-        for (int j = 0; j < kH; ++j)
-            s_h1[lane][j] = h1[j];
-        float y[kNB];
+        for (int b = 0; b < 4; ++b)
+            gW2[a][b] = zero;
 #pragma unroll
         for (int c = 0; c < kNB; ++c)
-            y[c] = w[kOffB3 + c];
-        for (int k = 0; k < kH; ++k) {
-            const float a = mlp_unit2(w, k, h1);
-            const float sg = sigm(a);
-            const float h = a * sg;
-            s_h2[lane][k] = h;
-            s_d2[lane][k] = sg * (1.0f + a * (1.0f - sg));
+            gW3[c][a] = 0.0f;
+    }
 #pragma unroll
-            for (int c = 0; c < kNB; ++c)
-                y[c] = fmaf(w[kOffW3 + c * kH + k], h, y[c]);
+    for (int c = 0; c < kNB; ++c)
+        gb3[c] = 0.0f;
+    double lacc = 0.0;
+    const int64_t ntiles = (n_batch + kFwdTile - 1) / kFwdTile;
+    float(&sh)[kFwdTile][kPadA] = L.h[wv];
+    // the row of sample m of a tile, -1 past the batch end and for an index outside the data
+    auto row_of = [&](int64_t tile, int m) -> int64_t {
+        const int64_t b = tile * kFwdTile + m;
+        if (b >= n_batch)
+            return -1;
+        const int64_t r = idx ? (int64_t)idx[b] : b;
+        return r < 0 || r >= n_rows ? -1 : r;
+    };
+    // a tile's inputs: features as the A operand of layer 1 (sample lr) and as the B operand of gW1
+    // (samples 4 lg + v), basis and target of sample 4 lg + lr mod 4.  The next tile's are loaded
+    // while the current one is computed, and its row (of sample lr) one tile before that, so that no
+    // load waits for another.
+    struct In {
+        float xa[3], xb[4], bs[kNB][3], tg[3];
+    };
+    auto load = [&](int64_t tile, int64_t ra, In& in) {
+        const int64_t rs = __shfl((long long)ra, 4 * lg + (lr & 3));
+        if (lg == 0 && ra < 0 && tile * kFwdTile + lr < n_batch)
+            atomicOr(flags, kFlagBadIndex);
+#pragma unroll
+        for (int s3 = 0; s3 < 3; ++s3) {
+            const int f = 4 * s3 + lg;
+            in.xa[s3] = ra >= 0 && f < kNF ? (feat[ra * kNF + f] - mean[s3]) * inv[s3] : 0.0f;
         }
-        float gmu[3];
-        float l = 0.f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t rv = __shfl((long long)ra, 4 * lg + v);
+            in.xb[v] = rv >= 0 && lr < kNF ? (feat[rv * kNF + lr] - mean_x) * inv_x : 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < kNB; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                in.bs[k][c] = rs >= 0 ? basis[rs * kNB * 3 + k * 3 + c] : 0.0f;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            in.tg[c] = rs >= 0 ? target[rs * 3 + c] : 0.0f;
+    };
+    const int64_t stride = (int64_t)gridDim.x * kGradWaves, tile0 = (int64_t)blockIdx.x * kGradWaves + wv;
+    In in;
+    int64_t row_next = row_of(tile0 + stride, lr);
+    load(tile0, row_of(tile0, lr), in);
+    __syncthreads();  // the weights are in LDS
+    for (int64_t tile = tile0; tile < ntiles; tile += stride) {
+        float xa[3], xb[4], bs[kNB][3], tg[3];
+#pragma unroll
+        for (int s3 = 0; s3 < 3; ++s3)
+            xa[s3] = in.xa[s3];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            xb[v] = in.xb[v];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            float m = 0.f;
+            tg[c] = in.tg[c];
 #pragma unroll
             for (int k = 0; k < kNB; ++k)
-                m = fmaf(so.s[k] + y[k], v[k][c], m);
-            const float dlt = m - tg[c];
-            l = fmaf(dlt, dlt, l);
-            gmu[c] = 2.0f * lscale * dlt;
+                bs[k][c] = in.bs[k][c];
         }
-        float d3[kNB];
+        load(tile + stride, row_next, in);
+        row_next = row_of(tile + 2 * stride, lr);
+        // layer 1
+        mfma_f4 h1[4], s1[4];
 #pragma unroll
-        for (int k = 0; k < kNB; ++k) {
-            d3[k] = gmu[0] * v[k][0] + gmu[1] * v[k][1] + gmu[2] * v[k][2];
-            s_d3[lane][k] = d3[k];
+        for (int nt = 0; nt < 4; ++nt)
+            h1[nt] = zero;
+#pragma unroll
+        for (int s3 = 0; s3 < 3; ++s3)
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+                h1[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[s3], L.w1[16 * nt + lr][4 * s3 + lg], h1[nt], 0, 0, 0);
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            const float bias = L.b1[16 * nt + lr];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float a = h1[nt][v] + bias, sg = sigm(a);
+                h1[nt][v] = a * sg;
+                s1[nt][v] = sg * (1.0f + a * (1.0f - sg));
+                sh[4 * lg + v][16 * nt + lr] = h1[nt][v];
+            }
         }
-        s_d3[lane][3] = 0.f;
-        // delta2 and W2^T delta2
-        float t1[kH];
+        wave_sync();
+        // layer 2
+        mfma_f4 h2[4], d2[4];  // d2: silu'(a2) until the delta replaces it
 #pragma unroll
-        for (int j = 0; j < kH; ++j)
-            t1[j] = 0.f;
-        for (int k = 0; k < kH; ++k) {
-            float g = 0.f;
+        for (int nt = 0; nt < 4; ++nt)
+            h2[nt] = zero;
+#pragma unroll
+        for (int s16 = 0; s16 < 16; ++s16) {
+            const float ha = sh[lr][4 * s16 + lg];
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+                h2[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ha, L.w2a[16 * nt + lr][4 * s16 + lg], h2[nt], 0, 0, 0);
+        }
+        float y[4][kNB];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
 #pragma unroll
             for (int c = 0; c < kNB; ++c)
-                g = fmaf(w[kOffW3 + c * kH + k], d3[c], g);
-            const float d2 = g * s_d2[lane][k];
-            s_d2[lane][k] = d2;
-            const float* wr = w + kOffW2 + k * kH;
+                y[v][c] = 0.0f;
 #pragma unroll
-            for (int j = 0; j < kH; ++j)
-                t1[j] = fmaf(wr[j], d2, t1[j]);
+        for (int nt = 0; nt < 4; ++nt) {
+            const int u = 16 * nt + lr;
+            const float bias = L.b2[u], w3[kNB] = {L.w3[0][u], L.w3[1][u], L.w3[2][u]};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float a = h2[nt][v] + bias, sg = sigm(a);
+                h2[nt][v] = a * sg;
+                d2[nt][v] = sg * (1.0f + a * (1.0f - sg));
+#pragma unroll
+                for (int c = 0; c < kNB; ++c)
+                    y[v][c] = fmaf(w3[c], h2[nt][v], y[v][c]);
+            }
         }
 #pragma unroll
-        for (int j = 0; j < kH; ++j) {
-            const float sg = sigm(a1[j]);
-            s_d1[lane][j] = t1[j] * (sg * (1.0f + a1[j] * (1.0f - sg)));
-        }
-        // chunk loss, summed over the wave in a fixed tree
-        float ls = l * lscale;
+        for (int v = 0; v < 4; ++v)
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-            ls += __shfl_xor(ls, o);
-        lacc += (double)ls;
-        __syncthreads();
-        // ---- phase 2: lane = hidden unit h
-        const int h = lane;
-        const int na = (int)min((int64_t)kBlock, n_batch - q * kBlock);
-        for (int a = 0; a < na; ++a) {
-            const float d2 = s_d2[a][h];
-            const float d1 = s_d1[a][h];
-            const float h2 = s_h2[a][h];
-            gb2 += d2;
-            gb1 += d1;
-            const float4* hr = reinterpret_cast<const float4*>(&s_h1[a][0]);
+            for (int c = 0; c < kNB; ++c)
+                y[v][c] = row_sum(y[v][c]);
+        // loss and d3 of sample 4 lg + lr mod 4 (four lanes hold the same), then of all four
+        float d3[4][kNB], l = 0.0f;
+        {
+            const int vs = lr & 3;
+            float yk[kNB], gm[3], dk[kNB];
 #pragma unroll
-            for (int j4 = 0; j4 < kH / 4; ++j4) {
-                const float4 hv = hr[j4];
-                gW2[4 * j4] = fmaf(d2, hv.x, gW2[4 * j4]);
-                gW2[4 * j4 + 1] = fmaf(d2, hv.y, gW2[4 * j4 + 1]);
-                gW2[4 * j4 + 2] = fmaf(d2, hv.z, gW2[4 * j4 + 2]);
-                gW2[4 * j4 + 3] = fmaf(d2, hv.w, gW2[4 * j4 + 3]);
+            for (int c = 0; c < kNB; ++c)
+                yk[c] = so.s[c] + (bias3[c] + (vs == 0 ? y[0][c] : vs == 1 ? y[1][c] : vs == 2 ? y[2][c] : y[3][c]));
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                float m = 0.0f;
+#pragma unroll
+                for (int k = 0; k < kNB; ++k)
+                    m = fmaf(yk[k], bs[k][c], m);
+                const float dlt = m - tg[c];
+                l = fmaf(dlt, dlt, l);
+                gm[c] = 2.0f * lscale * dlt;
             }
 #pragma unroll
-            for (int f = 0; f < kNF; ++f)
-                gW1[f] = fmaf(d1, s_x[a][f], gW1[f]);
-            const float4 dv = *reinterpret_cast<const float4*>(&s_d3[a][0]);
-            gW3[0] = fmaf(dv.x, h2, gW3[0]);
-            gW3[1] = fmaf(dv.y, h2, gW3[1]);
-            gW3[2] = fmaf(dv.z, h2, gW3[2]);
-            gb3 += h == 0 ? dv.x : (h == 1 ? dv.y : (h == 2 ? dv.z : 0.f));
+            for (int k = 0; k < kNB; ++k) {
+                dk[k] = gm[0] * bs[k][0] + gm[1] * bs[k][1] + gm[2] * bs[k][2];
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    d3[v][k] = __shfl(dk[k], (lane & 48) + v);
+            }
+            l = lr < 4 ? l * lscale : 0.0f;
+            l = row_sum(l);
+            l += __shfl_xor(l, 16);
+            l += __shfl_xor(l, 32);
+            lacc += (double)l;
+        }
+        // delta of layer 2, and what it and the output layer add to their gradients
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            const int u = 16 * nt + lr;
+            const float w3[kNB] = {L.w3[0][u], L.w3[1][u], L.w3[2][u]};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                float g = 0.0f;
+#pragma unroll
+                for (int c = 0; c < kNB; ++c) {
+                    g = fmaf(w3[c], d3[v][c], g);
+                    gW3[c][nt] = fmaf(d3[v][c], h2[nt][v], gW3[c][nt]);
+                }
+                d2[nt][v] *= g;
+                gb2[nt] += d2[nt][v];
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int c = 0; c < kNB; ++c)
+                gb3[c] += d3[v][c];
+        wave_sync();  // h1 has been read from LDS
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                sh[4 * lg + v][16 * nt + lr] = d2[nt][v];
+        wave_sync();
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt)
+                    gW2[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(d2[mt][v], h1[nt][v], gW2[mt][nt], 0, 0, 0);
+        mfma_f4 d1[4];
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+            d1[nt] = zero;
+#pragma unroll
+        for (int s16 = 0; s16 < 16; ++s16) {
+            const float da = sh[lr][4 * s16 + lg];
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+                d1[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(da, L.w2b[4 * s16 + lg][16 * nt + lr], d1[nt], 0, 0, 0);
+        }
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                d1[nt][v] *= s1[nt][v];
+                gb1[nt] += d1[nt][v];
+            }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+                gW1[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(d1[mt][v], xb[v], gW1[mt], 0, 0, 0);
+        wave_sync();  // d2 has been read from LDS
+    }
+    // sums over the four row groups of the vector-unit gradients (every lane)
+    auto groups = [](float x) {
+        x += __shfl_xor(x, 16);
+        return x + __shfl_xor(x, 32);
+    };
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        gb1[nt] = groups(gb1[nt]);
+        gb2[nt] = groups(gb2[nt]);
+#pragma unroll
+        for (int c = 0; c < kNB; ++c)
+            gW3[c][nt] = groups(gW3[c][nt]);
+    }
+#pragma unroll
+    for (int c = 0; c < kNB; ++c)
+        gb3[c] = groups(gb3[c]);
+    if (lane == 0)
+        s_loss[wv] = lacc;
+    __syncthreads();  // the weights in LDS are no longer read
+    // the first half of the waves into a sum each, the second half added to them, the sums added
+    // where they are written out
+    for (int r = 0; r < 2; ++r) {
+        if (wv / kGradSums == r) {
+            float* sum = lds.sum[wv % kGradSums];
+            auto add = [&](int p, float v) { sum[p] = r ? sum[p] + v : v; };
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int k = 16 * mt + 4 * lg + v;
+                    if (lr < kNF)
+                        add(k * kNF + lr, gW1[mt][v]);
+#pragma unroll
+                    for (int nt = 0; nt < 4; ++nt)
+                        add(kOffW2 + k * kH + 16 * nt + lr, gW2[mt][nt][v]);
+                }
+            if (lg == 0) {
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt) {
+                    add(kOffB1 + 16 * nt + lr, gb1[nt]);
+                    add(kOffB2 + 16 * nt + lr, gb2[nt]);
+#pragma unroll
+                    for (int c = 0; c < kNB; ++c)
+                        add(kOffW3 + c * kH + 16 * nt + lr, gW3[c][nt]);
+                }
+                if (lr == 0)
+#pragma unroll
+                    for (int c = 0; c < kNB; ++c)
+                        add(kOffB3 + c, gb3[c]);
+            }
         }
         __syncthreads();
     }
     float* p = part + (size_t)blockIdx.x * kNP;
-    const int h = lane;
-#pragma unroll
-    for (int f = 0; f < kNF; ++f)
-        p[h * kNF + f] = gW1[f];
-    p[kOffB1 + h] = gb1;
-#pragma unroll
-    for (int j = 0; j < kH; ++j)
-        p[kOffW2 + h * kH + j] = gW2[j];
-    p[kOffB2 + h] = gb2;
-#pragma unroll
-    for (int c = 0; c < kNB; ++c)
-        p[kOffW3 + c * kH + h] = gW3[c];
-    if (h < kNB)
-        p[kOffB3 + h] = gb3;
-    if (lane == 0)
-        lossp[blockIdx.x] = lacc;
+    for (int i = tid; i < kNP; i += 64 * kGradWaves)
+        p[i] = lds.sum[0][i] + lds.sum[1][i];
+    if (tid == 0) {
+        double l = 0.0;
+        for (int q = 0; q < kGradWaves; ++q)
+            l += s_loss[q];
+        lossp[blockIdx.x] = l;
+    }
 }
 
 // Sum of the workgroup partials per parameter in FP64, in a fixed order: 64 parameters per
-// workgroup, four groups of partials per parameter (g, g+4, ...) combined in LDS in group
+// workgroup, sixteen groups of partials per parameter (g, g+16, ...) combined in LDS in group
 // order.  Then the gradient is written out and/or an Adam step is applied -- skipped when the
 // gradient kernel flagged an index outside the data, so a rejected step changes nothing.  The
-// loss is summed by thread 0 of workgroup 0.
-__global__ __launch_bounds__(256) void k_guess_reduce(int nwg, const float* __restrict__ part,
+// loss is summed by the first wave of workgroup 0.  (Four groups over 512 partials took 52 us, a
+// chain of 128 loads a thread.)
+constexpr int kRedGroups = 16;
+__global__ __launch_bounds__(64 * kRedGroups) void k_guess_reduce(int nwg, const float* __restrict__ part,
                                                       const double* __restrict__ lossp, float* __restrict__ grad,
                                                       float* __restrict__ w, float* __restrict__ m,
                                                       float* __restrict__ v, int adam, float lr, float bc1,
                                                       float bc2, double* __restrict__ loss,
                                                       const int* __restrict__ flags)
 {
-    __shared__ double s_sum[4][64];
+    __shared__ double s_sum[kRedGroups][64];
     const int tid = threadIdx.x, g = tid >> 6, pl = tid & 63;
     const int p = blockIdx.x * 64 + pl;
-    if (blockIdx.x == 0 && tid == 0) {
+    if (blockIdx.x == 0 && g == 0) {
         double l = 0.0;
-        for (int q = 0; q < nwg; ++q)
+        for (int q = pl; q < nwg; q += 64)
             l += lossp[q];
-        loss[0] = l;
+        for (int off = 32; off > 0; off >>= 1)
+            l += __shfl_xor(l, off);
+        if (pl == 0)
+            loss[0] = l;
     }
     double acc = 0.0;
-    if (p < kNP)
-        for (int q = g; q < nwg; q += 4)
-            acc += (double)part[(size_t)q * kNP + p];
+    if (p < kNP) {
+        // four loads in flight
+        for (int q = g; q < nwg; q += 4 * kRedGroups) {
+            float x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                x[u] = q + u * kRedGroups < nwg ? part[(size_t)(q + u * kRedGroups) * kNP + p] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                acc += (double)x[u];
+        }
+    }
     s_sum[g][pl] = acc;
     __syncthreads();
     if (g != 0 || p >= kNP)
         return;
-    const float gr = (float)(((s_sum[0][pl] + s_sum[1][pl]) + s_sum[2][pl]) + s_sum[3][pl]);
+    double tot = s_sum[0][pl];
+#pragma unroll
+    for (int q = 1; q < kRedGroups; ++q)
+        tot += s_sum[q][pl];
+    const float gr = (float)tot;
     if (grad)
         grad[p] = gr;
     if (adam && !(flags[0] & kFlagBadIndex)) {
@@ -944,8 +1131,9 @@ static int guess_grad(amoeba_ctx* c, const float* feat, const float* basis, cons
     if (adam && !(lr > 0.0f && std::isfinite(lr)))
         return set_error(c, AMOEBA_E_INVALID, std::string(who) + ": lr must be positive");
     hipStream_t st = c->stream;
-    const int64_t nchunk = (n_batch + kBlock - 1) / kBlock;
-    const int nwg = (int)std::min<int64_t>(nchunk, kGuessWG);
+    // a tile of 16 samples to a wave
+    const int64_t per_wg = (int64_t)kFwdTile * kGradWaves;
+    const int nwg = (int)std::min<int64_t>((n_batch + per_wg - 1) / per_wg, kGuessWG);
     if (ws.fill_flags)
         hipLaunchKernelGGL(k_zero_flag, dim3(1), dim3(64), 0, st, ws.flags);
     else
@@ -959,9 +1147,9 @@ static int guess_grad(amoeba_ctx* c, const float* feat, const float* basis, cons
     {
         StageTimer tm(c, AMOEBA_T_GUESS);
         const float lscale = (float)(kDebye * kDebye / (double)n_batch);
-        hipLaunchKernelGGL(k_guess_grad, dim3(nwg), dim3(64), 0, st, n_batch, n_rows, idx, c->g_model, feat, basis,
+        hipLaunchKernelGGL(k_guess_grad, dim3(nwg), dim3(64 * kGradWaves), 0, st, n_batch, n_rows, idx, c->g_model, feat, basis,
                            guess_offsets(c), target, lscale, ws.part, ws.lossp, ws.flags);
-        hipLaunchKernelGGL(k_guess_reduce, dim3((kNP + 63) / 64), dim3(256), 0, st, nwg, ws.part, ws.lossp,
+        hipLaunchKernelGGL(k_guess_reduce, dim3((kNP + 63) / 64), dim3(64 * kRedGroups), 0, st, nwg, ws.part, ws.lossp,
                            grad_out, c->g_model, c->g_adam_m, c->g_adam_v, adam ? 1 : 0, lr, bc1, bc2, ws.scal,
                            ws.flags);
     }
@@ -1240,7 +1428,7 @@ int amoeba_guess_gradient_noalloc(amoeba_ctx* c, const float* feat, const float*
     c->err.clear();
     if (!grad_out)
         return set_error(c, AMOEBA_E_INVALID, "amoeba_guess_gradient_noalloc: NULL grad_out");
-    if (n_batch > (int64_t)kScratchWG * kBlock)
+    if (n_batch > AMOEBA_GUESS_NOALLOC_MAX_BATCH)
         return set_error(c, AMOEBA_E_INVALID, "amoeba_guess_gradient_noalloc: n_batch above "
                                               "AMOEBA_GUESS_NOALLOC_MAX_BATCH (8192)");
     int rc = guess_ready(c, "amoeba_guess_gradient_noalloc");

@@ -261,3 +261,32 @@ def test_predict_matches_features_and_forward(c1):
     ref = G.forward(model.astype(np.float64), x_ref, b_ref)
     assert rel(mu0, ref) < 2e-5
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 8191, 16385])
+def test_gradient_at_the_edges_of_its_tiles(n):
+    """Batches around the 16-sample tiles, the 64 samples of a workgroup and the launch's workgroup
+    limit (256 of them), drawn with repetition from more rows than the batch, against FP64
+    backpropagation at the bars of the gradient's other comparison."""
+    s = synth.water648()
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal((5000, G.NFEAT)).astype(np.float32)
+    b = (0.05 * rng.standard_normal((5000, G.NBASIS, 3))).astype(np.float32)
+    y = (0.05 * rng.standard_normal((5000, 3))).astype(np.float32)
+    idx = rng.integers(0, 5000, n).astype(np.int32)
+    model = random_model(61)
+    ctx, _ = amoeba.context_for(s, precision="mixed", device=DEV)
+    try:
+        ctx.guess_set_model(model)
+        loss, g = ctx.guess_gradient(f32(x), f32(b), f32(y), idx=torch.tensor(idx, device=DEV))
+        idx_bad = torch.tensor(idx, device=DEV)
+        idx_bad[-1] = 5000
+        with pytest.raises(amoeba.AmoebaError) as ei:
+            ctx.guess_gradient(f32(x), f32(b), f32(y), idx=idx_bad)
+        assert ei.value.status == amoeba.AMOEBA_E_INVALID
+    finally:
+        ctx.close()
+    l_ref, g_ref = G.loss_grad(model.astype(np.float64), x[idx].astype(np.float64), b[idx].astype(np.float64),
+                               y[idx].astype(np.float64))
+    assert abs(loss - l_ref) < 1e-5 * l_ref
+    assert rel(g.cpu().numpy(), g_ref) < 1e-4
