@@ -388,6 +388,7 @@ int next_coef_mode(const amoeba_ctx* c);  // the next dipole product: 0 evaluate
 void launch_real_reduce(amoeba_ctx* c, double* ereal, hipStream_t st = nullptr, bool use_done = false);
 void launch_perm_tiles(amoeba_ctx* c, hipStream_t st = nullptr);
 void launch_perm_assemble(amoeba_ctx* c, double* out_slot, const double* scales);  // scales in slot order
+void launch_radial_sums(amoeba_ctx* c, double* out);  // neighbour sums of the learned guess
 void launch_force_tiles(amoeba_ctx* c, const void* src, double* out, hipStream_t st);  // real-space gradient pair sums
 
 // pme.hip

@@ -6,7 +6,8 @@
 // real-space dipole field of the pair kernel (the same tiles and precision as a PCG product)
 // and c the Ewald self coefficient.  Invariant features: alpha, Thole a, |v_k| in Debye, the
 // three cosines between the bases, and three Gaussian-weighted neighbour counts over the
-// in-cutoff pairs of the tile list.  Network: SiLU MLP NFEAT -> 64 -> 64 -> NBASIS in FP32, mu0 = sum_k (s_k + y_k) v_k with s = (1, 1, 1).
+// in-cutoff pairs of the tile list.  Network: SiLU MLP NFEAT -> 64 -> 64 -> NBASIS in FP32,
+// mu0 = sum_k (s_k + y_k) v_k with s = (1, 1, 1).
 //
 // Delta kind, for a configuration that follows a solved one (converged dipoles mu_ref and
 // permanent field E_ref of that one, held by the context in caller order): v0 = mu_ref,
@@ -29,9 +30,6 @@
 
 namespace amoeba {
 
-template <typename R> struct V4R;
-template <> struct V4R<float> { using T = float4; };
-template <> struct V4R<double> { using T = double4; };
 template <typename R4T> struct Cast4G;
 template <> struct Cast4G<float4> {
     __device__ static float4 make(double x, double y, double z, double w)
@@ -77,109 +75,11 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 struct GuessOffsets {
     float s[kNB];
 };
-constexpr float kRadialC[3] = {1.0f, 2.0f, 3.0f};
-constexpr float kRadialInvW = 1.0f / 0.6f;
 
 // logistic function with the hardware reciprocal (1 ulp) instead of an IEEE division sequence
 __device__ __forceinline__ float sigm(float a) { return __builtin_amdgcn_rcpf(1.0f + __expf(-a)); }
 
 static inline int nblk64(int64_t n, int b) { return (int)((n + b - 1) / b); }
-
-// ------------------------------------------------------------------------------------------
-// Radial neighbour sums over the tile list: one workgroup (4 waves) per i-block, wave w takes
-// the block's tiles w, w+4, ...  Lane l sums its row of a tile (pairs (l, k) with bit k set)
-// and the tile's column l (pairs (i, l) with bit l of row i set).  Rows accumulate in
-// registers per wave and are summed over the waves in a fixed order at the end; columns of
-// off-diagonal tiles go to the tile's jbuf slot and are added to their atom by the
-// reverse-index reduction; the diagonal tile's column belongs to the block's own atom l.
-// ------------------------------------------------------------------------------------------
-__device__ __forceinline__ float rad_exp(float x) { return __expf(x); }
-__device__ __forceinline__ double rad_exp(double x) { return exp(x); }
-__device__ __forceinline__ float rad_len(float r2) { return r2 * __builtin_amdgcn_rsqf(r2); }
-__device__ __forceinline__ double rad_len(double r2) { return sqrt(r2); }
-
-template <typename R>
-__device__ __forceinline__ void radial_add(R dx, R dy, R dz, R L0, R L1, R L2, R Li0, R Li1, R Li2, R (&acc)[3])
-{
-    dx -= L0 * rint(dx * Li0);
-    dy -= L1 * rint(dy * Li1);
-    dz -= L2 * rint(dz * Li2);
-    const R r = rad_len(dx * dx + dy * dy + dz * dz);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const R u = (r - (R)kRadialC[c]) * (R)kRadialInvW;
-        acc[c] += rad_exp(-u * u);
-    }
-}
-
-template <typename R>
-__global__ __launch_bounds__(256) void k_guess_radial(const int* __restrict__ blk_tile0,
-                                                      const unsigned long long* __restrict__ tile_mask,
-                                                      const typename V4R<R>::T* __restrict__ jrel,
-                                                      const typename V4R<R>::T* __restrict__ off, R L0, R L1, R L2,
-                                                      R Li0, R Li1, R Li2, double* __restrict__ eipart,
-                                                      R* __restrict__ jbuf)
-{
-    using R4 = typename V4R<R>::T;
-    __shared__ R4 s_i[kBlock];
-    __shared__ R4 s_j[4][kBlock];
-    __shared__ unsigned long long s_m[4][kBlock];
-    __shared__ R s_row[4][3][kBlock];
-    const int I = blockIdx.x, tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    const int si = I * kBlock + lane;
-    if (tid < kBlock)
-        s_i[tid] = off[I * kBlock + tid];
-    __syncthreads();
-    const R4 oi = s_i[lane];
-    const int t0 = blk_tile0[I], nt = blk_tile0[I + 1] - t0;
-    R row[3] = {0, 0, 0};
-    for (int tt = w; tt < nt; tt += 4) {
-        const int t = t0 + tt;
-        s_j[w][lane] = jrel[(size_t)t * kBlock + lane];
-        s_m[w][lane] = tile_mask[(size_t)t * kBlock + lane];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        unsigned long long m = s_m[w][lane];
-        while (m) {
-            const int k = __ffsll((long long)m) - 1;
-            m &= m - 1ull;
-            const R4 q = s_j[w][k];
-            radial_add(oi.x - q.x, oi.y - q.y, oi.z - q.z, L0, L1, L2, Li0, Li1, Li2, row);
-        }
-        R col[3] = {0, 0, 0};
-        const R4 q = s_j[w][lane];
-#pragma unroll 8
-        for (int i = 0; i < kBlock; ++i) {
-            const bool set = (s_m[w][i] >> lane) & 1ull;
-            if (set) {
-                const R4 p = s_i[i];
-                radial_add(p.x - q.x, p.y - q.y, p.z - q.z, L0, L1, L2, Li0, Li1, Li2, col);
-            }
-        }
-        if (tt == 0) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-                row[c] += col[c];
-        } else {
-            reinterpret_cast<R4*>(jbuf)[(size_t)t * kBlock + lane] = R4{col[0], col[1], col[2], (R)0};
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-        s_row[w][c][lane] = row[c];
-    __syncthreads();
-    if (tid < 3 * kBlock) {
-        const int c = tid / kBlock, l = tid % kBlock;
-        const double v = (double)s_row[0][c][l] + (double)s_row[1][c][l] + (double)s_row[2][c][l] +
-                         (double)s_row[3][c][l];
-        eipart[3 * ((size_t)I * kBlock + l) + c] = v;
-    }
-    (void)si;
-}
 
 // next basis vector: v = alpha (ereal + cself vprev), or v0 = alpha e when ereal is NULL; the
 // pair kernel's copy of it is written to pv for the following real-space product
@@ -930,15 +830,6 @@ __global__ __launch_bounds__(256) void k_guess_norm_final(int nparts, int64_t n,
 // ------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------
-template <typename R> static void launch_radial(amoeba_ctx* c, R* jbuf, const void* jrel, const void* off)
-{
-    using R4 = typename V4R<R>::T;
-    const R L0 = (R)c->prm.box[0], L1 = (R)c->prm.box[1], L2 = (R)c->prm.box[2];
-    hipLaunchKernelGGL(k_guess_radial<R>, dim3(c->nb), dim3(256), 0, c->stream, c->blk_tile0, c->tile_mask,
-                       (const R4*)jrel, (const R4*)off, L0, L1, L2, (R)(1.0 / c->prm.box[0]),
-                       (R)(1.0 / c->prm.box[1]), (R)(1.0 / c->prm.box[2]), c->eipart, jbuf);
-}
-
 static int guess_alloc_config(amoeba_ctx* c)
 {
     if (c->g_v)
@@ -1003,21 +894,8 @@ int guess_compute(amoeba_ctx* c)
     // the radial sums (a walk over every tile) only for the Neumann kind; the delta kind's
     // features leave them out (zero)
     const bool radial = c->g_kind == AMOEBA_GUESS_KIND_NEUMANN;
-    if (radial) {
-        {
-            StageTimer tm(c, AMOEBA_T_GUESS);
-            if (c->ntiles > 0) {
-                if (c->mixed)
-                    launch_radial<float>(c, (float*)c->jbuf, c->jrel_f, c->off_f);
-                else
-                    launch_radial<double>(c, (double*)c->jbuf, c->jrel_d, c->off_d);
-            }
-        }
-        if (c->ntiles > 0)
-            launch_real_reduce(c, c->g_radial);
-        else
-            hipMemsetAsync(c->g_radial, 0, sizeof(double) * n3, c->stream);
-    }
+    if (radial)
+        launch_radial_sums(c, c->g_radial);
     StageTimer tm(c, AMOEBA_T_GUESS);
     hipLaunchKernelGGL(k_guess_features, dim3(g), dim3(256), 0, c->stream, c->npad, c->perm, c->par_d, c->g_v,
                        radial ? c->g_radial : nullptr, 0, c->g_feat, c->g_basis);

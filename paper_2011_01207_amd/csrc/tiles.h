@@ -65,6 +65,8 @@ __device__ __forceinline__ double d_erfc_g(double x, double) { return erfc(x); }
 // hardware reciprocal square root (1 ulp); pair distances are far above the FP32 denormal range
 __device__ __forceinline__ float d_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double d_rsqrt(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ float d_length(float r2) { return r2 * __builtin_amdgcn_rsqf(r2); }
+__device__ __forceinline__ double d_length(double r2) { return sqrt(r2); }
 __device__ __forceinline__ float d_rint(float x) { return rintf(x); }
 __device__ __forceinline__ double d_rint(double x) { return rint(x); }
 
@@ -500,6 +502,34 @@ template <typename R> struct ForceKind {
         for (int c = 0; c < 3; ++c) {
             ei[c] += G[c];
             ej[c] = -G[c];
+        }
+    }
+};
+
+// Radial neighbour sums of the learned guess: per atom the sum over its in-cutoff neighbours of
+// exp(-((r - c) / 0.6 A)^2) for c = 1, 2, 3 A.  Both atoms of a pair get the same three terms.
+constexpr double kRadialC[3] = {1.0, 2.0, 3.0};
+constexpr double kRadialInvW = 1.0 / 0.6;
+template <typename R> struct RadialKind {
+    using R4 = typename V4<R>::T;
+    static constexpr int NV = 1;
+    static constexpr int kMinWaves = 1;
+    static constexpr bool kScaledJ = false, kScaleJSrc = false;
+    static constexpr bool kParamsInSrc = true;
+    __device__ static void scale_i(R4*, R) {}
+    __device__ static void load(const R4*, size_t, R, R4* d) { d[0] = R4{0, 0, 0, 0}; }  // no source
+    template <bool MI>
+    __device__ static void pair(const R4& ip, const R4*, const R4& jp, const R4*, const EwaldArgs<R>& ew, R* ei, R* ej)
+    {
+        R dx, dy, dz;
+        pair_disp<R, MI>(ip, jp, ew, dx, dy, dz);
+        const R r = d_length(dx * dx + dy * dy + dz * dz);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const R u = (r - (R)kRadialC[c]) * (R)kRadialInvW;
+            const R g = d_exp(-u * u);
+            ei[c] += g;
+            ej[c] = g;
         }
     }
 };

@@ -290,3 +290,22 @@ def test_gradient_at_the_edges_of_its_tiles(n):
                                y[idx].astype(np.float64))
     assert abs(loss - l_ref) < 1e-5 * l_ref
     assert rel(g.cpu().numpy(), g_ref) < 1e-4
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("waters,box", [(1, 18.63), (21, 18.63), (22, 18.63), (216, 18.63), (8640, 63.7)])
+def test_radial_sums_on_both_sides_of_the_wave_limit(waters, box, prec):
+    """The neighbour sums of one to four blocks (eight waves a block, with and without neighbours in
+    other blocks) and of 405 blocks (four waves), against the FP64 sums of sampled atoms, at the bars
+    of the features' other comparison."""
+    s = synth.water_box(waters, box, 48, 3, "water")
+    print(f"[gpu] radial sums N={s.n} {prec}", flush=True)
+    ctx, t = amoeba.context_for(s, precision=prec, device=DEV)
+    try:
+        feat, _ = ctx.guess_features(t["pos"], torch.zeros_like(t["pos"]))
+    finally:
+        ctx.close()
+    idx = np.unique(np.linspace(0, s.n - 1, 200).astype(np.int64))
+    ref = G.radial_sums(s, idx)
+    x = feat.cpu().numpy().astype(np.float64)[idx][:, 8:11]
+    assert np.max(np.abs(x - ref)) < (1e-6 if prec == "fp64" else 2e-5) * max(1.0, float(np.max(ref)))
