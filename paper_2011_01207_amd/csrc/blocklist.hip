@@ -5,8 +5,9 @@
 //   1. atoms get a key along a column-serpentine cell order: the box is cut into ny x nz
 //      columns along x whose cross-section holds about one block's worth of atoms per block
 //      length, odd columns / odd z-slabs run backwards, so consecutive atoms stay spatially
-//      adjacent across column ends; keys (with the atom index as tie-break, so all distinct)
-//      are radix-sorted, giving a deterministic order;
+//      adjacent across column ends; the atoms are ordered by key (with the atom index as
+//      tie-break, so all distinct) through buckets of about two atoms, ranked within their
+//      bucket, which gives a deterministic order;
 //   2. the sorted order is cut into 64-atom blocks (one block = one wave64); the last block is
 //      padded with phantom atoms;
 //   3. every block gets a bounding box; block pairs whose boxes come within cutoff + buffer
@@ -26,8 +27,6 @@
 #include <algorithm>
 #include <cmath>
 
-#include <rocprim/device/device_radix_sort.hpp>
-
 #include "common.h"
 #include <type_traits>
 
@@ -43,14 +42,28 @@ __device__ __forceinline__ double wrap_box(double x, double L)
 
 // Sort key of atom a: column (cz, cy) in a serpentine order, then x within the column (also
 // serpentine) quantised to kXBits bits (box / 4096, far below the block size); packed as
-// col | xq.  The sort is stable and the values are the atom indices in increasing order, so that
-// equal keys keep index order and the result is deterministic.  The largest column value is kept
-// for non-finite positions, which sort last (the gather check reports them).
+// col | xq.  Equal keys keep index order, so the order is deterministic.  The order is built from
+// buckets key >> shift, at most one per slot (about two atoms each at an even density): k_sort_keys
+// counts them and notes each atom's arrival in its bucket, k_sort_place writes the entries (key,
+// atom) bucket by bucket, k_sort_rank ranks each entry among its bucket's.  These and a scan, five
+// launches, take 34 us at 288,000 atoms, positions included; a merge sort took 21 launches and 135 us,
+// the order and positions after it 18 us more.
+// Non-finite positions go to a last bucket of their own, which is not ranked (the build reports
+// them); nor is a bucket of more than kRankMax atoms (65,536 atoms within a slice of box / 4096 or
+// a few: no list capacity holds their neighbours), so that no input makes the ranking slow.
 // Also clears the build's error flags.
 constexpr int kXBits = 12;
+constexpr int kRankMax = 65536;
+constexpr unsigned kKeyNonFinite = 0xffffffffu;
 
-__global__ void k_sort_keys(int n, const double* __restrict__ pos, double3 box, int ny, int nz, int colbits,
-                            unsigned* __restrict__ keys, int* __restrict__ vals, int* __restrict__ flags)
+__device__ __forceinline__ int bucket_of(unsigned key, int shift, int nbucket)
+{
+    return key == kKeyNonFinite ? nbucket - 1 : (int)(key >> shift);
+}
+
+__global__ void k_sort_keys(int n, const double* __restrict__ pos, double3 box, int ny, int nz, int shift,
+                            int nbucket, unsigned* __restrict__ keys, int* __restrict__ arrival,
+                            int* __restrict__ count, int* __restrict__ flags)
 {
     int a = blockIdx.x * blockDim.x + threadIdx.x;
     if (a == 0)
@@ -59,23 +72,81 @@ __global__ void k_sort_keys(int n, const double* __restrict__ pos, double3 box, 
         return;
     double x = wrap_box(pos[3 * a], box.x), y = wrap_box(pos[3 * a + 1], box.y),
            z = wrap_box(pos[3 * a + 2], box.z);
-    unsigned col, xq;
-    const unsigned xmax = (1u << kXBits) - 1u;
-    if (!(x == x) || !(y == y) || !(z == z)) {
-        col = (1u << colbits) - 1u;
-        xq = xmax;
-    } else {
+    unsigned key = kKeyNonFinite;
+    if (x == x && y == y && z == z) {
+        const unsigned xmax = (1u << kXBits) - 1u;
         int cy = min(ny - 1, (int)(y / box.y * ny));
         int cz = min(nz - 1, (int)(z / box.z * nz));
         int cys = (cz & 1) ? ny - 1 - cy : cy;
-        col = (unsigned)(cz * ny + cys);
+        const unsigned col = (unsigned)(cz * ny + cys);
         unsigned q = min(xmax, (unsigned)(x / box.x * (double)(1u << kXBits)));
         if (col & 1u)
             q = xmax - q;
-        xq = q;
+        key = (col << kXBits) | q;
     }
-    keys[a] = (col << kXBits) | xq;
-    vals[a] = a;
+    keys[a] = key;
+    arrival[a] = atomicAdd(&count[bucket_of(key, shift, nbucket)], 1);
+}
+
+__global__ void k_sort_place(int n, int shift, int nbucket, const unsigned* __restrict__ keys,
+                             const int* __restrict__ arrival, const int* __restrict__ start,
+                             int* __restrict__ count, unsigned long long* __restrict__ entry)
+{
+    const int a = blockIdx.x * blockDim.x + threadIdx.x;
+    if (a >= n)
+        return;
+    const unsigned key = keys[a];
+    const int b = bucket_of(key, shift, nbucket), r = arrival[a];
+    entry[start[b] + r] = (unsigned long long)key << 32 | (unsigned)a;
+    if (r == 0)
+        count[b] = 0;  // the counters are zero between their uses
+}
+
+// The order (perm, slot), and each atom's position (wrapped into the box) at its slot, also as the
+// reference of the staleness test.  Phantom slots (perm < 0) hold zeros.
+__global__ __launch_bounds__(256) void k_sort_rank(int n, int npad, int shift, int nbucket,
+                                                   const unsigned long long* __restrict__ entry,
+                                                   const int* __restrict__ start, const double* __restrict__ pos,
+                                                   double3 box, int* __restrict__ perm, int* __restrict__ slot,
+                                                   double4* __restrict__ pos_s, double4* __restrict__ pos_ref,
+                                                   int* __restrict__ flags)
+{
+    __shared__ int s_f;
+    if (threadIdx.x == 0)
+        s_f = 0;
+    __syncthreads();
+    const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p < npad) {
+        int dst = p, a = -1;
+        double x = 0.0, y = 0.0, z = 0.0;
+        if (p < n) {
+            const unsigned long long e = entry[p];
+            const unsigned key = (unsigned)(e >> 32);
+            a = (int)(unsigned)e;
+            x = pos[3 * (size_t)a];
+            y = pos[3 * (size_t)a + 1];
+            z = pos[3 * (size_t)a + 2];
+            const int b = bucket_of(key, shift, nbucket), s0 = start[b], s1 = start[b + 1];
+            if (key != kKeyNonFinite && s1 - s0 <= kRankMax) {
+                dst = s0;
+                for (int q = s0; q < s1; ++q)
+                    dst += entry[q] < e ? 1 : 0;
+            }
+            if (!isfinite(x) || !isfinite(y) || !isfinite(z)) {
+                atomicOr(&s_f, kFlagNonFinite);
+                x = y = z = 0.0;
+            }
+            x = wrap_box(x, box.x);
+            y = wrap_box(y, box.y);
+            z = wrap_box(z, box.z);
+            slot[a] = dst;
+        }
+        perm[dst] = a;
+        pos_s[dst] = pos_ref[dst] = make_double4(x, y, z, 0.0);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_f != 0)
+        atomicOr(flags, s_f);
 }
 
 // Two-phase exclusive scan for long arrays: block sums (1024 per workgroup), then block-local
@@ -151,31 +222,20 @@ __global__ __launch_bounds__(256) void k_scan_apply(int n, const int* __restrict
 }
 
 
-__global__ void k_perm(int n, int npad, const int* __restrict__ sorted_atoms, int* __restrict__ perm,
-                       int* __restrict__ slot)
-{
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= npad)
-        return;
-    if (s < n) {
-        int a = sorted_atoms[s];
-        perm[s] = a;
-        slot[a] = s;
-    } else {
-        perm[s] = -1;
-    }
-}
-
-// Per-slot parameters and the slot's count of scaled pairs (the CSR in slot order).
+// Per-slot parameters and the slot's count of scaled pairs (the CSR in slot order).  The Thole
+// factor also goes into w of the dipole tiles' source copy pv (the vector kernels that fill it
+// write x, y, z only), so that the tiles read a j atom's dipole and factor in one load.
+template <typename R>
 __global__ void k_params(int npad, const int* __restrict__ perm, const double* __restrict__ alpha,
                          const double* __restrict__ thole, double4* __restrict__ pd, float4* __restrict__ pf,
                          double* __restrict__ as, double* __restrict__ ais, const int* __restrict__ ptr_in,
-                         int* __restrict__ cnt)
+                         int* __restrict__ cnt, R* __restrict__ pv)
 {
     int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= npad)
         return;
     int a = perm[s];
+    pv[4 * (size_t)s + 3] = a >= 0 ? (R)thole[a] : (R)0;
     cnt[s] = a >= 0 ? ptr_in[a + 1] - ptr_in[a] : 0;
     double al = a >= 0 ? alpha[a] : 1.0;
     double th = a >= 0 ? thole[a] : 0.0;
@@ -267,11 +327,38 @@ __global__ void k_csr_fill(int npad, const int* __restrict__ perm, const int* __
     }
 }
 
+// Block origin = FP64 position of the block's first atom; per-atom minimum-image offsets.  Called by
+// all 64 lanes of a wave, lane l with slot l of one block (its position, and whether it is an atom);
+// returns the lane's offset.
+__device__ __forceinline__ double lane0(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                            __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
+__device__ __forceinline__ double3 block_frame(int s, bool real, double x, double y, double z, double3 box,
+                                               double4* __restrict__ org, double4* __restrict__ off_d,
+                                               float4* __restrict__ off_f)
+{
+    const double ox = lane0(x), oy = lane0(y), oz = lane0(z);
+    if ((s & (kBlock - 1)) == 0)
+        org[s / kBlock] = make_double4(ox, oy, oz, 0.0);
+    double dx = 0.0, dy = 0.0, dz = 0.0;
+    if (real) {
+        dx = mimg(x - ox, box.x);
+        dy = mimg(y - oy, box.y);
+        dz = mimg(z - oz, box.z);
+    }
+    off_d[s] = make_double4(dx, dy, dz, 0.0);
+    off_f[s] = make_float4((float)dx, (float)dy, (float)dz, 0.0f);
+    return make_double3(dx, dy, dz);
+}
+
 // Caller positions into slot order (one thread per slot: the slot's reads and writes are
 // coalesced, the only scattered access is the read of its atom's caller-order position), wrapped
 // into the box; flags NaN/Inf, a changed configuration and (if a reference exists) atoms that
-// moved more than buffer/2 since the list build.  ref_out (list build): also keep the positions
-// as the reference of the staleness test.  Phantom slots (perm < 0) hold zeros.
+// moved more than buffer/2 since the list build.  Phantom slots (perm < 0) hold zeros.  A wave's 64
+// slots are a block, whose frame is written along (block_frame).
 // Flags go to one device word that every workgroup may set; same-address device atomics are
 // serialized, so each workgroup ORs its flags in LDS first and issues at most one atomic, and
 // the grid is capped at kScatterWG workgroups (grid-stride loop).
@@ -281,7 +368,8 @@ __global__ __launch_bounds__(256) void k_gather_pos(int npad, const int* __restr
                                                     const double* __restrict__ pos, double3 box,
                                                     double4* __restrict__ pos_s, const double4* __restrict__ ref,
                                                     double half_buf2, int* __restrict__ flags,
-                                                    double4* __restrict__ ref_out)
+                                                    double4* __restrict__ org, double4* __restrict__ off_d,
+                                                    float4* __restrict__ off_f)
 {
     __shared__ int s_f;
     if (threadIdx.x == 0)
@@ -335,8 +423,7 @@ __global__ __launch_bounds__(256) void k_gather_pos(int npad, const int* __restr
                 }
             }
             pos_s[s] = make_double4(x, y, z, 0.0);
-            if (ref_out)
-                ref_out[s] = make_double4(x, y, z, 0.0);
+            block_frame(s, a[u] >= 0, x, y, z, box, org, off_d, off_f);
         }
     }
     if (f != 0)
@@ -346,44 +433,23 @@ __global__ __launch_bounds__(256) void k_gather_pos(int npad, const int* __restr
         atomicOr(flags, s_f);
 }
 
-// Block origin = FP64 position of the block's first atom; per-atom minimum-image offsets.
-__global__ void k_block_frame(int npad, const int* __restrict__ perm, const double4* __restrict__ pos_s,
-                              double3 box, double4* __restrict__ org, double4* __restrict__ off_d,
-                              float4* __restrict__ off_f)
+// Frame of each block, and its bounding box in coordinates unwrapped around its first atom (one
+// block per wave).
+__global__ __launch_bounds__(256) void k_bbox(int nb, const int* __restrict__ perm,
+                                              const double4* __restrict__ pos_s, double3 box,
+                                              double4* __restrict__ bc, double4* __restrict__ bh,
+                                              double4* __restrict__ org, double4* __restrict__ off_d,
+                                              float4* __restrict__ off_f)
 {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= npad)
+    const int lane = threadIdx.x & 63;
+    const int I = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (I >= nb)
         return;
-    int I = s / kBlock;
-    double4 o = pos_s[I * kBlock];
-    if ((s & (kBlock - 1)) == 0)
-        org[I] = o;
-    double4 p = pos_s[s];
-    double dx = 0.0, dy = 0.0, dz = 0.0;
-    if (perm[s] >= 0) {
-        dx = mimg(p.x - o.x, box.x);
-        dy = mimg(p.y - o.y, box.y);
-        dz = mimg(p.z - o.z, box.z);
-    }
-    off_d[s] = make_double4(dx, dy, dz, 0.0);
-    off_f[s] = make_float4((float)dx, (float)dy, (float)dz, 0.0f);
-}
-
-// Bounding box of each block in coordinates unwrapped around its first atom.
-__global__ __launch_bounds__(64) void k_bbox(int nb, const int* __restrict__ perm,
-                                             const double4* __restrict__ pos_s, double3 box,
-                                             double4* __restrict__ bc, double4* __restrict__ bh)
-{
-    int I = blockIdx.x, lane = threadIdx.x;
     int s = I * kBlock + lane;
-    double4 o = pos_s[I * kBlock];
-    double rx = 0.0, ry = 0.0, rz = 0.0;
-    if (perm[s] >= 0) {
-        double4 p = pos_s[s];
-        rx = mimg(p.x - o.x, box.x);
-        ry = mimg(p.y - o.y, box.y);
-        rz = mimg(p.z - o.z, box.z);
-    }
+    const double4 p = pos_s[s];
+    const double4 o = make_double4(lane0(p.x), lane0(p.y), lane0(p.z), 0.0);
+    const double3 r = block_frame(s, perm[s] >= 0, p.x, p.y, p.z, box, org, off_d, off_f);
+    const double rx = r.x, ry = r.y, rz = r.z;
     double mnx = rx, mny = ry, mnz = rz, mxx = rx, mxy = ry, mxz = rz;
     for (int off = 32; off > 0; off >>= 1) {
         mnx = fmin(mnx, __shfl_xor(mnx, off));
@@ -400,6 +466,24 @@ __global__ __launch_bounds__(64) void k_bbox(int nb, const int* __restrict__ per
     }
 }
 
+// Exclusive prefix sum over the 64 lanes of a wave (all lanes active) and the wave total, by
+// data-parallel primitives: shifts by 1, 2, 4, 8 lanes within each row of 16, then row 0's total
+// into row 1 and row 2's into row 3 (broadcast of lane 15 of the row before), then the first two
+// rows' total into rows 2 and 3 (broadcast of lane 31).  Lanes a shift or broadcast does not
+// reach add 0.
+__device__ __forceinline__ int wave_excl_scan_i(int x, int& total)
+{
+    int v = x;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 -> rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 -> rows 2, 3
+    total = __builtin_amdgcn_readlane(v, 63);
+    return v - x;
+}
+
 // Block grid of the candidate search.  grid[0] = 1 when it is used, grid[1..3] = cells per
 // axis.  A cell is at least 2 h_max + rcb (+ a margin) wide on every axis, h_max the largest
 // block half-extent on that axis, so two blocks whose boxes come within rcb have centres
@@ -409,25 +493,44 @@ constexpr double kCellMargin = 0.01;  // A
 
 __device__ __forceinline__ int cell_of(double v, double L, int n)
 {
-    const double y = wrap_box(v, L) * (double)n / L;
+    // rounding may take a centre at a cell's face to the cell beside it: the width's margin covers that
+    const double f = v * (1.0 / L), y = (f - floor(f)) * (double)n;
     const int c = (y == y) ? (int)y : 0;  // a non-finite centre (reported by the build) goes to cell 0
     return min(max(c, 0), n - 1);
 }
 
-// One workgroup: the largest half-extent per axis (ext_out, read by the host after the build),
-// and the grid shape.
-__global__ __launch_bounds__(1024) void k_block_grid(int nb, const double4* __restrict__ bh, double3 box,
-                                                     double rcb, int3 ncap, double* __restrict__ ext_out,
-                                                     int* __restrict__ grid)
+// One workgroup: the largest half-extent per axis (ext_out, read by the host after the build), the
+// grid shape, and the blocks counted into cells: cell_start[c] = first entry of cell c.  The
+// counters (at most kGridCells cells) are in LDS; `entry` keeps each block's cell and arrival there,
+// `unranked` the blocks cell by cell, which k_cell_rank puts in index order within their cell.
+// 10 and 5 us for 4,500 blocks; a merge sort of the cells and a search for their starts took eight
+// launches and 30 us.
+constexpr int kGridCells = 12288;
+
+__global__ __launch_bounds__(1024) void k_block_grid(int nb, const double4* __restrict__ bc,
+                                                     const double4* __restrict__ bh, double3 box, double rcb,
+                                                     int3 ncap, double* __restrict__ ext_out,
+                                                     int* __restrict__ grid, int2* __restrict__ entry,
+                                                     int* __restrict__ unranked, int* __restrict__ cell_start)
 {
     __shared__ double s_m[3][16];
+    __shared__ int s_n[4];
+    __shared__ int s_w[16];
+    __shared__ int s_cnt[kGridCells];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     double m[3] = {0.0, 0.0, 0.0};
-    for (int b = tid; b < nb; b += 1024) {
-        const double4 h = bh[b];
-        m[0] = fmax(m[0], h.x);
-        m[1] = fmax(m[1], h.y);
-        m[2] = fmax(m[2], h.z);
+    constexpr int U = 4;  // blocks per thread and round, their loads in flight together
+    for (int b0 = tid; b0 < nb; b0 += U * 1024) {
+        double4 h[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            h[u] = bh[min(b0 + u * 1024, nb - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            m[0] = fmax(m[0], h[u].x);
+            m[1] = fmax(m[1], h[u].y);
+            m[2] = fmax(m[2], h[u].z);
+        }
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -448,67 +551,82 @@ __global__ __launch_bounds__(1024) void k_block_grid(int nb, const double4* __re
             ext_out[a] = e;
             const double cells = floor(L[a] / (2.0 * e + rcb + kCellMargin));
             const int nc = cells >= (double)cap[a] ? cap[a] : (int)fmax(cells, 1.0);
-            grid[1 + a] = nc;
+            grid[1 + a] = s_n[1 + a] = nc;
             use = use && nc >= 3;
         }
-        grid[0] = use ? 1 : 0;
+        grid[0] = s_n[0] = use ? 1 : 0;
+    }
+    __syncthreads();
+    if (!s_n[0])
+        return;
+    const int nx = s_n[1], ny = s_n[2], nz = s_n[3], ncell = nx * ny * nz;
+    for (int k = tid; k < ncell; k += 1024)
+        s_cnt[k] = 0;
+    __syncthreads();
+    for (int b0 = tid; b0 < nb; b0 += U * 1024) {
+        double4 c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            c[u] = bc[min(b0 + u * 1024, nb - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int b = b0 + u * 1024;
+            if (b < nb) {
+                const int key = (cell_of(c[u].z, box.z, nz) * ny + cell_of(c[u].y, box.y, ny)) * nx +
+                                cell_of(c[u].x, box.x, nx);
+                entry[b] = make_int2(key, atomicAdd(&s_cnt[key], 1));
+            }
+        }
+    }
+    __syncthreads();
+    // exclusive scan of the counters, thread t holding P consecutive ones
+    const int P = (ncell + 1023) / 1024;
+    int sum = 0;
+    for (int u = 0; u < P; ++u)
+        sum += tid * P + u < ncell ? s_cnt[tid * P + u] : 0;
+    int tot;
+    const int ex = wave_excl_scan_i(sum, tot);
+    if (lane == 0)
+        s_w[w] = tot;
+    __syncthreads();
+    int run = ex;
+    for (int k = 0; k < w; ++k)
+        run += s_w[k];
+    for (int u = 0; u < P; ++u)
+        if (tid * P + u < ncell) {
+            const int v = s_cnt[tid * P + u];
+            s_cnt[tid * P + u] = run;
+            cell_start[tid * P + u] = run;
+            run += v;
+        }
+    if (tid == 0)
+        cell_start[ncell] = nb;
+    __syncthreads();
+    for (int b0 = tid; b0 < nb; b0 += U * 1024) {
+        int2 e[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            e[u] = entry[min(b0 + u * 1024, nb - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (b0 + u * 1024 < nb)
+                unranked[s_cnt[e[u].x] + e[u].y] = b0 + u * 1024;
     }
 }
 
-// Sort key of block b: its cell (x fastest), or 0 when the grid is not used.
-__global__ void k_block_cell(int nb, const double4* __restrict__ bc, double3 box, const int* __restrict__ grid,
-                             unsigned* __restrict__ keys, int* __restrict__ vals)
+__global__ void k_cell_rank(int nb, const int* __restrict__ grid, const int2* __restrict__ entry,
+                            const int* __restrict__ unranked, const int* __restrict__ cell_start,
+                            int* __restrict__ cell_blk)
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb)
+    if (b >= nb || !grid[0])
         return;
-    unsigned key = 0u;
-    if (grid[0]) {
-        const double4 c = bc[b];
-        const int nx = grid[1], ny = grid[2], nz = grid[3];
-        key = (unsigned)((cell_of(c.z, box.z, nz) * ny + cell_of(c.y, box.y, ny)) * nx + cell_of(c.x, box.x, nx));
-    }
-    keys[b] = key;
-    vals[b] = b;
-}
-
-// cell_start[c] = the first position of cell c in the sorted keys (c = 0 .. number of cells).
-__global__ void k_cell_start(int nb, int ncell_cap, const unsigned* __restrict__ skeys, const int* __restrict__ grid,
-                             int* __restrict__ cell_start)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    const int ncell = grid[0] ? grid[1] * grid[2] * grid[3] : 0;
-    if (c > ncell || c > ncell_cap)
-        return;
-    int lo = 0, hi = nb;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (skeys[mid] < (unsigned)c)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    cell_start[c] = lo;
-}
-
-
-// Exclusive prefix sum over the 64 lanes of a wave (all lanes active) and the wave total, by
-// data-parallel primitives: shifts by 1, 2, 4, 8 lanes within each row of 16, then row 0's total
-// into row 1 and row 2's into row 3 (broadcast of lane 15 of the row before), then the first two
-// rows' total into rows 2 and 3 (broadcast of lane 31).  Lanes a shift or broadcast does not
-// reach add 0.
-__device__ __forceinline__ int wave_excl_scan_i(int x, int lane, int& total)
-{
-    (void)lane;
-    int v = x;
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 -> rows 1, 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 -> rows 2, 3
-    total = __builtin_amdgcn_readlane(v, 63);
-    return v - x;
+    const int key = entry[b].x, s0 = cell_start[key], s1 = cell_start[key + 1];
+    int dst = s0;
+#pragma unroll 4
+    for (int q = s0; q < s1; ++q)
+        dst += unranked[q] < b ? 1 : 0;
+    cell_blk[dst] = b;
 }
 
 // Whether j (offset from the i-block centre, inside rcb of the block's box) lies within rf2 of an
@@ -727,7 +845,7 @@ __global__ __launch_bounds__(256) void k_filter(int nb, const int* __restrict__ 
             // queue of those atoms: candidate k owns entries s_qoff[k] .. s_qoff[k+1]-1
             const int k = tid;
             int tot;
-            const int ex = wave_excl_scan_i(k < nc ? __popcll(s_inb[k]) : 0, lane, tot);
+            const int ex = wave_excl_scan_i(k < nc ? __popcll(s_inb[k]) : 0, tot);
             if (lane == 0)
                 s_wk[w] = tot;
             __syncthreads();
@@ -764,7 +882,7 @@ __global__ __launch_bounds__(256) void k_filter(int nb, const int* __restrict__ 
             // ordered exclusive scan of the kept counts (wave w holds candidates 64w .. 64w+63)
             const int k = tid;
             int tot;
-            const int ex = wave_excl_scan_i(k < nc ? __popcll(s_keep[k]) : 0, lane, tot);
+            const int ex = wave_excl_scan_i(k < nc ? __popcll(s_keep[k]) : 0, tot);
             if (lane == 0)
                 s_wk[w] = tot;
             __syncthreads();
@@ -958,7 +1076,7 @@ __global__ __launch_bounds__(256) void k_tile_refresh(int ntiles, const int* __r
     // per configuration instead of by every product.
     {
         int P;
-        const int off = wave_excl_scan_i(__popcll(m), lane, P);
+        const int off = wave_excl_scan_i(__popcll(m), P);
         s_off[w][lane] = off;
         s_m[w][lane] = m;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1049,24 +1167,21 @@ int device_scan(amoeba_ctx* c, int n, const int* in, int* out, int* total_copy)
     return AMOEBA_OK;
 }
 
-// Thole factor of every slot into w of the dipole tiles' source copy (the vector kernels that
-// fill it write x, y, z only), so that the tiles read a j atom's dipole and factor in one load.
-template <typename R>
-__global__ void k_pv_thole(int npad, const double4* __restrict__ par, R* __restrict__ pv)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < npad)
-        pv[4 * (size_t)s + 3] = (R)par[s].w;
-}
-
 int sort_params(amoeba_ctx* c)
 {
     hipStream_t st = c->stream;
     coef_invalidate(c);  // the coefficients depend on the polarizabilities and Thole factors
     // parameters and the scaled-pair CSR in slot order
     int* cnt = c->b_cnt;
-    hipLaunchKernelGGL(k_params, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->perm, c->alpha_in,
-                       c->thole_in, c->par_d, c->par_f, c->alpha_s, c->alpha_inv_s, c->sc_ptr_in, cnt);
+    auto params = [&](auto* pv) {
+        using R = std::remove_pointer_t<decltype(pv)>;
+        hipLaunchKernelGGL(k_params<R>, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->perm, c->alpha_in,
+                           c->thole_in, c->par_d, c->par_f, c->alpha_s, c->alpha_inv_s, c->sc_ptr_in, cnt, pv);
+    };
+    if (c->mixed)
+        params((float*)c->pv_f);
+    else
+        params((double*)c->pv_d);
     int rcs = device_scan(c, c->npad, cnt, c->sc_ptr);
     if (rcs)
         return rcs;
@@ -1076,12 +1191,6 @@ int sort_params(amoeba_ctx* c)
     if (c->n_scaled > 0 && c->dscales_set)  // the same pairs, their direct scales (sc_j rewritten alike)
         hipLaunchKernelGGL(k_csr_fill, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->perm, c->slot,
                            c->sc_ptr_in, c->sc_j_in, c->sc_sd_in, c->sc_ptr, c->sc_j, c->sc_sd);
-    if (c->mixed)
-        hipLaunchKernelGGL(k_pv_thole<float>, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->par_d,
-                           (float*)c->pv_f);
-    else
-        hipLaunchKernelGGL(k_pv_thole<double>, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->par_d,
-                           (double*)c->pv_d);
     // the tiles' j records carry the slots' polarizability factors: refresh them before the
     // next product
     c->cfg_valid = false;
@@ -1115,8 +1224,6 @@ static int refresh_tiles(amoeba_ctx* c)
     StageTimer tm(c, AMOEBA_T_LIST);
     hipStream_t st = c->stream;
     double3 box = make_double3(c->prm.box[0], c->prm.box[1], c->prm.box[2]);
-    hipLaunchKernelGGL(k_block_frame, dim3(nblk(c->npad, 256)), dim3(256), 0, st, c->npad, c->perm, c->pos_s, box,
-                       c->blk_org, c->off_d, c->off_f);
     double3 binv = make_double3(1.0 / box.x, 1.0 / box.y, 1.0 / box.z);
     const int nwg = nblk((long)c->ntiles * kBlock, 256);
     hipLaunchKernelGGL(c->skip_mimg ? k_tile_refresh<false> : k_tile_refresh<true>, dim3(nwg), dim3(256), 0, st,
@@ -1146,21 +1253,18 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
     double edge = cbrt(kBlock * vol / n);
     int ny = (int)fmin(255.0, fmax(1.0, floor(box.y / edge + 0.5)));
     int nz = (int)fmin(255.0, fmax(1.0, floor(box.z / edge + 0.5)));
-    auto bits_for = [](long long v) {  // bits of the values 0 .. v-1
-        int b = 1;
-        while ((1ll << b) < v)
-            ++b;
-        return b;
-    };
-    const int colbits = bits_for((long long)ny * nz) + 1;
-    const unsigned end_bit = (unsigned)(kXBits + colbits);
+    // at most npad buckets, the last one for non-finite positions
+    const long long nkeys = (long long)ny * nz << kXBits;
+    int shift = 0;
+    while (((nkeys - 1) >> shift) + 2 > npad)
+        ++shift;
+    const int nbucket = (int)((nkeys - 1) >> shift) + 2;
 
     int rc = AMOEBA_OK;
     if (!c->b_keys) {
         if ((rc = ctx_alloc(c, (void**)&c->b_keys, sizeof(unsigned) * n)) ||
-            (rc = ctx_alloc(c, (void**)&c->b_keys2, sizeof(unsigned) * n)) ||
-            (rc = ctx_alloc(c, (void**)&c->b_vals, sizeof(int) * n)) ||
-            (rc = ctx_alloc(c, (void**)&c->b_vals2, sizeof(int) * n)) ||
+            (rc = ctx_alloc(c, (void**)&c->b_entry, sizeof(unsigned long long) * n)) ||
+            (rc = ctx_alloc(c, (void**)&c->b_cell_blk, sizeof(int) * nb)) ||
             (rc = ctx_alloc(c, (void**)&c->b_bc, sizeof(double4) * nb)) ||
             (rc = ctx_alloc(c, (void**)&c->b_bh, sizeof(double4) * nb)) ||
             (rc = ctx_alloc(c, (void**)&c->b_rowc, sizeof(int) * nb)) ||
@@ -1169,12 +1273,12 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
             (rc = ctx_alloc(c, (void**)&c->rev_cnt, sizeof(int) * (npad + 1))))
             return rc;
         // block grid: at most floor(L / rcb) cells per axis (the cell width is at least rcb),
-        // and not many more cells than blocks
+        // and not many more cells than blocks (nor than the grid kernel has counters)
         const double rcb = c->prm.cutoff + c->prm.buffer;
         for (int a = 0; a < 3; ++a)
             c->b_ncap[a] = (int)std::max(1.0, std::min(1024.0, std::floor(c->prm.box[a] / rcb)));
         auto ncells = [&]() { return (long long)c->b_ncap[0] * c->b_ncap[1] * c->b_ncap[2]; };
-        while (ncells() > 2ll * nb + 27) {
+        while (ncells() > std::min(2ll * nb + 27, (long long)kGridCells)) {
             int* big = std::max_element(c->b_ncap, c->b_ncap + 3);
             if (*big <= 3)
                 break;
@@ -1183,18 +1287,7 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
         c->b_ncell_cap = (int)ncells();
         if ((rc = ctx_alloc(c, (void**)&c->b_cell_start, sizeof(int) * ((size_t)c->b_ncell_cap + 1))))
             return rc;
-        size_t tb = 0, tb2 = 0;
-        if (rocprim::radix_sort_pairs(nullptr, tb, c->b_keys, c->b_keys2, c->b_vals, c->b_vals2, n, 0u, 32u, st) !=
-                hipSuccess ||
-            rocprim::radix_sort_pairs(nullptr, tb2, c->b_keys, c->b_keys2, c->b_vals, c->b_vals2, nb, 0u, 32u, st) !=
-                hipSuccess)
-            return set_error(c, AMOEBA_E_DEVICE, "build_blocklist: radix sort size query failed");
-        tb = std::max(tb, tb2);
-        if ((rc = ctx_alloc(c, &c->b_sort_tmp, tb)))
-            return rc;
-        c->b_sort_bytes = tb;
     }
-    unsigned* keys = c->b_keys;
     double4 *bc = c->b_bc, *bh = c->b_bh;
     int *row_count = c->b_rowc, *row_j = c->b_rowj, *tpb = c->b_tpb, *t0 = c->blk_tile0;
     auto fail = [&](int code) { return code; };
@@ -1202,39 +1295,33 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
     // count, flags[4..9] the largest block half-extents (b_extent); flags[16..19] the block grid
     // (device only)
     int* grid = c->flags + 16;
-    hipLaunchKernelGGL(k_sort_keys, dim3(nblk(n, 256)), dim3(256), 0, st, n, pos, box, ny, nz, colbits, keys,
-                       c->b_vals, c->flags);
-    {
-        size_t tb = c->b_sort_bytes;
-        if (rocprim::radix_sort_pairs(c->b_sort_tmp, tb, keys, c->b_keys2, c->b_vals, c->b_vals2, n, 0u, end_bit,
-                                      st) != hipSuccess)
-            return set_error(c, AMOEBA_E_DEVICE, "build_blocklist: radix sort failed");
+    // rev_cnt, zero between its uses, counts the buckets; rev_ptr and b_cnt serve until their own use
+    int *arrival = c->b_cnt, *start = c->rev_ptr;
+    hipLaunchKernelGGL(k_sort_keys, dim3(nblk(n, 256)), dim3(256), 0, st, n, pos, box, ny, nz, shift, nbucket,
+                       c->b_keys, arrival, c->rev_cnt, c->flags);
+    if ((rc = device_scan(c, nbucket, c->rev_cnt, start))) {
+        hipMemsetAsync(c->rev_cnt, 0, sizeof(int) * (npad + 1), st);
+        return rc;
     }
-    hipLaunchKernelGGL(k_perm, dim3(nblk(npad, 256)), dim3(256), 0, st, n, npad, c->b_vals2, c->perm, c->slot);
+    hipLaunchKernelGGL(k_sort_place, dim3(nblk(n, 256)), dim3(256), 0, st, n, shift, nbucket, c->b_keys, arrival,
+                       start, c->rev_cnt, c->b_entry);
+    hipLaunchKernelGGL(k_sort_rank, dim3(nblk(npad, 256)), dim3(256), 0, st, n, npad, shift, nbucket, c->b_entry,
+                       start, pos, box, c->perm, c->slot, c->pos_s, c->pos_ref, c->flags);
     if (c->atoms_set && (rc = sort_params(c)) != AMOEBA_OK)
         return fail(rc);
 
-    hipLaunchKernelGGL(k_gather_pos, dim3(std::min(nblk(npad, 256), kScatterWG)), dim3(256), 0, st, npad, c->perm,
-                       pos, box, c->pos_s, (const double4*)nullptr, 0.0, c->flags, c->pos_ref);
-    hipLaunchKernelGGL(k_bbox, dim3(nb), dim3(64), 0, st, nb, c->perm, c->pos_s, box, bc, bh);
+    hipLaunchKernelGGL(k_bbox, dim3(nblk(nb, 4)), dim3(256), 0, st, nb, c->perm, c->pos_s, box, bc, bh, c->blk_org,
+                       c->off_d, c->off_f);
     const double rcb = c->prm.cutoff + c->prm.buffer;
-    hipLaunchKernelGGL(k_block_grid, dim3(1), dim3(1024), 0, st, nb, bh, box, rcb,
-                       make_int3(c->b_ncap[0], c->b_ncap[1], c->b_ncap[2]), c->b_extent, grid);
-    hipLaunchKernelGGL(k_block_cell, dim3(nblk(nb, 256)), dim3(256), 0, st, nb, bc, box, grid, c->b_keys,
-                       c->b_vals);
-    {
-        // stable: the blocks of a cell stay in index order
-        size_t tb = c->b_sort_bytes;
-        const unsigned cell_bits = (unsigned)bits_for((long long)c->b_ncell_cap + 1);
-        if (rocprim::radix_sort_pairs(c->b_sort_tmp, tb, c->b_keys, c->b_keys2, c->b_vals, c->b_vals2, nb, 0u,
-                                      cell_bits, st) != hipSuccess)
-            return set_error(c, AMOEBA_E_DEVICE, "build_blocklist: block sort failed");
-    }
-    hipLaunchKernelGGL(k_cell_start, dim3(nblk(c->b_ncell_cap + 1, 256)), dim3(256), 0, st, nb, c->b_ncell_cap,
-                       c->b_keys2, grid, c->b_cell_start);
+    // the entries' space serves as the blocks' (key, arrival) and the keys' as the unranked order
+    hipLaunchKernelGGL(k_block_grid, dim3(1), dim3(1024), 0, st, nb, bc, bh, box, rcb,
+                       make_int3(c->b_ncap[0], c->b_ncap[1], c->b_ncap[2]), c->b_extent, grid, (int2*)c->b_entry,
+                       (int*)c->b_keys, c->b_cell_start);
+    hipLaunchKernelGGL(k_cell_rank, dim3(nblk(nb, 256)), dim3(256), 0, st, nb, grid, (const int2*)c->b_entry,
+                       (const int*)c->b_keys, c->b_cell_start, c->b_cell_blk);
     double3 binv = make_double3(1.0 / box.x, 1.0 / box.y, 1.0 / box.z);
     hipLaunchKernelGGL(k_filter, dim3(nb), dim3(256), 0, st, nb, c->perm, c->pos_s, bc, bh, c->b_extent, grid,
-                       c->b_vals2, c->b_cell_start, box, binv, rcb, row_count, row_j, tpb, c->flags);
+                       c->b_cell_blk, c->b_cell_start, box, binv, rcb, row_count, row_j, tpb, c->flags);
     if ((rc = device_scan(c, nb, tpb, t0, c->flags + 1)))
         return rc;
     hipMemcpyAsync(c->flags_host, c->flags, 4 * sizeof(int) + 3 * sizeof(double), hipMemcpyDeviceToHost, st);
@@ -1323,8 +1410,8 @@ int prepare_config(amoeba_ctx* c, const double* pos)
     double hb = 0.5 * c->prm.buffer;
     hipMemsetAsync(c->flags, 0, sizeof(int), st);
     hipLaunchKernelGGL(k_gather_pos, dim3(std::min(nblk(c->npad, 256), kScatterWG)), dim3(256), 0, st, c->npad,
-                       c->perm, pos, box, c->pos_s, (const double4*)c->pos_ref, hb * hb, c->flags,
-                       (double4*)nullptr);
+                       c->perm, pos, box, c->pos_s, (const double4*)c->pos_ref, hb * hb, c->flags, c->blk_org,
+                       c->off_d, c->off_f);
     hipMemcpyAsync(c->flags_host, c->flags, sizeof(int), hipMemcpyDeviceToHost, st);
     int rc = hip_check(c, hipStreamSynchronize(st), "prepare_config");
     if (rc)

@@ -297,11 +297,8 @@ struct amoeba_ctx {
 
     // list-build scratch, kept between builds
     unsigned* b_keys = nullptr;            // [n] sort keys (column | x)
-    unsigned* b_keys2 = nullptr;           // [n] sorted keys
-    int* b_vals = nullptr;                 // [n] atom indices
-    int* b_vals2 = nullptr;                // [n] atom indices in key order
-    void* b_sort_tmp = nullptr;            // radix sort scratch
-    size_t b_sort_bytes = 0;
+    unsigned long long* b_entry = nullptr; // [n] (key, atom) bucket by bucket
+    int* b_cell_blk = nullptr;             // [nb] blocks in the order of the block grid's cells
     double4* b_bc = nullptr;               // [nb] block box centres
     double4* b_bh = nullptr;               // [nb] block box half-extents
     int* b_cell_start = nullptr;           // [b_ncell_cap + 1] first entry of each cell (block grid)

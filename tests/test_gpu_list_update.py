@@ -74,3 +74,41 @@ def test_update_builds_a_missing_list_and_rejects_bad_positions():
     e = ctx.perm_field(t, *(torch.tensor(a, device=DEV) for a in (s.q, s.dip, s.quad)))
     assert_fields(e.cpu().numpy(), O.perm_field(s, "spme"), 2e-5)
     ctx.close()
+
+
+@pytest.mark.parametrize("waters,cube,box,grid", [
+    (1, 18.63, (18.63, 18.63, 18.63), (24, 24, 24)),
+    (216, 18.63, (120.0, 120.0, 120.0), (48, 48, 48)),     # a droplet: most columns and cells empty
+    (216, 18.63, (18.7, 18.7, 400.0), (20, 20, 320)),      # a slab: one column of the box holds many atoms
+    (343, 21.8, (900.0, 21.9, 21.9), (720, 24, 24)),       # all atoms in few slices of x
+    (8640, 63.7, (66.0, 64.0, 90.0), (64, 64, 96))],       # the grid of blocks, some of its cells empty
+    ids=lambda v: str(v))
+def test_order_of_uneven_systems(waters, cube, box, grid):
+    """Buckets and cells that hold many atoms or none: every pair once, the product at the bars of
+    its other comparison with the oracle, and the same bits from a second build, also after one that
+    was refused for its positions (all of them, one of them not finite)."""
+    s = synth.water_box(waters, cube, grid[0], 7, "water")
+    s = dataclasses.replace(s, box=np.array(box), grid=grid, buffer=0.5)
+    mu = 0.05 * np.random.default_rng(3).standard_normal((s.n, 3))
+    ref = O.matvec(s, mu, "spme")
+    for prec in ("fp64", "mixed"):
+        print(f"[gpu] uneven system N={s.n} box={box} {prec}", flush=True)
+        ctx, t = amoeba.context_for(s, precision=prec, device=DEV)
+        try:
+            out = ctx.dipole_matvec(t["pos"], torch.tensor(mu, device=DEV)).cpu().numpy()
+            assert ctx.info()["n_pairs"] == O.count_pairs(s)
+            for bad in (slice(None), slice(0, 1)):
+                p = t["pos"].clone()
+                p[bad] = float("nan")
+                with pytest.raises(amoeba.AmoebaError) as ei:
+                    ctx.build_blocklist(p)
+                assert ei.value.status == amoeba.AMOEBA_E_NUMERIC
+            ctx.build_blocklist(t["pos"])
+            again = ctx.dipole_matvec(t["pos"], torch.tensor(mu, device=DEV)).cpu().numpy()
+        finally:
+            ctx.close()
+        assert_fields(out, ref, 1e-12 if prec == "fp64" else 2e-6)
+        if prec == "mixed":
+            assert np.array_equal(out, again)   # fixed-point sums; FP64 sums follow the list's order
+        else:
+            assert_fields(again, ref, 1e-12)
