@@ -367,6 +367,7 @@ int amoeba_create(const amoeba_params* p, void* hip_stream, amoeba_ctx** out)
             hipEventCreateWithFlags(&c->ev[1], hipEventDisableTiming) != hipSuccess ||
             hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) != hipSuccess ||
             hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) != hipSuccess ||
+            hipEventCreateWithFlags(&c->ev_build, hipEventDisableTiming) != hipSuccess ||
             hipEventCreateWithFlags(&c->ev_pairs, hipEventDisableTiming) != hipSuccess ||
             hipStreamCreateWithFlags(&c->stream2, hipStreamNonBlocking) != hipSuccess ||
             hipStreamCreateWithFlags(&c->gstream, hipStreamNonBlocking) != hipSuccess) {
@@ -424,6 +425,8 @@ int amoeba_destroy(amoeba_ctx* c)
         hipEventDestroy(c->ev_fork);
     if (c->ev_join)
         hipEventDestroy(c->ev_join);
+    if (c->ev_build)
+        hipEventDestroy(c->ev_build);
     if (c->ev_pairs)
         hipEventDestroy(c->ev_pairs);
     for (auto& e : c->tev)

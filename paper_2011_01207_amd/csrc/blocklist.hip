@@ -629,44 +629,6 @@ __global__ void k_cell_rank(int nb, const int* __restrict__ grid, const int2* __
     cell_blk[dst] = b;
 }
 
-// Whether j (offset from the i-block centre, inside rcb of the block's box) lies within rf2 of an
-// atom of the block.  MI: apply the minimum image to every pair offset and test all atoms.
-// Without it the offsets are taken as they are, which is exact when twice the largest block
-// half-extent plus rcb stays below half the box edge (then no offset can exceed half the box);
-// the block's atoms (spatially sorted) then form eight groups of eight with their own boxes
-// (s_gc centre, s_gh half-extent, w < 0 for a group without real atoms), and a group is tested
-// atom by atom only when j comes within reach of its box (a box contains its atoms, so a group
-// it rules out holds no atom within reach).
-template <bool MI>
-__device__ __forceinline__ bool near_block(const float4* s_i, const float4* s_gc, const float4* s_gh, float jx,
-                                           float jy, float jz, float rf2, float Lx, float Ly, float Lz, float Lix,
-                                           float Liy, float Liz)
-{
-    bool keep = false;
-    for (int g = 0; g < 8 && !keep; ++g) {
-        if (!MI) {
-            const float4 c = s_gc[g], h = s_gh[g];
-            const float ex = fmaxf(fabsf(c.x - jx) - h.x, 0.0f);
-            const float ey = fmaxf(fabsf(c.y - jy) - h.y, 0.0f);
-            const float ez = fmaxf(fabsf(c.z - jz) - h.z, 0.0f);
-            if (h.w < 0.0f || ex * ex + ey * ey + ez * ez >= rf2)
-                continue;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float4 q = s_i[8 * g + u];
-            float dx = q.x - jx, dy = q.y - jy, dz = q.z - jz;
-            if (MI) {
-                dx -= Lx * rintf(dx * Lix);
-                dy -= Ly * rintf(dy * Liy);
-                dz -= Lz * rintf(dz * Liz);
-            }
-            keep = keep || (q.w != 0.0f && dx * dx + dy * dy + dz * dz < rf2);
-        }
-    }
-    return keep;
-}
-
 // Position of the r-th set bit (from 0) of m, r < popcount(m).
 __device__ __forceinline__ int nth_set_bit(unsigned long long m, int r)
 {
@@ -693,32 +655,38 @@ __device__ __forceinline__ int nth_set_bit(unsigned long long m, int r)
 // (d = nb/2 only for I < nb/2) that lie within rcb of any atom of I.  Every unordered block
 // pair is examined exactly once.  The candidate blocks J are those of the 27 grid cells around
 // I's cell (k_block_grid), in (cell, J) order, or all J = I + 1 .. I + nb/2 in d order when
-// the grid is not used.  Chunks of 256 candidates: each thread tests one candidate's bounding
-// box; the waves test the candidates' atoms against the block's box, and the atoms within reach
-// of it are queued densely and tested one per thread against the block's atoms (FP32 distances
-// with a 1e-3 A margin: the filter only has to keep a superset, the masks of every
-// configuration decide at rc in FP64); the kept atoms are written at offsets from an ordered
-// scan, so the list does not depend on scheduling.
-constexpr int kFiltChunk = 256;
+// the grid is not used.  Each thread tests one block's bounding box; the ones within reach are
+// collected, in order, until a round of boxes might not fit any more (most blocks: once), and a wave
+// takes one candidate at a time: lane l holds its atom l, atoms out of reach of I's box drop out, and
+// the squared distances of 16 of them at a time to the 64 atoms of I are four matrix instructions,
+// |q|^2 + (-2 q, 1) . (j, |j|^2), taken to the least over I's atoms.  FP32 with a 1e-3 A margin, far
+// above the rounding of the sums (offsets of 50 A: 1e-4 A^2 at the reach of 10 A, 1e-5 A): the filter
+// only has to keep a superset, the masks of every configuration decide at rc in FP64.  MI (a box
+// where twice the largest half-extent plus rcb reaches half an edge): the minimum image of every
+// pair, on the vector units.  The kept atoms are written at offsets from an ordered scan, so the list
+// does not depend on scheduling, and counted for the reverse index.
+// 76 us for 4,500 blocks; testing the queued atoms one per thread against the block's atoms on the
+// vector units, in rounds of 256 boxes, took 163 us.
+constexpr int kFiltCap = 512;  // candidates of a round
 
-__global__ __launch_bounds__(256) void k_filter(int nb, const int* __restrict__ perm,
-                                                const double4* __restrict__ pos_s,
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(256, 6) void k_filter(int nb, int n, const double4* __restrict__ pos_s,
                                                 const double4* __restrict__ bc, const double4* __restrict__ bh,
                                                 const double* __restrict__ ext_in, const int* __restrict__ grid,
                                                 const int* __restrict__ cell_blk,
                                                 const int* __restrict__ cell_start, double3 box, double3 binv,
                                                 double rcb, int* __restrict__ row_count, int* __restrict__ row_j,
-                                                int* __restrict__ tpb, int* __restrict__ flags)
+                                                int* __restrict__ tpb, int* __restrict__ rev_cnt,
+                                                int* __restrict__ flags)
 {
-    __shared__ float4 s_i[kBlock];                       // i atoms relative to the block centre, w = real atom
-    __shared__ unsigned long long s_keep[kFiltChunk];    // kept atoms of each candidate of the chunk
-    __shared__ int s_cand[kFiltChunk];
-    __shared__ int s_off[kFiltChunk + 1];
-    __shared__ int s_wn[4], s_wk[4];
-    __shared__ float4 s_gc[8], s_gh[8];                  // boxes of the eight 8-atom groups
-    __shared__ int s_cs[27], s_cp[28];                   // neighbour cells: first entry, prefix of sizes
-    __shared__ unsigned long long s_inb[kFiltChunk];     // atoms of each candidate within reach of the box
-    __shared__ int s_qoff[kFiltChunk + 1];
+    __shared__ float4 s_i[kBlock];                      // i atoms relative to the block centre, w = |.|^2
+    __shared__ __align__(16) float s_j[4][4 * kBlock];  // each wave's candidate, likewise
+    __shared__ unsigned long long s_keep[kFiltCap];     // kept atoms of each candidate
+    __shared__ int s_cand[kFiltCap];
+    __shared__ int s_off[kFiltCap + 1];
+    __shared__ int s_wn[4];
+    __shared__ int s_cs[27], s_cp[28];                  // neighbour cells: first entry, prefix of sizes
     const int I = blockIdx.x, tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
     const double4 ci = bc[I], hi = bh[I];
     const bool cells = grid[0] != 0;
@@ -737,28 +705,10 @@ __global__ __launch_bounds__(256) void k_filter(int nb, const int* __restrict__ 
     if (tid < kBlock) {
         const int si = I * kBlock + tid;
         const double4 pi = pos_s[si];
-        const bool real = perm[si] >= 0;
-        const float4 q = make_float4((float)mimg_fp64(pi.x - ci.x, box.x, binv.x),
-                                     (float)mimg_fp64(pi.y - ci.y, box.y, binv.y),
-                                     (float)mimg_fp64(pi.z - ci.z, box.z, binv.z), real ? 1.0f : 0.0f);
-        s_i[tid] = q;
-        // group box over the real atoms of lanes 8g .. 8g+7 (xor-shuffles within the group)
-        float mn[3] = {real ? q.x : 3e38f, real ? q.y : 3e38f, real ? q.z : 3e38f};
-        float mx[3] = {real ? q.x : -3e38f, real ? q.y : -3e38f, real ? q.z : -3e38f};
-#pragma unroll
-        for (int off = 1; off < 8; off <<= 1)
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                mn[a] = fminf(mn[a], __shfl_xor(mn[a], off));
-                mx[a] = fmaxf(mx[a], __shfl_xor(mx[a], off));
-            }
-        if ((tid & 7) == 0) {
-            const bool any = mn[0] <= mx[0];
-            // half-extent rounded up by 1e-4 A so the box contains its atoms despite FP32 rounding
-            s_gc[tid >> 3] = make_float4(0.5f * (mn[0] + mx[0]), 0.5f * (mn[1] + mx[1]), 0.5f * (mn[2] + mx[2]), 0.0f);
-            s_gh[tid >> 3] = make_float4(0.5f * (mx[0] - mn[0]) + 1e-4f, 0.5f * (mx[1] - mn[1]) + 1e-4f,
-                                         0.5f * (mx[2] - mn[2]) + 1e-4f, any ? 1.0f : -1.0f);
-        }
+        const float x = (float)mimg_fp64(pi.x - ci.x, box.x, binv.x), y = (float)mimg_fp64(pi.y - ci.y, box.y, binv.y),
+                    z = (float)mimg_fp64(pi.z - ci.z, box.z, binv.z);
+        // a phantom slot is far from everything
+        s_i[tid] = si < n ? make_float4(x, y, z, x * x + y * y + z * z) : make_float4(0.0f, 0.0f, 0.0f, 1e30f);
     }
     const double rcb2 = rcb * rcb;
     const float rf2 = (float)((rcb + 1e-3) * (rcb + 1e-3));
@@ -771,26 +721,48 @@ __global__ __launch_bounds__(256) void k_filter(int nb, const int* __restrict__ 
                       2.0 * ext[2] + rcb + 0.01 < 0.5 * box.z);
     const int dmax = (nb % 2 == 0 && I < nb / 2) ? nb / 2 : (nb - 1) / 2;
     __syncthreads();
-    if (cells && tid == 0) {
-        s_cp[0] = 0;
-        for (int k = 1; k <= 27; ++k)
-            s_cp[k] += s_cp[k - 1];
+    if (cells && w == 0) {
+        int tot;
+        const int v = lane < 27 ? s_cp[lane + 1] : 0;
+        const int ex = wave_excl_scan_i(v, tot);
+        if (lane < 27)
+            s_cp[lane + 1] = ex + v;
+        if (lane == 0)
+            s_cp[0] = 0;
+    }
+    // the matrix operands of the block's atoms: row lr of tile m is atom 16 m + lr, column lg its
+    // component; the accumulator's register v of tile m starts at |q|^2 of atom 16 m + 4 lg + v
+    const int lr = lane & 15, lg = lane >> 4;
+    float qa[4];
+    f4 qq[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const float4 q = s_i[16 * m + lr];
+        qa[m] = lg == 3 ? 1.0f : -2.0f * (lg == 0 ? q.x : lg == 1 ? q.y : q.z);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            qq[m][v] = s_i[16 * m + 4 * lg + v].w;
     }
     __syncthreads();
     const int ncand = cells ? s_cp[27] : dmax;
     int count = 0;
-    for (int g0 = 0; g0 < ncand; g0 += kFiltChunk) {
-        __syncthreads();
-        {
+    for (int g0 = 0; g0 < ncand;) {
+        int nc = 0;
+        for (; g0 < ncand && nc + 256 <= kFiltCap; g0 += 256) {
             const int g = g0 + tid;
             int J = 0;
             bool inwin = false;
             if (g < ncand) {
                 if (cells) {
-                    int k = 0;
-                    while (s_cp[k + 1] <= g)
-                        ++k;
-                    J = cell_blk[s_cs[k] + g - s_cp[k]];
+                    int lo = 0, up = 26;  // the last cell whose entries start at or before g
+                    while (lo < up) {
+                        const int mid = (lo + up + 1) >> 1;
+                        if (s_cp[mid] <= g)
+                            lo = mid;
+                        else
+                            up = mid - 1;
+                    }
+                    J = cell_blk[s_cs[lo] + g - s_cp[lo]];
                     const int d = J - I + (J < I ? nb : 0);
                     inwin = d >= 1 && d <= dmax;
                 } else {
@@ -814,93 +786,102 @@ __global__ __launch_bounds__(256) void k_filter(int nb, const int* __restrict__ 
             if (lane == 0)
                 s_wn[w] = __popcll(cm);
             __syncthreads();
-            const int wbase = (w > 0 ? s_wn[0] : 0) + (w > 1 ? s_wn[1] : 0) + (w > 2 ? s_wn[2] : 0);
+            const int wbase = nc + (w > 0 ? s_wn[0] : 0) + (w > 1 ? s_wn[1] : 0) + (w > 2 ? s_wn[2] : 0);
             if (cand)
                 s_cand[wbase + __popcll(cm & ((1ull << lane) - 1ull))] = J;
-        }
-        const int nc = s_wn[0] + s_wn[1] + s_wn[2] + s_wn[3];
-        __syncthreads();
-        // the candidates' atoms within reach of the block's box (one wave per candidate); an
-        // atom outside it is outside reach of every atom in it
-        for (int k = w; k < nc; k += 4) {
-            const int sj = s_cand[k] * kBlock + lane;
-            bool inb = false;
-            if (perm[sj] >= 0) {
-                const double4 pj = pos_s[sj];
-                const float jx = (float)mimg_fp64(pj.x - ci.x, box.x, binv.x);
-                const float jy = (float)mimg_fp64(pj.y - ci.y, box.y, binv.y);
-                const float jz = (float)mimg_fp64(pj.z - ci.z, box.z, binv.z);
-                const float bx = fmaxf(fabsf(jx) - hxf, 0.0f), by = fmaxf(fabsf(jy) - hyf, 0.0f),
-                            bz = fmaxf(fabsf(jz) - hzf, 0.0f);
-                inb = bx * bx + by * by + bz * bz < rf2;
-            }
-            const unsigned long long m = __ballot(inb);
-            if (lane == 0) {
-                s_inb[k] = m;
-                s_keep[k] = 0ull;
-            }
-        }
-        __syncthreads();
-        {
-            // queue of those atoms: candidate k owns entries s_qoff[k] .. s_qoff[k+1]-1
-            const int k = tid;
-            int tot;
-            const int ex = wave_excl_scan_i(k < nc ? __popcll(s_inb[k]) : 0, tot);
-            if (lane == 0)
-                s_wk[w] = tot;
+            nc += s_wn[0] + s_wn[1] + s_wn[2] + s_wn[3];
             __syncthreads();
-            const int wbase = (w > 0 ? s_wk[0] : 0) + (w > 1 ? s_wk[1] : 0) + (w > 2 ? s_wk[2] : 0);
-            s_qoff[k] = wbase + ex;
-            if (tid == 0)
-                s_qoff[kFiltChunk] = s_wk[0] + s_wk[1] + s_wk[2] + s_wk[3];
         }
-        __syncthreads();
-        // one queued atom per thread against the block's atoms (dense waves: the atoms outside
-        // the box no longer hold lanes)
-        const int nq = s_qoff[kFiltChunk];
-        for (int e = tid; e < nq; e += kFiltChunk) {
-            int lo = 0, hi = nc - 1;  // the last candidate whose entries start at or before e
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (s_qoff[mid] <= e)
-                    lo = mid;
-                else
-                    hi = mid - 1;
-            }
-            const int bit = nth_set_bit(s_inb[lo], e - s_qoff[lo]);
-            const double4 pj = pos_s[s_cand[lo] * kBlock + bit];
+        double4 next = pos_s[w < nc ? s_cand[w] * kBlock + lane : 0];
+        for (int k = w; k < nc; k += 4) {
+            const double4 pj = next;
+            const bool real = s_cand[k] * kBlock + lane < n;
+            if (k + 4 < nc)
+                next = pos_s[s_cand[k + 4] * kBlock + lane];
             const float jx = (float)mimg_fp64(pj.x - ci.x, box.x, binv.x);
             const float jy = (float)mimg_fp64(pj.y - ci.y, box.y, binv.y);
             const float jz = (float)mimg_fp64(pj.z - ci.z, box.z, binv.z);
-            const bool keep = mi ? near_block<true>(s_i, s_gc, s_gh, jx, jy, jz, rf2, Lx, Ly, Lz, Lix, Liy, Liz)
-                                 : near_block<false>(s_i, s_gc, s_gh, jx, jy, jz, rf2, Lx, Ly, Lz, Lix, Liy, Liz);
-            if (keep)
-                atomicOr(&s_keep[lo], 1ull << bit);
+            const float bx = fmaxf(fabsf(jx) - hxf, 0.0f), by = fmaxf(fabsf(jy) - hyf, 0.0f),
+                        bz = fmaxf(fabsf(jz) - hzf, 0.0f);
+            // an atom outside the reach of the block's box is outside that of every atom in it
+            const bool inb = real && bx * bx + by * by + bz * bz < rf2;
+            const unsigned long long m = __ballot(inb);
+            unsigned long long near = 0ull;
+            if (mi) {
+                if (m) {
+                    float r2 = 3e38f;
+#pragma unroll 4
+                    for (int i = 0; i < kBlock; ++i) {
+                        const float4 q = s_i[i];
+                        float dx = q.x - jx, dy = q.y - jy, dz = q.z - jz;
+                        dx -= Lx * rintf(dx * Lix);
+                        dy -= Ly * rintf(dy * Liy);
+                        dz -= Lz * rintf(dz * Liz);
+                        const float d2 = dx * dx + dy * dy + dz * dz;
+                        r2 = fminf(r2, q.w < 1e30f ? d2 : 3e38f);
+                    }
+                    near = __ballot(r2 < rf2);
+                }
+            } else if (m) {
+                float* sj = &s_j[w][4 * lane];
+                sj[0] = jx;
+                sj[1] = jy;
+                sj[2] = jz;
+                sj[3] = jx * jx + jy * jy + jz * jz;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    if (!((m >> (16 * t)) & 0xffffull))
+                        continue;
+                    const float b = s_j[w][4 * (16 * t + lr) + lg];
+                    float r2 = 3e38f;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const f4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[u], b, qq[u], 0, 0, 0);
+                        r2 = fminf(r2, fminf(fminf(d[0], d[1]), fminf(d[2], d[3])));
+                    }
+                    unsigned long long hit = __ballot(r2 < rf2);  // lane (lr, lg): atom 16 t + lr
+                    hit |= hit >> 32;
+                    hit |= hit >> 16;
+                    near |= (hit & 0xffffull) << (16 * t);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (lane == 0)
+                s_keep[k] = near & m;
         }
         __syncthreads();
         {
-            // ordered exclusive scan of the kept counts (wave w holds candidates 64w .. 64w+63)
-            const int k = tid;
+            // ordered exclusive scan of the kept counts (thread t holds candidates 2t and 2t + 1)
+            const int k = 2 * tid;
+            const int n0 = k < nc ? __popcll(s_keep[k]) : 0, n1 = k + 1 < nc ? __popcll(s_keep[k + 1]) : 0;
             int tot;
-            const int ex = wave_excl_scan_i(k < nc ? __popcll(s_keep[k]) : 0, tot);
+            const int ex = wave_excl_scan_i(n0 + n1, tot);
             if (lane == 0)
-                s_wk[w] = tot;
+                s_wn[w] = tot;
             __syncthreads();
-            const int wbase = (w > 0 ? s_wk[0] : 0) + (w > 1 ? s_wk[1] : 0) + (w > 2 ? s_wk[2] : 0);
+            const int wbase = (w > 0 ? s_wn[0] : 0) + (w > 1 ? s_wn[1] : 0) + (w > 2 ? s_wn[2] : 0);
             s_off[k] = wbase + ex;
-            if (tid == 0)
-                s_off[kFiltChunk] = s_wk[0] + s_wk[1] + s_wk[2] + s_wk[3];
+            s_off[k + 1] = wbase + ex + n0;
+            if (tid == 255)
+                s_off[kFiltCap] = wbase + tot;
         }
         __syncthreads();
         for (int k = w; k < nc; k += 4) {
             const unsigned long long km = s_keep[k];
             if ((km >> lane) & 1ull) {
                 const int pos = count + s_off[k] + __popcll(km & ((1ull << lane) - 1ull));
-                if (pos < kMaxFiltered)
-                    row_j[(size_t)I * kMaxFiltered + pos] = s_cand[k] * kBlock + lane;
+                if (pos < kMaxFiltered) {
+                    const int sj = s_cand[k] * kBlock + lane;
+                    row_j[(size_t)I * kMaxFiltered + pos] = sj;
+                    atomicAdd(&rev_cnt[sj], 1);
+                }
             }
         }
-        count += s_off[kFiltChunk];
+        count += s_off[kFiltCap];
+        __syncthreads();
     }
     if (tid == 0) {
         const int kept = min(count, kMaxFiltered);
@@ -911,51 +892,33 @@ __global__ __launch_bounds__(256) void k_filter(int nb, const int* __restrict__ 
     }
 }
 
-__global__ __launch_bounds__(64) void k_fill_tiles(int nb, const int* __restrict__ tile0,
-                                                   const int* __restrict__ row_count,
-                                                   const int* __restrict__ row_j, int* __restrict__ tile_blk,
-                                                   int* __restrict__ tile_j)
+// The tiles of block I (a workgroup): its diagonal tile and its filtered j-atoms, and their entries
+// (tile, lane) in the reverse index: for every slot those where it is a j-atom, in the order the
+// counters' atomics give (the sums over them do not depend on it: exact fixed point in mixed
+// precision, see JSum).  Does nothing when the tiles exceed the arrays (the host then launches it
+// again).
+__global__ __launch_bounds__(256) void k_fill_tiles(int nb, int tile_cap, const int* __restrict__ tile0,
+                                                    const int* __restrict__ row_count,
+                                                    const int* __restrict__ row_j, const int* __restrict__ rev_ptr,
+                                                    int* __restrict__ rev_cnt, int* __restrict__ tile_blk,
+                                                    int* __restrict__ tile_j, int* __restrict__ rev_idx)
 {
-    int I = blockIdx.x, lane = threadIdx.x;
-    int t0 = tile0[I], nt = tile0[I + 1] - t0, cnt = row_count[I];
-    if (lane == 0)
-        for (int t = 0; t < nt; ++t)
-            tile_blk[t0 + t] = I;
-    tile_j[(size_t)t0 * kBlock + lane] = I * kBlock + lane;  // diagonal tile
-    for (int t = 1; t < nt; ++t) {
-        int idx = (t - 1) * kBlock + lane;
-        tile_j[(size_t)(t0 + t) * kBlock + lane] = idx < cnt ? row_j[(size_t)I * kMaxFiltered + idx] : -1;
+    if (tile0[nb] > tile_cap)
+        return;
+    const int I = blockIdx.x, t0 = tile0[I], nt = tile0[I + 1] - t0, cnt = row_count[I];
+    for (int t = threadIdx.x; t < nt; t += 256)
+        tile_blk[t0 + t] = I;
+    for (int e = threadIdx.x; e < nt * kBlock; e += 256) {
+        const int r = e - kBlock;
+        int sj = I * kBlock + e;  // diagonal tile
+        if (r >= 0) {
+            sj = r < cnt ? row_j[(size_t)I * kMaxFiltered + r] : -1;
+            if (sj >= 0)  // the counter counts down from the slot's count: zero again afterwards
+                rev_idx[rev_ptr[sj] + atomicSub(&rev_cnt[sj], 1) - 1] = t0 * kBlock + e;
+        }
+        tile_j[(size_t)t0 * kBlock + e] = sj;
     }
 }
-
-// Reverse index of the off-diagonal tiles: for every slot, the (tile, lane) entries where it
-// is a j-atom, in the order the fill's atomics give (the sums over them do not depend on it:
-// exact fixed point in mixed precision, see JSum).
-__global__ void k_rev_count(int ntiles, const int* __restrict__ tile_blk, const int* __restrict__ tile0,
-                            const int* __restrict__ tile_j, int* __restrict__ cnt)
-{
-    long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    int t = (int)(g >> 6), k = (int)(g & 63);
-    if (t >= ntiles || t == tile0[tile_blk[t]])
-        return;
-    int sj = tile_j[(size_t)t * kBlock + k];
-    if (sj >= 0)
-        atomicAdd(&cnt[sj], 1);
-}
-
-__global__ void k_rev_fill(int ntiles, const int* __restrict__ tile_blk, const int* __restrict__ tile0,
-                           const int* __restrict__ tile_j, const int* __restrict__ rev_ptr, int* __restrict__ cursor,
-                           int* __restrict__ rev_idx)
-{
-    long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    int t = (int)(g >> 6), k = (int)(g & 63);
-    if (t >= ntiles || t == tile0[tile_blk[t]])
-        return;
-    int sj = tile_j[(size_t)t * kBlock + k];
-    if (sj >= 0)  // the cursor counts down from the slot's count: zero again afterwards
-        rev_idx[rev_ptr[sj] + atomicSub(&cursor[sj], 1) - 1] = t * kBlock + k;
-}
-
 
 // lane l of (lo, hi) = the two halves of x (x and l uniform: scalar registers; the lane select
 // goes through m0, which the one scalar operand read of the instruction leaves free)
@@ -1290,7 +1253,6 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
     }
     double4 *bc = c->b_bc, *bh = c->b_bh;
     int *row_count = c->b_rowc, *row_j = c->b_rowj, *tpb = c->b_tpb, *t0 = c->blk_tile0;
-    auto fail = [&](int code) { return code; };
     // build status words, read back with one copy: flags[0] error flags, flags[1] the tile
     // count, flags[4..9] the largest block half-extents (b_extent); flags[16..19] the block grid
     // (device only)
@@ -1308,7 +1270,7 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
     hipLaunchKernelGGL(k_sort_rank, dim3(nblk(npad, 256)), dim3(256), 0, st, n, npad, shift, nbucket, c->b_entry,
                        start, pos, box, c->perm, c->slot, c->pos_s, c->pos_ref, c->flags);
     if (c->atoms_set && (rc = sort_params(c)) != AMOEBA_OK)
-        return fail(rc);
+        return rc;
 
     hipLaunchKernelGGL(k_bbox, dim3(nblk(nb, 4)), dim3(256), 0, st, nb, c->perm, c->pos_s, box, bc, bh, c->blk_org,
                        c->off_d, c->off_f);
@@ -1320,12 +1282,28 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
     hipLaunchKernelGGL(k_cell_rank, dim3(nblk(nb, 256)), dim3(256), 0, st, nb, grid, (const int2*)c->b_entry,
                        (const int*)c->b_keys, c->b_cell_start, c->b_cell_blk);
     double3 binv = make_double3(1.0 / box.x, 1.0 / box.y, 1.0 / box.z);
-    hipLaunchKernelGGL(k_filter, dim3(nb), dim3(256), 0, st, nb, c->perm, c->pos_s, bc, bh, c->b_extent, grid,
-                       c->b_cell_blk, c->b_cell_start, box, binv, rcb, row_count, row_j, tpb, c->flags);
+    // the counters are zero again after every complete build: counted up here, down by the fill
+    auto fail = [&](int code) {
+        hipMemsetAsync(c->rev_cnt, 0, sizeof(int) * (npad + 1), st);
+        return code;
+    };
+    hipLaunchKernelGGL(k_filter, dim3(nb), dim3(256), 0, st, nb, n, c->pos_s, bc, bh, c->b_extent, grid,
+                       c->b_cell_blk, c->b_cell_start, box, binv, rcb, row_count, row_j, tpb, c->rev_cnt, c->flags);
     if ((rc = device_scan(c, nb, tpb, t0, c->flags + 1)))
-        return rc;
+        return fail(rc);
     hipMemcpyAsync(c->flags_host, c->flags, 4 * sizeof(int) + 3 * sizeof(double), hipMemcpyDeviceToHost, st);
-    if ((rc = hip_check(c, hipStreamSynchronize(st), "build_blocklist")))
+    hipEventRecord(c->ev_build, st);
+    // the fill runs while the host waits for the counts, if the tiles fit the arrays there are
+    auto fill = [&] {
+        hipLaunchKernelGGL(k_fill_tiles, dim3(nb), dim3(256), 0, st, nb, (int)c->tile_cap, t0, row_count, row_j,
+                           c->rev_ptr, c->rev_cnt, c->tile_blk, c->tile_j, c->rev_idx);
+    };
+    if ((rc = device_scan(c, npad, c->rev_cnt, c->rev_ptr)))
+        return fail(rc);
+    const int filled_cap = c->tile_cap;
+    if (filled_cap > 0)
+        fill();
+    if ((rc = hip_check(c, hipEventSynchronize(c->ev_build), "build_blocklist")))
         return fail(rc);
     const int total = c->flags_host[1];
     {
@@ -1372,19 +1350,8 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
         c->rev_cap = (int64_t)tb;
     }
     c->ntiles = total;
-    hipLaunchKernelGGL(k_fill_tiles, dim3(nb), dim3(64), 0, st, nb, t0, row_count, row_j, c->tile_blk, c->tile_j);
-    {
-        // rev_cnt is zero between builds (zeroed at allocation; the fill counts it back down)
-        const long nthr = (long)total * kBlock;
-        hipLaunchKernelGGL(k_rev_count, dim3(nblk(nthr, 256)), dim3(256), 0, st, total, c->tile_blk, t0, c->tile_j,
-                           c->rev_cnt);
-        if ((rc = device_scan(c, npad, c->rev_cnt, c->rev_ptr))) {
-            hipMemsetAsync(c->rev_cnt, 0, sizeof(int) * (npad + 1), st);
-            return rc;
-        }
-        hipLaunchKernelGGL(k_rev_fill, dim3(nblk(nthr, 256)), dim3(256), 0, st, total, c->tile_blk, t0, c->tile_j,
-                           c->rev_ptr, c->rev_cnt, c->rev_idx);
-    }
+    if (total > filled_cap)
+        fill();
     return AMOEBA_OK;
 }
 

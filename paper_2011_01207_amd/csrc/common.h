@@ -283,6 +283,7 @@ struct amoeba_ctx {
     // the reciprocal passes on the context stream: forked and joined with events
     hipStream_t stream2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    hipEvent_t ev_build = nullptr;         // recorded after a list build's counts are copied
     hipEvent_t ev_pairs = nullptr;         // recorded after the pair count of a refresh is written
     // one PCG iteration (product on both streams, update, direction) as a HIP graph: captured on
     // gstream, replayed on the context stream; recaptured when a launch parameter it bakes in
