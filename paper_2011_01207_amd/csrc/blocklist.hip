@@ -920,117 +920,181 @@ __global__ __launch_bounds__(256) void k_fill_tiles(int nb, int tile_cap, const 
     }
 }
 
-// lane l of (lo, hi) = the two halves of x (x and l uniform: scalar registers; the lane select
-// goes through m0, which the one scalar operand read of the instruction leaves free)
-__device__ __forceinline__ void write_lane2(unsigned& lo, unsigned& hi, unsigned long long x, int l)
+// Per configuration: in-cutoff bitmasks (strict r < rc, decided as in FP64) and j positions
+// relative to the i-block origin.  The diagonal tile keeps only k > i.  One tile per wave.
+// The squared distances less rc^2 of 16 i-atoms to the 64 j-atoms are four FP32 matrix
+// instructions, |j|^2 - rc^2 + (-2 j, 1) . (q, |q|^2): lane (lr, lg) then holds those of i-atom
+// 16 t + lr to the j-atoms 16 m + 4 lg + v, shifts their signs into 16 bits and takes the least
+// magnitude of either sign (two vector instructions a pair); an exchange through LDS and a transpose of
+// 4 x 4 groups of four bits make them rows.  With S >= |q|^2 + |j|^2 the offsets' rounding moves a
+// squared distance by at most 4 S 2^-24, that of the squares and of the five sums by less than
+// 28 S 2^-24 (also if they are cut off): where the least magnitude is above S 2^-19, every sign is
+// that of the exact value.  Otherwise (one tile in ten or so) the 16 i-atoms' pairs are classified
+// anew from the differences of their FP32 offsets, and those within a relative 1e-5 of rc^2 (far
+// above the error of that form) by the FP64 distance, so every bit equals the FP64 test.
+// MI: minimum image per pair offset, all pairs classified from the differences; without it the
+// block-relative offsets are used as they are (valid when the list build proved that no tile offset
+// can reach half the box, as for the pair kernels).
+// 54 us for 42,600 tiles (69 us with a vector subtraction and comparison per pair and component).
+__device__ __forceinline__ unsigned long long transpose_nibbles(unsigned long long x)
 {
-    asm("s_mov_b32 m0, %4\n\tv_writelane_b32 %0, %2, m0\n\tv_writelane_b32 %1, %3, m0"
-        : "+v"(lo), "+v"(hi)
-        : "s"((unsigned)x), "s"((unsigned)(x >> 32)), "s"(l)
-        : "m0");
+    unsigned long long y = (x ^ (x >> 12)) & 0x0000f0f00000f0f0ull;
+    x ^= y ^ (y << 12);
+    y = (x ^ (x >> 24)) & 0x00000000ff00ff00ull;
+    return x ^ y ^ (y << 24);
 }
 
-// Per configuration: in-cutoff bitmasks (strict r < rc, decided as in FP64) and j positions
-// relative to the i-block origin.  The diagonal tile keeps only k > i.  Each pair is first
-// classified from FP32 offsets; only pairs within a relative 1e-5 of rc^2 (far above the FP32
-// error of the offsets) are decided by the FP64 distance, so every bit equals the FP64 test.
-// Lane k of a wave holds j-atom k of its tile and the wave walks the 64 rows: row i's mask is
-// the wave's vote on its 64 pairs, written into lane i (two lane writes per row instead of a
-// per-pair shift and or).
-// MI: minimum image per pair offset; without it the block-relative offsets are used as they are
-// (valid when the list build proved that no tile offset can reach half the box, as for the
-// pair kernels).
-template <bool MI>
-__global__ __launch_bounds__(256) void k_tile_refresh(int ntiles, const int* __restrict__ tile_blk,
-                                                      const int* __restrict__ tile_j,
-                                                      const int* __restrict__ perm,
+// largest of a wave's non-negative floats (their order is that of their bits)
+__device__ __forceinline__ float wave_max_pos(float x)
+{
+    int v = __float_as_int(x);
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));  // row_bcast:15, :31
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_readlane(v, 63));
+}
+
+template <typename R, bool MI>
+__global__ __launch_bounds__(256, 6) void k_tile_refresh(int ntiles, const int* __restrict__ tile_blk,
+                                                      const int* __restrict__ tile_j, int n,
                                                       const double4* __restrict__ pos_s,
                                                       const double4* __restrict__ org,
                                                       const float4* __restrict__ off_f,
-                                                      const double4* __restrict__ par, double3 box, double3 binv,
-                                                      double rc2, unsigned long long* __restrict__ mask,
-                                                      double4* __restrict__ jrel_d, float4* __restrict__ jrel_f,
+                                                      const typename V4<R>::T* __restrict__ par, double3 box,
+                                                      double3 binv, double rc2,
+                                                      unsigned long long* __restrict__ mask,
+                                                      typename V4<R>::T* __restrict__ jrel,
                                                       int* __restrict__ tile_np, int* __restrict__ tile_rows,
                                                       uint16_t* __restrict__ walk,
                                                       unsigned long long* __restrict__ pair_part)
 {
-    __shared__ double4 s_id[4][kBlock];
-    __shared__ float4 s_if[4][kBlock];
+    using R4 = typename V4<R>::T;
+    __shared__ __align__(16) float s_i[4][4 * kBlock];  // i offsets and |.|^2
+    __shared__ __align__(16) float s_j[4][4 * kBlock];  // j likewise
+    __shared__ __align__(16) float s_jn[4][kBlock];     // |j|^2 - rc^2
+    __shared__ uint16_t s_p[4][4 * kBlock];
     __shared__ unsigned long long s_cnt[4];
     __shared__ unsigned long long s_m[4][kBlock];
     __shared__ int s_off[4][kBlock];
     // one tile per wave: its index and everything derived from it are wave-uniform
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int t = blockIdx.x * 4 + w;
-    bool act = t < ntiles;
-    int I = act ? tile_blk[t] : 0;
-    int si = I * kBlock + lane;
-    bool ivalid = act && perm[si] >= 0;
-    double4 pi = pos_s[si];
-    int sj = act ? tile_j[(size_t)t * kBlock + lane] : -1;
-    double4 pj = sj >= 0 ? pos_s[sj] : pi;
-    bool jvalid = sj >= 0 && perm[sj] >= 0;
-    double4 o = org[I];
-    double jx = mimg_fp64(pj.x - o.x, box.x, binv.x), jy = mimg_fp64(pj.y - o.y, box.y, binv.y),
-           jz = mimg_fp64(pj.z - o.z, box.z, binv.z);
-    // absent atoms (no i-atom, no j-atom, phantom slots) take infinite offsets: every FP32
-    // distance test involving one is false (an infinite or NaN r^2), with no per-row masks
-    const float inf = __builtin_inff();
-    s_id[w][lane] = make_double4(pi.x, pi.y, pi.z, 0.0);
-    s_if[w][lane] = ivalid ? off_f[si] : make_float4(inf, inf, inf, 0.0f);
-    __syncthreads();
+    const bool act = t < ntiles;
+    const int I = act ? tile_blk[t] : 0;
+    const int si = I * kBlock + lane;
+    const int sj = act ? tile_j[(size_t)t * kBlock + lane] : -1;
     unsigned long long m = 0;
+    int P = 0;
     if (act) {  // uniform: one tile per wave
-        // the pair kernels of the context's precision read one of the two
-        const double wj = sj >= 0 ? par[sj].z : 0.0;  // the j atom's polarizability factor
-        if (jrel_d)
-            jrel_d[(size_t)t * kBlock + lane] = make_double4(jx, jy, jz, wj);
-        if (jrel_f)
-            jrel_f[(size_t)t * kBlock + lane] = make_float4((float)jx, (float)jy, (float)jz, (float)wj);
+        const double4 o = org[I];
+        const bool jvalid = sj >= 0 && sj < n;
+        const double4 pj = sj >= 0 ? pos_s[sj] : o;
+        const R wj = sj >= 0 ? par[sj].z : (R)0;  // the j atom's polarizability factor
+        const float4 oi = off_f[si];
+        const double jx = mimg_fp64(pj.x - o.x, box.x, binv.x), jy = mimg_fp64(pj.y - o.y, box.y, binv.y),
+                     jz = mimg_fp64(pj.z - o.z, box.z, binv.z);
+        jrel[(size_t)t * kBlock + lane] = R4{(R)jx, (R)jy, (R)jz, wj};
+        const float rcf = (float)rc2;
         const float lo2 = (float)(rc2 * (1.0 - 1e-5)), hi2 = (float)(rc2 * (1.0 + 1e-5));
         const float Lx = (float)box.x, Ly = (float)box.y, Lz = (float)box.z;
         const float Lix = (float)binv.x, Liy = (float)binv.y, Liz = (float)binv.z;
-        const float qx = jvalid ? (float)jx : inf, qy = jvalid ? (float)jy : inf, qz = jvalid ? (float)jz : inf;
-        unsigned mlo = 0, mhi = 0;
-        // DIAG: the block with itself, row i keeps the lanes k > i
-        auto rows = [&](auto diag_tag) {
-            constexpr bool DIAG = decltype(diag_tag)::value;
-#pragma unroll 8
-            for (int i = 0; i < kBlock; ++i) {
-                const float4 oi = s_if[w][i];
-                float dx = oi.x - qx, dy = oi.y - qy, dz = oi.z - qz;
-                if (MI) {
-                    dx -= Lx * rintf(dx * Lix);
-                    dy -= Ly * rintf(dy * Liy);
-                    dz -= Lz * rintf(dz * Liz);
-                }
-                const float r2 = dx * dx + dy * dy + dz * dz;
-                unsigned long long in = __ballot(r2 < lo2);
-                unsigned long long band = __ballot(r2 < hi2) & ~in;
-                if (DIAG) {
-                    const unsigned long long upper = i == kBlock - 1 ? 0ull : ~0ull << (i + 1);
-                    in &= upper;
-                    band &= upper;
-                }
-                if (band) {  // rare: decided by the FP64 distance
-                    bool fin = false;
-                    if ((band >> lane) & 1) {
-                        const double4 p = s_id[w][i];
-                        const double ex = mimg_fp64(p.x - pj.x, box.x, binv.x),
-                                     ey = mimg_fp64(p.y - pj.y, box.y, binv.y),
-                                     ez = mimg_fp64(p.z - pj.z, box.z, binv.z);
-                        fin = ex * ex + ey * ey + ez * ez < rc2;
-                    }
-                    in |= __ballot(fin);
-                }
-                write_lane2(mlo, mhi, in, i);
+        // absent atoms (no i-atom, no j-atom, phantom slots) lie at the origin with a square that
+        // puts every sum with them far out of reach
+        constexpr float kFar = 1e30f;
+        const float qx = (float)jx, qy = (float)jy, qz = (float)jz;
+        const float jn = qx * qx + qy * qy + qz * qz, in2 = oi.x * oi.x + oi.y * oi.y + oi.z * oi.z;
+        const bool ivalid = si < n;
+        float* wi = &s_i[w][4 * lane];
+        wi[0] = ivalid ? oi.x : 0.0f;
+        wi[1] = ivalid ? oi.y : 0.0f;
+        wi[2] = ivalid ? oi.z : 0.0f;
+        wi[3] = ivalid ? in2 : kFar;
+        float* wp = &s_j[w][4 * lane];
+        wp[0] = jvalid ? qx : 0.0f;
+        wp[1] = jvalid ? qy : 0.0f;
+        wp[2] = jvalid ? qz : 0.0f;
+        wp[3] = jvalid ? jn : kFar;
+        s_jn[w][lane] = jvalid ? jn - rcf : kFar;
+        // S: twice the largest square of the tile
+        const float thr = wave_max_pos(fmaxf(ivalid ? in2 : 0.0f, jvalid ? jn : 0.0f)) * 3.814697265625e-6f;  // 2^-18
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int lr = lane & 15, lg = lane >> 4;
+        float ja[4];
+        f4 jq[4];
+        if constexpr (!MI) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                ja[k] = lg == 3 ? 1.0f : -2.0f * s_j[w][4 * (16 * k + lr) + lg];
+                jq[k] = *(const f4*)&s_jn[w][16 * k + 4 * lg];
             }
-        };
-        if (tile_j[(size_t)t * kBlock] == I * kBlock)
-            rows(std::true_type{});
-        else
-            rows(std::false_type{});
-        m = ((unsigned long long)mhi << 32) | mlo;
+        }
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            unsigned bits = 0;
+            bool redo = MI;
+            if constexpr (!MI) {
+                const float b = s_i[w][4 * (16 * tt + lr) + lg];
+                // the bits of the least positive value, and those of the negative one nearest to 0
+                // (a positive value's bits are the smaller the less it is; a negative one's, as a
+                // signed number, too)
+                unsigned above = __float_as_uint(kFar);
+                int below = __float_as_int(-kFar);
+#pragma unroll
+                for (int k = 3; k >= 0; --k) {
+                    const f4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(ja[k], b, jq[k], 0, 0, 0);
+#pragma unroll
+                    for (int v = 3; v >= 0; --v)  // bits << 1 | sign of d
+                        bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(d[v]), 31);
+#pragma unroll
+                    for (int v = 0; v < 4; v += 2) {
+                        above = min(above, min(__float_as_uint(d[v]), __float_as_uint(d[v + 1])));
+                        below = min(below, min(__float_as_int(d[v]), __float_as_int(d[v + 1])));
+                    }
+                }
+                redo = __any(__uint_as_float(above) <= thr || -__int_as_float(below) <= thr);
+            }
+            if (redo) {  // uniform
+                bits = 0;
+                const float* pi = &s_i[w][4 * (16 * tt + lr)];
+#pragma unroll MI ? 4 : 1
+                for (int e = 0; e < 16; ++e) {
+                    const int k = 16 * (e >> 2) + 4 * lg + (e & 3);
+                    const float* q = &s_j[w][4 * k];
+                    float dx = pi[0] - q[0], dy = pi[1] - q[1], dz = pi[2] - q[2];
+                    if (MI) {
+                        dx -= Lx * rintf(dx * Lix);
+                        dy -= Ly * rintf(dy * Liy);
+                        dz -= Lz * rintf(dz * Liz);
+                    }
+                    const float r2 = dx * dx + dy * dy + dz * dz;
+                    bool in = r2 < hi2 && pi[3] < kFar && q[3] < kFar;
+                    if (in && !(r2 < lo2)) {  // rare: decided by the FP64 distance
+                        const double4 p = pos_s[I * kBlock + 16 * tt + lr];
+                        const double4 pk = pos_s[tile_j[(size_t)t * kBlock + k]];
+                        const double ex = mimg_fp64(p.x - pk.x, box.x, binv.x),
+                                     ey = mimg_fp64(p.y - pk.y, box.y, binv.y),
+                                     ez = mimg_fp64(p.z - pk.z, box.z, binv.z);
+                        in = ex * ex + ey * ey + ez * ez < rc2;
+                    }
+                    bits |= in ? 1u << e : 0u;
+                }
+            }
+            s_p[w][4 * (16 * tt + lr) + lg] = (uint16_t)bits;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // row `lane`: bits 16 lg + 4 m + v of its four parts are the columns 16 m + 4 lg + v
+        const uint16_t* pp = &s_p[w][4 * lane];
+        m = transpose_nibbles((unsigned long long)pp[0] | (unsigned long long)pp[1] << 16 |
+                              (unsigned long long)pp[2] << 32 | (unsigned long long)pp[3] << 48);
+        if (tile_j[(size_t)t * kBlock] == I * kBlock)  // the block with itself
+            m &= lane == kBlock - 1 ? 0ull : ~0ull << (lane + 1);
         mask[(size_t)t * kBlock + lane] = m;
     }
     // The pair kernels split a tile's in-cutoff pairs (row-major) among the 64 lanes of a wave,
@@ -1038,7 +1102,6 @@ __global__ __launch_bounds__(256) void k_tile_refresh(int ntiles, const int* __r
     // last row whose exclusive pair offset is <= l B) and that row's bit, is found here once
     // per configuration instead of by every product.
     {
-        int P;
         const int off = wave_excl_scan_i(__popcll(m), P);
         s_off[w][lane] = off;
         s_m[w][lane] = m;
@@ -1064,14 +1127,11 @@ __global__ __launch_bounds__(256) void k_tile_refresh(int ntiles, const int* __r
     }
     // pairs of the workgroup's tiles: one partial per workgroup, summed in order by
     // k_sum_pairs (no global atomics)
-    unsigned long long cnt = (unsigned long long)__popcll(m);
-    for (int off = 32; off > 0; off >>= 1)
-        cnt += __shfl_xor(cnt, off);
     if (lane == 0) {
-        s_cnt[w] = cnt;
+        s_cnt[w] = (unsigned long long)P;
         if (act) {
-            tile_np[t] = (int)cnt;                 // the pair kernels balance their waves by it
-            tile_rows[t] = (int)((cnt + 63) >> 6);  // rows of the tile's stored coefficients
+            tile_np[t] = P;               // the pair kernels balance their waves by it
+            tile_rows[t] = (P + 63) >> 6;  // rows of the tile's stored coefficients
         }
     }
     __syncthreads();
@@ -1189,11 +1249,16 @@ static int refresh_tiles(amoeba_ctx* c)
     double3 box = make_double3(c->prm.box[0], c->prm.box[1], c->prm.box[2]);
     double3 binv = make_double3(1.0 / box.x, 1.0 / box.y, 1.0 / box.z);
     const int nwg = nblk((long)c->ntiles * kBlock, 256);
-    hipLaunchKernelGGL(c->skip_mimg ? k_tile_refresh<false> : k_tile_refresh<true>, dim3(nwg), dim3(256), 0, st,
-                       c->ntiles, c->tile_blk, c->tile_j, c->perm,
-                       c->pos_s, c->blk_org, c->off_f, c->par_d, box, binv, c->prm.cutoff * c->prm.cutoff,
-                       c->tile_mask,
-                       c->jrel_d, c->jrel_f, c->tile_np, c->tile_rows, c->tile_walk, c->pair_part);
+    auto refresh = [&](auto* kernel, auto* par, auto* jrel) {
+        hipLaunchKernelGGL(kernel, dim3(nwg), dim3(256), 0, st, c->ntiles, c->tile_blk, c->tile_j, c->n, c->pos_s,
+                           c->blk_org, c->off_f, par, box, binv, c->prm.cutoff * c->prm.cutoff, c->tile_mask, jrel,
+                           c->tile_np, c->tile_rows, c->tile_walk, c->pair_part);
+    };
+    // the pair kernels of the context's precision read one of the two j records
+    if (c->mixed)
+        refresh(c->skip_mimg ? k_tile_refresh<float, false> : k_tile_refresh<float, true>, c->par_f, c->jrel_f);
+    else
+        refresh(c->skip_mimg ? k_tile_refresh<double, false> : k_tile_refresh<double, true>, c->par_d, c->jrel_d);
     c->pair_nwg = nwg;
     launch_sum_pairs(c);
     c->pairs_pending = true;  // read by amoeba_get_info

@@ -25,6 +25,11 @@ constexpr int kMaxFiltered = 2048;               // filtered j-atoms per block (
 constexpr int kRedBlocks = 512;                  // workgroups of the deterministic reductions
 constexpr double kPi = 3.14159265358979323846;
 
+// four components in a precision
+template <typename R> struct V4;
+template <> struct V4<float> { using T = float4; };
+template <> struct V4<double> { using T = double4; };
+
 // Device flags written by validation / preparation kernels.
 enum : int {
     kFlagNonFinite = 1,

@@ -6,9 +6,6 @@
 
 namespace amoeba {
 
-template <typename R> struct V4;
-template <> struct V4<float> { using T = float4; };
-template <> struct V4<double> { using T = double4; };
 template <typename R> struct V2;
 template <> struct V2<float> { using T = float2; };
 template <> struct V2<double> { using T = double2; };
