@@ -47,4 +47,41 @@ __device__ __forceinline__ void sum_partials(const double* __restrict__ part, in
     block_sum<NV>(tot);
 }
 
+// E_real of slot s = eipart[s] + sum of the jbuf slots of s in the reverse index (JSum; four loads
+// in flight).
+template <typename R>
+__device__ __forceinline__ void real_reduce(int s, const double* __restrict__ eipart, const R* __restrict__ jbuf,
+                                            const int* __restrict__ rev_ptr, const int* __restrict__ rev_idx,
+                                            double* __restrict__ ereal)
+{
+    using R4 = typename V4<R>::T;
+    using J = JSum<R>;
+    double e0 = J::start(eipart[3 * (size_t)s]), e1 = J::start(eipart[3 * (size_t)s + 1]),
+           e2 = J::start(eipart[3 * (size_t)s + 2]);
+    const R4* jb = reinterpret_cast<const R4*>(jbuf);
+    const int k1 = rev_ptr[s + 1];
+    int k = rev_ptr[s];
+    for (; k + 4 <= k1; k += 4) {
+        R4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = jb[rev_idx[k + u]];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            e0 += J::term(v[u].x);
+            e1 += J::term(v[u].y);
+            e2 += J::term(v[u].z);
+        }
+    }
+    for (; k < k1; ++k) {
+        const R4 v = jb[rev_idx[k]];
+        e0 += J::term(v.x);
+        e1 += J::term(v.y);
+        e2 += J::term(v.z);
+    }
+    ereal[3 * (size_t)s] = J::finish(e0);
+    ereal[3 * (size_t)s + 1] = J::finish(e1);
+    ereal[3 * (size_t)s + 2] = J::finish(e2);
+}
+
 }  // namespace amoeba

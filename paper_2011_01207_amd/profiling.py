@@ -24,12 +24,14 @@ CSRC = os.path.join(HERE, "csrc")
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 COPY_BYTES = 256 * 1024 * 1024
 # sources of each profiled kernel family (the .hip file and the headers it includes)
-HEADERS = ["common.h", "reduce.h", "spline.h"]
+HEADERS = ["common.h", "reduce.h", "spline.h", "plane_fft.h", "plane_spread.h"]
 KERNEL_SOURCES = {
     "k_block_tiles": ["realspace.hip"], "k_real_reduce": ["realspace.hip"], "k_perm_assemble": ["realspace.hip"],
+    "k_product_head": ["realspace.hip"],
     "k_pme_": ["plane.hip"], "k_plane_": ["plane.hip"], "k_xybin": ["plane.hip"],
-    "k_update": ["pcg.hip"], "k_direction": ["pcg.hip"], "k_init_residual": ["pcg.hip"],
-    "k_filter": ["blocklist.hip"], "k_tile_refresh": ["blocklist.hip"], "k_rev_sort": ["blocklist.hip"],
+    "k_update": ["pcg.hip"], "k_direction": ["pcg.hip"], "k_pcg_small": ["pcg.hip"], "k_init_residual": ["pcg.hip"],
+    "k_filter": ["blocklist.hip"], "k_tile_refresh": ["blocklist.hip"], "k_fill_tiles": ["blocklist.hip"],
+    "k_sort_": ["blocklist.hip"], "k_guess_": ["guess.hip"],
 }
 
 
