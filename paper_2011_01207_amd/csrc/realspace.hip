@@ -64,7 +64,7 @@ template <typename R> EwaldArgs<R> make_ewald(const amoeba_ctx* c)
     return e;
 }
 
-// exp and erfc of the pair kernels.  FP64 uses the math library.  FP32 uses the hardware
+// exp and erfc of the pair kernels.  FP64: below.  FP32 uses the hardware
 // exponential and erfc(x) = P(t) exp(-x^2), t = 1 / (1 + x/2), with P the degree-9 polynomial
 // fitted to erfc(x) exp(x^2) on [0, 4.5] by fit_erfc.py (relative error 2e-8 in exact
 // arithmetic, below 6e-7 evaluated in FP32 with the 1-ulp hardware reciprocal for t);
@@ -73,7 +73,21 @@ __device__ __forceinline__ float d_exp(float x) { return __expf(x); }
 __device__ __forceinline__ double d_exp(double x) { return exp(x); }
 // 2^x: the hardware base-2 exponential in FP32
 __device__ __forceinline__ float d_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ double d_exp2(double x) { return exp2(x); }
+// FP64: 2^x = 2^n (1 + f q(f)), x = n + f, |f| <= 1/2, q of degree 10 (relative error 8e-18 in exact
+// arithmetic).
+constexpr double kExp2Poly[11] = {
+    0.6931471805599453, 0.24022650695910097, 0.0555041086648216, 0.009618129107606888, 0.0013333558146416936,
+    0.0001540353044173605, 1.525273382983612e-05, 1.321544258792169e-06, 1.0178062445845774e-07,
+    7.072585949269223e-09, 4.4549605981865186e-10};
+__device__ __forceinline__ double d_exp2(double x)
+{
+    const double n = rint(x), f = x - n;
+    double q = kExp2Poly[10];
+#pragma unroll
+    for (int k = 9; k >= 0; --k)
+        q = fma(q, f, kExp2Poly[k]);
+    return ldexp(fma(q, f, 1.0), (int)n);
+}
 __device__ __forceinline__ float d_erfc_g(float x, float gauss)
 {
     const float t = __builtin_amdgcn_rcpf(1.0f + 0.5f * x);   // hardware reciprocal, 1 ulp
@@ -89,14 +103,46 @@ __device__ __forceinline__ float d_erfc_g(float x, float gauss)
     p = fmaf(p, t, -2.098618019e-04f);
     return p * gauss;
 }
-__device__ __forceinline__ double d_erfc_g(double x, double) { return erfc(x); }
+// FP64: erfc(x) = P(y) exp(-x^2), y = 12.923.. / (4 + x) - 2.230.. (1 at x = 0, -1 at x = 6.5), P the
+// degree-19 Chebyshev interpolant of erfc(x) exp(x^2) on [0, 6.5] by fit_fp64.py (relative error 8e-19
+// in exact arithmetic; beyond 6.5 the Gaussian is below 5e-19).  The library's erfc takes three of its
+// ranges in turn where a wave's pairs lie in them.
+constexpr double kErfcPoly[20] = {
+    0.27942855219368923, 0.3279650373568241, 0.210251198447979, 0.1110189355085153, 0.04830152065636551,
+    0.017119508331621246, 0.004801406001139516, 0.0009956606891018877, 0.00012401497071885562,
+    -1.4803669886577276e-06, -3.9276010180824785e-06, -5.208220816950657e-07, 7.124542354843774e-08,
+    2.523797547203749e-08, -8.63854257232425e-10, -1.0283977471600152e-09, 1.960646173695655e-12,
+    4.2527968352153286e-11, 4.331575594317064e-14, -1.5451793580623559e-12};
+constexpr double kErfcYScale = 12.923076923076923, kErfcYShift = -2.230769230769231;
+__device__ __forceinline__ double d_erfc_g(double x, double gauss)
+{
+    const double d = 4.0 + x;
+    double c = __builtin_amdgcn_rcp(d);  // 1 / d to 2^-24 or better, then cubic in its error
+    const double e = fma(-d, c, 1.0);
+    c = fma(c, fma(e, e, e), c);
+    const double y = fma(c, kErfcYScale, kErfcYShift);
+    double p = kErfcPoly[19];
+#pragma unroll
+    for (int k = 18; k >= 0; --k)
+        p = fma(p, y, kErfcPoly[k]);
+    return p * gauss;
+}
 // hardware reciprocal square root (1 ulp); pair distances are far above the FP32 denormal range
 __device__ __forceinline__ float d_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double d_rsqrt(double x) { return 1.0 / sqrt(x); }
+// FP64: the hardware's (2^-24 or better) and one step of third order
+__device__ __forceinline__ double d_rsqrt(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
 __device__ __forceinline__ float d_length(float r2) { return r2 * __builtin_amdgcn_rsqf(r2); }
 __device__ __forceinline__ double d_length(double r2) { return sqrt(r2); }
 __device__ __forceinline__ float d_rint(float x) { return rintf(x); }
 __device__ __forceinline__ double d_rint(double x) { return rint(x); }
+
+__device__ __forceinline__ float fma_r(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_r(double a, double b, double c) { return fma(a, b, c); }
 
 constexpr int kWavesPerWG = 4;  // waves of a block in the pair launches
 constexpr int kTileCost = 256;  // per-tile cost of staging and scanning, in units of pairs (measured)
@@ -236,31 +282,29 @@ template <typename R, bool THIRD, bool MI> struct PairGeom {
         const R rinv2 = rinv * rinv;
         const R gauss = d_exp2(ew.nb2l * r2);
         const R gb = ew.g * gauss;
-        const R b0 = d_erfc_g(ew.beta * r, gauss) * rinv;
-        const R b1 = (b0 + gb) * rinv2;
-        const R b2 = ((R)3 * b1 + ew.t * gb) * rinv2;
         const R a = ai < aj ? ai : aj;
         const R u = r * ip.w * jp.w;
         const R eps = a * u * u * u;
         const R ex = d_exp2(eps * (R)-1.4426950408889634);
-        const R rinv3 = rinv * rinv2, rinv5 = rinv3 * rinv2;
-        b1p = b1 - ex * rinv3;
-        b2p = b2 - (R)3 * ((R)1 + eps) * ex * rinv5;
-        if (THIRD) {
-            const R b3 = ((R)5 * b2 + ew.t2 * gb) * rinv2;
-            b3p = b3 - (R)15 * ((R)1 + eps + (R)0.6 * eps * eps) * ex * rinv5 * rinv2;
-        } else {
+        // the damped functions follow the recursion of the plain ones, with the Thole terms'
+        // increments 3 eps e^-eps / r^3 and 9 eps^2 e^-eps / r^5 taken off:
+        //   B1' = ((erfc - e^-eps) / r + gb) / r^2,
+        //   B2' = (3 B1' + t gb - 3 eps e^-eps / r^3) / r^2,
+        //   B3' = (5 B2' + t^2 gb - 9 eps^2 e^-eps / r^5) / r^2
+        const R s = d_erfc_g(ew.beta * r, gauss) - ex;
+        b1p = fma_r(s, rinv, gb) * rinv2;
+        const R er = eps * ex * (rinv * rinv2);
+        b2p = fma_r((R)3, b1p, fma_r((R)-3, er, ew.t * gb)) * rinv2;
+        if (THIRD)
+            b3p = fma_r((R)5, b2p, fma_r((R)-9 * eps, er * rinv2, ew.t2 * gb)) * rinv2;
+        else
             b3p = 0;
-        }
         if constexpr (sizeof(R) == 4) {
             if (r2 < kCloseR2)
                 close_pair_series<R, THIRD>(r2, r, rinv, a, ip.w * jp.w, ew, b1p, b2p, b3p);
         }
     }
 };
-
-__device__ __forceinline__ float fma_r(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ __forceinline__ double fma_r(double a, double b, double c) { return fma(a, b, c); }
 
 // Pair kinds: pair() adds the field at i from j to ei (the caller's running sum over the row)
 // and returns the field at j from i in ej.
@@ -743,7 +787,7 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
                     for (int v = 0; v < NV; ++v)
                         di[v] = s_id[v][i];
                 }
-                const int k = __ffsll((long long)rem) - 1;
+                const int k = __builtin_ctzll(rem);
                 rem &= rem - 1ull;
                 R4 dj[NV];
 #pragma unroll

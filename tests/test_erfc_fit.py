@@ -34,3 +34,33 @@ def test_fp32_erfc_relative_error():
         # with the Gaussian factor: erfc itself to FP32-level relative accuracy
         e = p.astype(np.float64) * np.exp(-x.astype(np.float64) ** 2)
         assert np.max(np.abs(e - erfc(x.astype(np.float64))) / erfc(x.astype(np.float64))) < 6e-7
+
+
+def kernel_table(name):
+    m = re.search(r"constexpr double %s\[\d+\] = \{([^}]*)\};" % name, open(SRC).read())
+    return [float(v) for v in m.group(1).replace("\n", " ").split(",")]
+
+
+def kernel_horner(coef, x):
+    """The value and a bound on its rounding: 2 n u sum |c_k| |x|^k."""
+    p = np.full_like(x, coef[-1])
+    for c in coef[-2::-1]:
+        p = p * x + c
+    return p, 2 * len(coef) * 2.0 ** -53 * sum(abs(c) * np.abs(x) ** k for k, c in enumerate(coef))
+
+
+def test_fp64_erfc_and_exp2_polynomials():
+    """The FP64 polynomials at their rounding bounds (and a few units of scipy's own), the erfc also
+    past the end of its fit, where the Gaussian makes it nothing beside a field."""
+    body = open(SRC).read()
+    scale, shift = (float(v) for v in re.search(
+        r"kErfcYScale = ([-0-9.]+), kErfcYShift = ([-0-9.]+);", body).groups())
+    x = np.linspace(0.0, 6.5, 100001)
+    p, bound = kernel_horner(kernel_table("kErfcPoly"), scale / (4.0 + x) + shift)
+    assert np.all(np.abs(p - erfcx(x)) <= bound + 4e-15 * erfcx(x))
+    far = np.linspace(6.5, 40.0, 1001)
+    p, _ = kernel_horner(kernel_table("kErfcPoly"), scale / (4.0 + far) + shift)
+    assert np.all(np.abs(p - erfcx(far)) * np.exp(-far ** 2) < 1e-20)
+    f = np.linspace(-0.5, 0.5, 100001)
+    q, bound = kernel_horner([1.0] + kernel_table("kExp2Poly"), f)
+    assert np.all(np.abs(q - np.exp2(f)) <= bound + 4e-16)
