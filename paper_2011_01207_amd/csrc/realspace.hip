@@ -615,13 +615,35 @@ template <typename R> struct RadialKind {
 // loads and stores are one contiguous row.  A tile whose rows end beyond coef_cap_rows is
 // evaluated as with kCoefCompute (the store did not fit); record and replay agree on which.
 // ------------------------------------------------------------------------------------------
+// A block's records in LDS.  FP64 records are held as two arrays of halves: 16-byte reads at a stride
+// of 32 bytes would use every other group of four banks only, and the lanes' reads of arbitrary
+// records are what bounds the FP64 replay (LDS busy 79 % of the time): 62 -> 58 us at 96,000 atoms.
+template <typename R> struct Records;
+template <> struct Records<float> {
+    float4 v[kBlock];
+    __device__ __forceinline__ float4 get(int k) const { return v[k]; }
+    __device__ __forceinline__ void set(int k, const float4& x) { v[k] = x; }
+};
+template <> struct Records<double> {
+    double2 lo[kBlock], hi[kBlock];
+    __device__ __forceinline__ double4 get(int k) const
+    {
+        const double2 a = lo[k], b = hi[k];
+        return make_double4(a.x, a.y, b.x, b.y);
+    }
+    __device__ __forceinline__ void set(int k, const double4& x)
+    {
+        lo[k] = make_double2(x.x, x.y);
+        hi[k] = make_double2(x.z, x.w);
+    }
+};
+
 template <typename R, bool FIX, class K, int W> struct TileLds {
-    using R4 = typename V4<R>::T;
     using LT = typename LdsAcc<FIX>::T;
-    R4 ip[kBlock];                  // i offset from the block origin, w = alpha^-1/6
-    R4 id[K::NV][kBlock];           // i source data
-    R4 jp[W][kBlock];               // j offset from the i-block origin, w = alpha^-1/6
-    R4 jd[W][K::NV][kBlock];
+    Records<R> ip;                  // i offset from the block origin, w = alpha^-1/6
+    Records<R> id[K::NV];           // i source data
+    Records<R> jp[W];               // j offset from the i-block origin, w = alpha^-1/6
+    Records<R> jd[W][K::NV];
     LT ei[3][kBlock];               // block i-field over all tiles
     LT ej[W][3][kBlock];            // tile j-field
     unsigned long long mask[W][kBlock];
@@ -657,14 +679,14 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
     if (tid < kBlock) {
         const int si = I * kBlock + tid;
         const R4 oi = off[si], pi = par[si];
-        s_ip[tid] = R4{oi.x, oi.y, oi.z, pi.z};
+        s_ip.set(tid, R4{oi.x, oi.y, oi.z, pi.z});
         R4 d[NV];
         K::load(src, si, pi.w, d);
         if constexpr (SJ)
             K::scale_i(d, (R)kFixQScaleF);
 #pragma unroll
         for (int v = 0; v < NV; ++v)
-            s_id[v][tid] = d[v];
+            s_id[v].set(tid, d[v]);
     }
     if (tid < 3 * kBlock)
         s_ei[tid / kBlock][tid % kBlock] = (LT)0;
@@ -732,7 +754,7 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
                     K::load(src, sj, aj, d);
                 }
             }
-            s_jp[w][lane] = R4{jr.x, jr.y, jr.z, dj};
+            s_jp[w].set(lane, R4{jr.x, jr.y, jr.z, dj});
             // with integer sums the i-field of a row is linear in the j sources, so they are held
             // times 2^38 as the i sources are, and a row's i-field goes to the accumulator
             // pre-scaled too
@@ -740,7 +762,7 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
                 K::scale_i(d, (R)kFixQScaleF);
 #pragma unroll
             for (int v = 0; v < NV; ++v)
-                s_jd[w][v][lane] = d[v];
+                s_jd[w][v].set(lane, d[v]);
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c)
@@ -757,11 +779,11 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
         if (p0 < p1) {
             int i = (int)(ws & 63u);
             unsigned long long rem = s_mask[w][i] & (~0ull << (ws >> 8));
-            R4 ip = s_ip[i];
+            R4 ip = s_ip.get(i);
             R4 di[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v)
-                di[v] = s_id[v][i];
+                di[v] = s_id[v].get(i);
             R ea[3] = {0, 0, 0};
             // one pair of the walk: the next set bit (when the row is used up, its i-field goes
             // to the block accumulator and the lane moves to the next row with pairs), the
@@ -782,19 +804,19 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
                     // the next row with pairs (one exists: the lane's share is not used up)
                     i = __builtin_ctzll(rows_used & (~1ull << i));
                     rem = s_mask[w][i];
-                    ip = s_ip[i];
+                    ip = s_ip.get(i);
 #pragma unroll
                     for (int v = 0; v < NV; ++v)
-                        di[v] = s_id[v][i];
+                        di[v] = s_id[v].get(i);
                 }
                 const int k = __builtin_ctzll(rem);
                 rem &= rem - 1ull;
                 R4 dj[NV];
 #pragma unroll
                 for (int v = 0; v < NV; ++v)
-                    dj[v] = s_jd[w][v][k];
+                    dj[v] = s_jd[w][v].get(k);
                 R ej[3];
-                eval(s_jp[w][k], dj, ej);
+                eval(s_jp[w].get(k), dj, ej);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     if constexpr (SJ)
