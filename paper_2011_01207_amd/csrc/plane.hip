@@ -120,9 +120,9 @@ template <typename R> struct RealReduceArgs {
     double* ereal;
     __device__ __forceinline__ void run(int wg) const
     {
-        const int s = wg * blockDim.x + threadIdx.x;
-        if (s < npad)
-            real_reduce<R>(s, eipart, jbuf, rev_ptr, rev_idx, ereal);
+        const int t = wg * blockDim.x + threadIdx.x;
+        if (t < 4 * npad)
+            real_reduce<R>(t, eipart, jbuf, rev_ptr, rev_idx, ereal);
     }
 };
 
@@ -1069,13 +1069,13 @@ template <typename R> struct PlanePasses {
         const RealReduceArgs<R> rr{reduce ? c->npad : 0, c->eipart, (const R*)c->jbuf, c->rev_ptr, c->rev_idx,
                                    c->ereal};
         if (const int nt = yxy) {
-            hipLaunchKernelGGL(k_pme_yxy<R>, dim3(g.kh + (reduce ? cdiv(c->npad, nt) : 0), ng), dim3(nt),
+            hipLaunchKernelGGL(k_pme_yxy<R>, dim3(g.kh + (reduce ? cdiv(4 * c->npad, nt) : 0), ng), dim3(nt),
                                lds_yxy(g, sizeof(C)), c->stream, g, d[1], d[0], gc, gc1, (const R*)c->theta_pl,
                                roots[1], roots[0], rr, c->sc, ud);
             return;
         }
         const size_t ly = lds_lines(g.K1, g.kc, sizeof(C)), lx = lds_lines(g.K0, g.kc, sizeof(C));
-        hipLaunchKernelGGL((k_pme_ylines<R, -1>), dim3(g.K0 * g.nkc + (reduce ? cdiv(c->npad, g.nty) : 0), ng),
+        hipLaunchKernelGGL((k_pme_ylines<R, -1>), dim3(g.K0 * g.nkc + (reduce ? cdiv(4 * c->npad, g.nty) : 0), ng),
                            dim3(g.nty), ly, c->stream, g, d[1], gc, gc1, roots[1], rr, c->sc, ud);
         hipLaunchKernelGGL(k_pme_xconv<R>, dim3(g.K1 * g.nkc, ng), dim3(g.ntx), lx, c->stream, g, d[0], gc, gc1,
                            (const R*)c->theta_pl, roots[0], c->sc, ud);

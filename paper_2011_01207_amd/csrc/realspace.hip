@@ -917,9 +917,9 @@ __global__ void k_real_reduce(int npad, const double* __restrict__ eipart, const
     __builtin_amdgcn_s_setprio(3);
     if (use_done && sc->done)
         return;
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < npad)
-        real_reduce<R>(s, eipart, jbuf, rev_ptr, rev_idx, ereal);
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < 4 * npad)
+        real_reduce<R>(t, eipart, jbuf, rev_ptr, rev_idx, ereal);
 }
 
 // Waves per block: four where the blocks fill the chip (a block's tiles share its staged i data and
@@ -1067,10 +1067,10 @@ void launch_real_reduce(amoeba_ctx* c, double* ereal, hipStream_t st, bool use_d
     if (!st)
         st = c->stream;
     if (c->mixed)
-        hipLaunchKernelGGL(k_real_reduce<float>, dim3((c->npad + 255) / 256), dim3(256), 0, st, c->npad,
+        hipLaunchKernelGGL(k_real_reduce<float>, dim3(c->npad / 64), dim3(256), 0, st, c->npad,
                            c->eipart, (const float*)c->jbuf, c->rev_ptr, c->rev_idx, ereal, c->sc, (int)use_done);
     else
-        hipLaunchKernelGGL(k_real_reduce<double>, dim3((c->npad + 255) / 256), dim3(256), 0, st, c->npad,
+        hipLaunchKernelGGL(k_real_reduce<double>, dim3(c->npad / 64), dim3(256), 0, st, c->npad,
                            c->eipart, (const double*)c->jbuf, c->rev_ptr, c->rev_idx, ereal, c->sc, (int)use_done);
 }
 
