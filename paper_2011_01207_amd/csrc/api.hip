@@ -231,14 +231,17 @@ static int check_overflow(amoeba_ctx* c, const double* v_slot)
     return AMOEBA_OK;
 }
 
-int begin_config(amoeba_ctx* c, const double* pos, const char* who)
+int begin_config(amoeba_ctx* c, const double* pos, const char* who, bool recip)
 {
     int rc = ready(c, who);
     if (rc)
         return rc;
     if (!pos)
         return set_error(c, AMOEBA_E_INVALID, std::string(who) + ": NULL pos");
-    return prepare_config(c, pos);
+    rc = prepare_config(c, pos);
+    if (rc == AMOEBA_OK && recip)
+        pme_bins_current(c);
+    return rc;
 }
 
 }  // namespace amoeba

@@ -1220,8 +1220,6 @@ int sort_params(amoeba_ctx* c)
     return AMOEBA_OK;
 }
 
-void pme_bin_atoms(amoeba_ctx* c);
-
 // Rows of the stored pair coefficients of the current masks; their total reaches the host with
 // its next wait.
 void coef_scan_rows(amoeba_ctx* c)
@@ -1266,7 +1264,7 @@ static int refresh_tiles(amoeba_ctx* c)
     c->coef_rows_ok = false;
     if (coef_store_on(c))
         coef_scan_rows(c);
-    pme_bin_atoms(c);
+    c->pme_bins_stale = true;
     return AMOEBA_OK;
 }
 
@@ -1430,6 +1428,7 @@ int build_blocklist(amoeba_ctx* c, const double* pos)
     if (rc != AMOEBA_OK)
         return rc;
     refresh_tiles(c);   // the pair count is read when amoeba_get_info asks for it
+    pme_bins_current(c);
     c->list_built = true;
     c->cfg_valid = true;
     return AMOEBA_OK;

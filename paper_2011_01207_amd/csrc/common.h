@@ -226,6 +226,7 @@ struct amoeba_ctx {
     mutable std::shared_ptr<amoeba::PlanePlan> plane_plan;  // geometry of the plane passes, made on first use
     int pme_path = 0;              // amoeba_pme_path requested by the caller
     bool rec_plane = false;        // the last reciprocal field came from the plane path
+    bool pme_bins_stale = true;    // the atoms are not binned for the current positions
     bool brick_bins_stale = true;  // brick bins and spline table not built for the current positions
     int32_t* xb_start = nullptr;   // [K0+1] atoms binned by the x line of their base point
     int32_t* xb_count = nullptr;   // [K0+1]
@@ -396,7 +397,7 @@ void launch_force_tiles(amoeba_ctx* c, const void* src, double* out, hipStream_t
 
 // pme.hip
 int pme_setup(amoeba_ctx* c);
-void pme_bin_atoms(amoeba_ctx* c);
+void pme_bins_current(amoeba_ctx* c);  // bin the atoms for the reciprocal passes, unless that is done
 int pme_dipole_field(amoeba_ctx* c, bool use_done);   // spread p -> FFT -> convolve -> FFT
 int pme_perm_potential(amoeba_ctx* c);                // spread multipoles -> ... -> potential grid
 void pme_scan_excl(amoeba_ctx* c, int n, const int* in, int* out);
@@ -430,7 +431,8 @@ int read_flags(amoeba_ctx* c, int* out);
 int check_vec_finite(amoeba_ctx* c, const double* v, size_t n, const char* what);
 void launch_check_overflow(amoeba_ctx* c, const double* v_slot);  // |v| < kFixRange, flag on the device
 void launch_gather_mpole(amoeba_ctx* c, const double* q, const double* dip, const double* quad, int* flags);
-int begin_config(amoeba_ctx* c, const double* pos, const char* who);
+// recip: the call needs the reciprocal passes
+int begin_config(amoeba_ctx* c, const double* pos, const char* who, bool recip = true);
 
 // guess.hip
 int guess_compute(amoeba_ctx* c);                     // bases + features of v_e (slot order)

@@ -1225,7 +1225,7 @@ int amoeba_guess_features(amoeba_ctx* c, const double* pos, const double* e_perm
     c->err.clear();
     if (!e_perm || !feat_out || !basis_out)
         return set_error(c, AMOEBA_E_INVALID, "amoeba_guess_features: NULL argument");
-    int rc = begin_config(c, pos, "amoeba_guess_features");
+    int rc = begin_config(c, pos, "amoeba_guess_features", false);
     if (rc)
         return rc;
     if ((rc = check_vec_finite(c, e_perm, 3 * (size_t)c->n, "e_perm")))
@@ -1341,7 +1341,7 @@ int amoeba_guess_predict(amoeba_ctx* c, const double* pos, const double* e_perm,
     int rc = guess_ready(c, "amoeba_guess_predict");
     if (rc)
         return rc;
-    if ((rc = begin_config(c, pos, "amoeba_guess_predict")))
+    if ((rc = begin_config(c, pos, "amoeba_guess_predict", false)))
         return rc;
     if ((rc = check_vec_finite(c, e_perm, 3 * (size_t)c->n, "e_perm")))
         return rc;

@@ -881,9 +881,14 @@ static void ensure_brick_bins(amoeba_ctx* c)
 }
 
 // Per configuration: the bins of the path in use (the plane bins whenever the grid fits the
-// plane path; the brick bins then only when a brick-path product asks for them).
-void pme_bin_atoms(amoeba_ctx* c)
+// plane path; the brick bins then only when a brick-path product asks for them).  Called by every
+// entry point that takes the reciprocal passes; the learned guess's features and predictions take the
+// real-space field alone, and binned for nothing (18 us and four launches at 96,000 atoms).
+void pme_bins_current(amoeba_ctx* c)
 {
+    if (!c->pme_bins_stale)
+        return;
+    c->pme_bins_stale = false;
     c->brick_bins_stale = true;
     plane_bin_atoms(c);
     if (!pme_use_planes(c))

@@ -309,3 +309,28 @@ def test_radial_sums_on_both_sides_of_the_wave_limit(waters, box, prec):
     ref = G.radial_sums(s, idx)
     x = feat.cpu().numpy().astype(np.float64)[idx][:, 8:11]
     assert np.max(np.abs(x - ref)) < (1e-6 if prec == "fp64" else 2e-5) * max(1.0, float(np.max(ref)))
+
+
+@pytest.mark.parametrize("path", ["planes", "bricks"])
+def test_prediction_then_products_on_the_same_positions(path):
+    """A prediction takes no reciprocal field; the calls after it on the same positions do, with the
+    atoms where they are then: the bits of a context that never predicted."""
+    s = synth.water648()
+    pos2 = torch.tensor(np.mod(s.pos + 0.02 * np.random.default_rng(8).standard_normal(s.pos.shape), s.box), device=DEV)
+    out = []
+    for predict in (False, True):
+        ctx, t = amoeba.context_for(dataclasses.replace(s, buffer=1.0), precision="mixed", device=DEV)
+        try:
+            ctx.set_pme_path(path)
+            ctx.guess_set_model(random_model(71))
+            ctx.perm_field(t["pos"], t["q"], t["dip"], t["quad"])
+            if predict:
+                ctx.guess_predict(pos2, torch.zeros_like(pos2))
+            e = ctx.perm_field(pos2, t["q"], t["dip"], t["quad"])
+            if predict:
+                ctx.guess_predict(t["pos"], e)
+            out.append((e.cpu().numpy(), ctx.dipole_matvec(t["pos"], 0.1 * e).cpu().numpy()))
+        finally:
+            ctx.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
