@@ -178,10 +178,7 @@ int sort_params(amoeba_ctx* c);
 
 int read_flags(amoeba_ctx* c, int* out)
 {
-    hipMemcpyAsync(c->flags_host, c->flags, sizeof(int), hipMemcpyDeviceToHost, c->stream);
-    int rc = hip_check(c, hipStreamSynchronize(c->stream), "flags");
-    *out = c->flags_host[0];
-    return rc;
+    return wait_flags(c, post_flags(c), out, "flags");
 }
 
 int check_vec_finite(amoeba_ctx* c, const double* v, size_t n, const char* what)
@@ -362,6 +359,8 @@ int amoeba_create(const amoeba_params* p, void* hip_stream, amoeba_ctx** out)
             hipHostGetDevicePointer((void**)&c->sc_host_dev, c->sc_host, 0) != hipSuccess ||
             hipHostMalloc((void**)&c->flags_host, 64, hipHostMallocDefault) != hipSuccess ||
             hipHostMalloc((void**)&c->pairs_host, 64, hipHostMallocDefault) != hipSuccess ||
+            hipHostMalloc((void**)&c->post_host, 64, hipHostMallocCoherent) != hipSuccess ||
+            hipHostGetDevicePointer((void**)&c->post_dev, c->post_host, 0) != hipSuccess ||
             hipHostGetDevicePointer((void**)&c->pairs_host_dev, c->pairs_host, 0) != hipSuccess) {
             rc = set_error(c, AMOEBA_E_NOMEM, "pinned host allocation failed");
             break;
@@ -418,6 +417,8 @@ int amoeba_destroy(amoeba_ctx* c)
         hipHostFree(c->flags_host);
     if (c->pairs_host)
         hipHostFree(c->pairs_host);
+    if (c->post_host)
+        hipHostFree(c->post_host);
     coef_release(c);
     if (c->g_scal_host)
         hipHostFree(c->g_scal_host);

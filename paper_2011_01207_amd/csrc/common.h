@@ -289,6 +289,9 @@ struct amoeba_ctx {
     // the reciprocal passes on the context stream: forked and joined with events
     hipStream_t stream2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    int* post_host = nullptr;              // coherent host memory: sequence number and flags (post_flags)
+    int* post_dev = nullptr;
+    int post_seq = 0;
     hipEvent_t ev_build = nullptr;         // recorded after a list build's counts are copied
     hipEvent_t ev_pairs = nullptr;         // recorded after the pair count of a refresh is written
     // one PCG iteration (product on both streams, update, direction) as a HIP graph: captured on
@@ -431,6 +434,8 @@ int read_flags(amoeba_ctx* c, int* out);
 int check_vec_finite(amoeba_ctx* c, const double* v, size_t n, const char* what);
 void launch_check_overflow(amoeba_ctx* c, const double* v_slot);  // |v| < kFixRange, flag on the device
 void launch_gather_mpole(amoeba_ctx* c, const double* q, const double* dip, const double* quad, int* flags);
+int post_flags(amoeba_ctx* c);  // enqueue the flags' way to the host
+int wait_flags(amoeba_ctx* c, int seq, int* f, const char* who);
 // recip: the call needs the reciprocal passes
 int begin_config(amoeba_ctx* c, const double* pos, const char* who, bool recip = true);
 

@@ -112,3 +112,42 @@ def test_order_of_uneven_systems(waters, cube, box, grid):
             assert np.array_equal(out, again)   # fixed-point sums; FP64 sums follow the list's order
         else:
             assert_fields(again, ref, 1e-12)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_masks_refreshed_ahead_of_the_flags(prec):
+    """Calls on the same, on changed and on refused positions in every order, and after new atom
+    parameters on the same positions: each gives what a context that saw only those positions gives."""
+    s = dataclasses.replace(synth.water648(), buffer=1.0)
+    rng = np.random.default_rng(12)
+    at = [torch.tensor(np.mod(s.pos + d, s.box), device=DEV)
+          for d in (0.0, 0.03 * rng.standard_normal(s.pos.shape))]
+    stale, nan = at[0].clone(), at[0].clone()
+    stale[5, 0] = (stale[5, 0] + 3.0) % float(s.box[0])
+    nan[7, 2] = float("nan")
+    mu = torch.tensor(0.05 * rng.standard_normal(s.pos.shape), device=DEV)
+    want = []
+    for scale in (1.0, 1.1):
+        for p in at:
+            ctx, t = amoeba.context_for(s, precision=prec, device=DEV)
+            ctx.set_atoms(t["alpha"] * scale, t["thole"], t["sc_ptr"], t["sc_j"], t["sc_s"])
+            want.append(ctx.dipole_matvec(p, mu).cpu().numpy())
+            ctx.close()
+    ctx, t = amoeba.context_for(s, precision=prec, device=DEV)
+    try:
+        for k, scale in ((0, 1.0), (0, 1.0), (1, 1.0), (stale, 4), (1, 1.0), (nan, 8), (stale, 4), (0, 1.0), (0, 1.1),
+                         (1, 1.1), (1, 1.0), (nan, 8), (1, 1.1), (0, 1.0)):
+            if not isinstance(k, int):
+                with pytest.raises(amoeba.AmoebaError) as ei:
+                    ctx.dipole_matvec(k, mu)
+                assert ei.value.status == (amoeba.AMOEBA_E_LIST if scale == 4 else amoeba.AMOEBA_E_NUMERIC)
+                continue
+            ctx.set_atoms(t["alpha"] * scale, t["thole"], t["sc_ptr"], t["sc_j"], t["sc_s"])
+            out = ctx.dipole_matvec(at[k], mu).cpu().numpy()
+            ref = want[k + (2 if scale == 1.1 else 0)]
+            if prec == "mixed":
+                assert np.array_equal(out, ref)
+            else:
+                assert_fields(out, ref, 1e-12)
+    finally:
+        ctx.close()
