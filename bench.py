@@ -468,10 +468,11 @@ def roofline(s, res):
     flops = FLOPS_PER_PAIR * res["n_pairs"] * n_real
     mi = "true" if res.get("pair_min_image") else "false"
     cm = 2 if res.get("pair_store") else 0
+    waves = 4 if n > 25600 else 8  # waves per block of the tiles (eight in a small system)
     stages["real"] = {"bound": "alu", "achieved": flops / (ms * 1e-3) / 1e12, "peak": PEAK_FP32_VALU,
                       "unit": "TFLOP/s", "ms_total": ms, "launches": tim["launches"]["real"],
                       "productive_launches": n_real,
-                      "kernel": f"k_block_tiles<float, true, DipoleKind<float>, {mi}, {cm}>",
+                      "kernel": f"k_block_tiles<float, true, DipoleKind<float>, {mi}, {cm}, {waves}>",
                       "algorithmic_per_launch": FLOPS_PER_PAIR * res["n_pairs"],
                       "peak_nonpacked": PEAK_FP32_NONPACKED,
                       "frac_nonpacked": flops / (ms * 1e-3) / 1e12 / PEAK_FP32_NONPACKED}

@@ -1479,16 +1479,15 @@ int post_flags(amoeba_ctx* c)
 
 int wait_flags(amoeba_ctx* c, int seq, int* f, const char* who)
 {
-    int rc = hip_check(c, hipGetLastError(), who);
-    if (rc)
-        return rc;
+    int rc = AMOEBA_OK;
     for (unsigned spin = 1; __atomic_load_n(&c->post_host[0], __ATOMIC_ACQUIRE) != seq; ++spin) {
         if (spin % 4096)
             continue;
         // the stream ended or failed: its own word on it
-        const hipError_t e = hipStreamQuery(c->stream);
-        if (e == hipErrorNotReady)
+        if (hipStreamQuery(c->stream) == hipErrorNotReady) {
+            (void)hipGetLastError();  // not an error to leave behind
             continue;
+        }
         if ((rc = hip_check(c, hipStreamSynchronize(c->stream), who)))
             return rc;
         if (__atomic_load_n(&c->post_host[0], __ATOMIC_ACQUIRE) != seq)
