@@ -28,18 +28,14 @@
 #include <climits>
 #include <cmath>
 
-#include "common.h"
 #include <type_traits>
+
+#include "common.h"
+#include "sort_key.h"
 
 namespace amoeba {
 
 __device__ __forceinline__ double mimg(double d, double L) { return mimg_fp64(d, L, 1.0 / L); }
-
-__device__ __forceinline__ double wrap_box(double x, double L)
-{
-    double y = x - L * floor(x / L);
-    return (y >= L) ? y - L : y;
-}
 
 // Sort key of atom a: column (cz, cy) in a serpentine order, then x within the column (also
 // serpentine) quantised to kXBits bits (box / 4096, far below the block size); packed as
@@ -53,14 +49,7 @@ __device__ __forceinline__ double wrap_box(double x, double L)
 // them); nor is a bucket of more than kRankMax atoms (65,536 atoms within a slice of box / 4096 or
 // a few: no list capacity holds their neighbours), so that no input makes the ranking slow.
 // Also clears the build's error flags.
-constexpr int kXBits = 12;
 constexpr int kRankMax = 65536;
-constexpr unsigned kKeyNonFinite = 0xffffffffu;
-
-__device__ __forceinline__ int bucket_of(unsigned key, int shift, int nbucket)
-{
-    return key == kKeyNonFinite ? nbucket - 1 : (int)(key >> shift);
-}
 
 __global__ void k_sort_keys(int n, const double* __restrict__ pos, double3 box, int ny, int nz, int shift,
                             int nbucket, unsigned* __restrict__ keys, int* __restrict__ arrival,
@@ -71,20 +60,8 @@ __global__ void k_sort_keys(int n, const double* __restrict__ pos, double3 box, 
         flags[0] = 0;
     if (a >= n)
         return;
-    double x = wrap_box(pos[3 * a], box.x), y = wrap_box(pos[3 * a + 1], box.y),
-           z = wrap_box(pos[3 * a + 2], box.z);
-    unsigned key = kKeyNonFinite;
-    if (x == x && y == y && z == z) {
-        const unsigned xmax = (1u << kXBits) - 1u;
-        int cy = min(ny - 1, (int)(y / box.y * ny));
-        int cz = min(nz - 1, (int)(z / box.z * nz));
-        int cys = (cz & 1) ? ny - 1 - cy : cy;
-        const unsigned col = (unsigned)(cz * ny + cys);
-        unsigned q = min(xmax, (unsigned)(x / box.x * (double)(1u << kXBits)));
-        if (col & 1u)
-            q = xmax - q;
-        key = (col << kXBits) | q;
-    }
+    const unsigned key = sort_key(wrap_box(pos[3 * a], box.x), wrap_box(pos[3 * a + 1], box.y),
+                                  wrap_box(pos[3 * a + 2], box.z), box.x, box.y, box.z, ny, nz);
     keys[a] = key;
     arrival[a] = atomicAdd(&count[bucket_of(key, shift, nbucket)], 1);
 }

@@ -151,3 +151,29 @@ def test_masks_refreshed_ahead_of_the_flags(prec):
                 assert_fields(out, ref, 1e-12)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_coordinates_of_any_magnitude(prec):
+    """Coordinates far beyond what the wrapping resolves (a diverged trajectory) build a list and give
+    a finite field, and the next ordinary positions the right one."""
+    s = synth.water648()
+    mu = 0.05 * np.random.default_rng(3).standard_normal((s.n, 3))
+    ref = O.matvec(s, mu, "spme")
+    m = torch.tensor(mu, device=DEV)
+    ctx, t = amoeba.context_for(s, precision=prec, device=DEV)
+    try:
+        for size in (1e14, 1e16, 1e17, 1e18, 1e21, 1e40, 1e300):
+            print(f"[gpu] coordinates of {size:g} {prec}", flush=True)
+            rng = np.random.default_rng(int(np.log10(size)))
+            far = s.pos.copy()
+            for a in (5, 200, 647):
+                far[a] = size * rng.uniform(-1.0, 1.0, 3)
+            far[70, 1] = size
+            pos = torch.tensor(far, device=DEV)
+            ctx.update_blocklist(pos)
+            assert torch.isfinite(ctx.dipole_matvec(pos, m)).all()
+            ctx.build_blocklist(t["pos"])
+            assert_fields(ctx.dipole_matvec(t["pos"], m).cpu().numpy(), ref, 1e-12 if prec == "fp64" else 2e-6)
+    finally:
+        ctx.close()
