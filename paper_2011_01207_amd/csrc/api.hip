@@ -365,6 +365,8 @@ int amoeba_create(const amoeba_params* p, void* hip_stream, amoeba_ctx** out)
             rc = set_error(c, AMOEBA_E_NOMEM, "pinned host allocation failed");
             break;
         }
+        // the host waits for a sequence number here: not one that the memory's last owner left
+        std::memset(c->post_host, 0, 64);
         if (hipEventCreateWithFlags(&c->ev[0], hipEventDisableTiming) != hipSuccess ||
             hipEventCreateWithFlags(&c->ev[1], hipEventDisableTiming) != hipSuccess ||
             hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) != hipSuccess ||

@@ -177,3 +177,23 @@ def test_coordinates_of_any_magnitude(prec):
             assert_fields(ctx.dipole_matvec(t["pos"], m).cpu().numpy(), ref, 1e-12 if prec == "fp64" else 2e-6)
     finally:
         ctx.close()
+
+
+def test_first_flags_of_a_context_are_its_own():
+    """A context of one checked call leaves its sequence number and flag word in host memory that the
+    next context may be given: the first check there is made all the same."""
+    s = synth.water648()
+    t = [torch.tensor(a, device=DEV) for a in (s.alpha, s.thole)]
+    csr = (torch.tensor(s.sc_ptr, dtype=torch.int32, device=DEV), torch.tensor(s.sc_j, dtype=torch.int32, device=DEV),
+           torch.tensor(s.sc_s, device=DEV))
+    for _ in range(4):
+        ctx = amoeba.Context(s.n, s.box, grid=s.grid, precision="mixed")
+        ctx.set_atoms(*t, *csr)
+        ctx.close()
+        ctx = amoeba.Context(s.n, s.box, grid=s.grid, precision="mixed")
+        try:
+            with pytest.raises(amoeba.AmoebaError) as ei:
+                ctx.set_atoms(-t[0], t[1], *csr)
+            assert ei.value.status == amoeba.AMOEBA_E_INVALID
+        finally:
+            ctx.close()
