@@ -637,12 +637,15 @@ __device__ __forceinline__ int nth_set_bit(unsigned long long m, int r)
 // collected, in order, until a round of boxes might not fit any more (most blocks: once), and a wave
 // takes one candidate at a time: lane l holds its atom l, atoms out of reach of I's box drop out, and
 // the squared distances of 16 of them at a time to the 64 atoms of I are four matrix instructions,
-// |q|^2 + (-2 q, 1) . (j, |j|^2), taken to the least over I's atoms.  FP32 with a 1e-3 A margin, far
-// above the rounding of the sums (offsets of 50 A: 1e-4 A^2 at the reach of 10 A, 1e-5 A): the filter
-// only has to keep a superset, the masks of every configuration decide at rc in FP64.  MI (a box
-// where twice the largest half-extent plus rcb reaches half an edge): the minimum image of every
-// pair, on the vector units.  The kept atoms are written at offsets from an ordered scan, so the list
-// does not depend on scheduling, and counted for the reverse index.
+// |q|^2 + (-2 q, 1) . (j, |j|^2), taken to the least over I's atoms.  The filter only has to keep a
+// superset, the masks of every configuration decide at rc in FP64: the reach has a margin of 1e-3 A, or
+// twice the rounding of a component of the difference form where that is more (offsets in thousands of
+// A).  The matrix form cancels: with S >= |q|^2 + |j|^2 its rounding is below S 2^-19 (as in
+// k_tile_refresh), and where that is above the margin, or the minimum image is needed (twice the
+// largest half-extent plus rcb reaches half an edge), the block's pairs are taken as differences on the
+// vector units: blocks of some 70 A and more, in dilute systems or across a void.  The kept atoms are
+// written at offsets from an ordered scan, so the list does not depend on scheduling, and counted for
+// the reverse index.
 // 76 us for 4,500 blocks; testing the queued atoms one per thread against the block's atoms on the
 // vector units, in rounds of 256 boxes, took 163 us.
 constexpr int kFiltCap = 512;  // candidates of a round
@@ -688,15 +691,22 @@ __global__ __launch_bounds__(256, 6) void k_filter(int nb, int n, const double4*
         // a phantom slot is far from everything
         s_i[tid] = si < n ? make_float4(x, y, z, x * x + y * y + z * z) : make_float4(0.0f, 0.0f, 0.0f, 1e30f);
     }
-    const double rcb2 = rcb * rcb;
-    const float rf2 = (float)((rcb + 1e-3) * (rcb + 1e-3));
-    const float hxf = (float)hi.x + 1e-3f, hyf = (float)hi.y + 1e-3f, hzf = (float)hi.z + 1e-3f;
     const float Lx = (float)box.x, Ly = (float)box.y, Lz = (float)box.z;
     const float Lix = (float)binv.x, Liy = (float)binv.y, Liz = (float)binv.z;
     // largest block half-extents; pair offsets |q - j| <= h_I + (h_I + rcb + margins) <= 2 h_max + rcb
     const double ext[3] = {ext_in[0], ext_in[1], ext_in[2]};
     const bool mi = !(2.0 * ext[0] + rcb + 0.01 < 0.5 * box.x && 2.0 * ext[1] + rcb + 0.01 < 0.5 * box.y &&
                       2.0 * ext[2] + rcb + 0.01 < 0.5 * box.z);
+    // a component of a difference of FP32 offsets, each up to D, is off by at most 2 D 2^-24, and by
+    // 3 edges' 2^-24 more where an image is taken off; the distance by less than twice that
+    const float D = 2.0f * (float)fmax(ext[0], fmax(ext[1], ext[2])) + (float)rcb;
+    const float margin = fmaxf(1e-3f, (2.0f * D + (mi ? 3.0f * fmaxf(Lx, fmaxf(Ly, Lz)) : 0.0f)) * 1.1920929e-7f);
+    const double rcb2 = rcb * rcb;
+    const float rf2 = (float)((rcb + margin) * (rcb + margin));
+    const float hxf = (float)hi.x + margin, hyf = (float)hi.y + margin, hzf = (float)hi.z + margin;
+    const float reach = (float)rcb + margin, Jx = hxf + reach, Jy = hyf + reach, Jz = hzf + reach;
+    const float S = hxf * hxf + hyf * hyf + hzf * hzf + Jx * Jx + Jy * Jy + Jz * Jz;
+    const bool direct = mi || !(S * 1.9073486e-6f < 2.0f * margin * (float)rcb);
     const int dmax = (nb % 2 == 0 && I < nb / 2) ? nb / 2 : (nb - 1) / 2;
     __syncthreads();
     if (cells && w == 0) {
@@ -785,7 +795,7 @@ __global__ __launch_bounds__(256, 6) void k_filter(int nb, int n, const double4*
             const bool inb = real && bx * bx + by * by + bz * bz < rf2;
             const unsigned long long m = __ballot(inb);
             unsigned long long near = 0ull;
-            if (mi) {
+            if (direct) {
                 if (m) {
                     float r2 = 3e38f;
 #pragma unroll 4

@@ -197,3 +197,29 @@ def test_first_flags_of_a_context_are_its_own():
             assert ei.value.status == amoeba.AMOEBA_E_INVALID
         finally:
             ctx.close()
+
+
+@pytest.mark.parametrize("spread,edge", [(60.0, 700.0), (300.0, 3000.0), (900.0, 4000.0), (900.0, 9000.0)])
+@pytest.mark.parametrize("along", [(1.0, 0.0, 0.0)], ids=["axis"])
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_pairs_of_dilute_blocks(spread, edge, prec, along):
+    """64 lone pairs near the cutoff, spread over hundreds of Angstrom, so that the offsets within a
+    block dwarf the cutoff: the list and the masks hold exactly the pairs within it (no buffer)."""
+    rng = np.random.default_rng(8)
+    print(f"[gpu] dilute pairs spread={spread} edge={edge} {along} {prec}", flush=True)
+    y, z = (a.ravel() for a in np.meshgrid(*2 * (np.linspace(-spread, spread, 8),), indexing="ij"))
+    a = np.stack([rng.uniform(-0.3, 0.3, 64), y, z], 1) + rng.uniform(0.0, 0.3, 3)
+    u = np.array(along) * np.where(rng.random((64, 3)) < 0.5, 1.0, [1.0, -1.0, -1.0])
+    u /= np.linalg.norm(u, axis=1)[:, None]
+    d = 7.0 + np.where(np.arange(64) % 2, -1.0, 1.0) * 10.0 ** rng.uniform(-9, -4, 64)
+    pos = np.concatenate([a, a + d[:, None] * u]) + 0.37 * edge
+    n = len(pos)
+    ctx = amoeba.Context(n, (edge,) * 3, cutoff=7.0, grid=(32, 32, 32), precision=prec)
+    try:
+        one = torch.ones(n, dtype=torch.float64, device=DEV)
+        ctx.set_atoms(one, 0.39 * one, torch.zeros(n + 1, dtype=torch.int32, device=DEV),
+                      torch.zeros(0, dtype=torch.int32, device=DEV), torch.zeros(0, dtype=torch.float64, device=DEV))
+        ctx.build_blocklist(torch.tensor(pos, device=DEV))
+        assert ctx.info()["n_pairs"] == 32
+    finally:
+        ctx.close()
