@@ -918,8 +918,9 @@ __global__ __launch_bounds__(256) void k_fill_tiles(int nb, int tile_cap, const 
 // squared distance by at most 4 S 2^-24, that of the squares and of the five sums by less than
 // 28 S 2^-24 (also if they are cut off): where the least magnitude is above S 2^-19, every sign is
 // that of the exact value.  Otherwise (one tile in ten or so) the 16 i-atoms' pairs are classified
-// anew from the differences of their FP32 offsets, and those within a relative 1e-5 of rc^2 (far
-// above the error of that form) by the FP64 distance, so every bit equals the FP64 test.
+// anew from the differences of their FP32 offsets, and those near rc^2 by the FP64 distance, so every
+// bit equals the FP64 test.  Near is within a relative 1e-5, or 4 rc d where that is more (dilute
+// systems), d = 2^-24 (2 sqrt(S/2) + 3 edges with MI) bounding the rounding of a component of a difference.
 // MI: minimum image per pair offset, all pairs classified from the differences; without it the
 // block-relative offsets are used as they are (valid when the list build proved that no tile offset
 // can reach half the box, as for the pair kernels).
@@ -991,7 +992,6 @@ __global__ __launch_bounds__(256, 6) void k_tile_refresh(int ntiles, int ngroup,
                          jz = mimg_fp64(pj.z - o.z, box.z, binv.z);
             jrel[(size_t)t * kBlock + lane] = R4{(R)jx, (R)jy, (R)jz, wj};
             const float rcf = (float)rc2;
-            const float lo2 = (float)(rc2 * (1.0 - 1e-5)), hi2 = (float)(rc2 * (1.0 + 1e-5));
             const float Lx = (float)box.x, Ly = (float)box.y, Lz = (float)box.z;
             const float Lix = (float)binv.x, Liy = (float)binv.y, Liz = (float)binv.z;
             // absent atoms (no i-atom, no j-atom, phantom slots) lie at the origin with a square that
@@ -1012,7 +1012,8 @@ __global__ __launch_bounds__(256, 6) void k_tile_refresh(int ntiles, int ngroup,
             wp[3] = jvalid ? jn : kFar;
             s_jn[w][lane] = jvalid ? jn - rcf : kFar;
             // S: twice the largest square of the tile
-            const float thr = wave_max_pos(fmaxf(ivalid ? in2 : 0.0f, jvalid ? jn : 0.0f)) * 3.814697265625e-6f;  // 2^-18
+            const float M = wave_max_pos(fmaxf(ivalid ? in2 : 0.0f, jvalid ? jn : 0.0f));
+            const float thr = M * 3.814697265625e-6f;  // 2^-18
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1053,6 +1054,10 @@ __global__ __launch_bounds__(256, 6) void k_tile_refresh(int ntiles, int ngroup,
                 }
                 if (redo) {  // uniform
                     bits = 0;
+                    const float rc = sqrtf(rcf);
+                    const float band = fmaxf(1e-5f * rcf, rc * (4.7683716e-7f * sqrtf(M) +
+                                                                (MI ? 7.1525574e-7f * fmaxf(Lx, fmaxf(Ly, Lz)) : 0.0f)));
+                    const float lo2 = rcf - band, hi2 = rcf + band;
                     const float* pi = &s_i[w][4 * (16 * tt + lr)];
 #pragma unroll MI ? 4 : 1
                     for (int e = 0; e < 16; ++e) {

@@ -199,8 +199,8 @@ def test_first_flags_of_a_context_are_its_own():
             ctx.close()
 
 
-@pytest.mark.parametrize("spread,edge", [(60.0, 700.0), (300.0, 3000.0), (900.0, 4000.0), (900.0, 9000.0)])
-@pytest.mark.parametrize("along", [(1.0, 0.0, 0.0)], ids=["axis"])
+@pytest.mark.parametrize("spread,edge", [(60.0, 700.0), (300.0, 3000.0), (900.0, 2000.0), (900.0, 4000.0), (900.0, 9000.0)])
+@pytest.mark.parametrize("along", [(1.0, 0.0, 0.0), (0.75, 0.45, 0.48)], ids=["axis", "oblique"])
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
 def test_pairs_of_dilute_blocks(spread, edge, prec, along):
     """64 lone pairs near the cutoff, spread over hundreds of Angstrom, so that the offsets within a
