@@ -74,19 +74,22 @@ __device__ __forceinline__ double d_exp(double x) { return exp(x); }
 // 2^x: the hardware base-2 exponential in FP32
 __device__ __forceinline__ float d_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // FP64: 2^x = 2^n (1 + f q(f)), x = n + f, |f| <= 1/2, q of degree 10 (relative error 8e-18 in exact
-// arithmetic).
+// arithmetic); what rounding takes off 1 + f q(0) is kept for the last step, so that the value is rounded
+// once (1.1e-16 of it; the library's 1.3e-16).
 constexpr double kExp2Poly[11] = {
     0.6931471805599453, 0.24022650695910097, 0.0555041086648216, 0.009618129107606888, 0.0013333558146416936,
     0.0001540353044173605, 1.525273382983612e-05, 1.321544258792169e-06, 1.0178062445845774e-07,
     7.072585949269223e-09, 4.4549605981865186e-10};
 __device__ __forceinline__ double d_exp2(double x)
 {
+    x = fmax(x, -1100.0);  // 0 from there on; n has to fit an int
     const double n = rint(x), f = x - n;
     double q = kExp2Poly[10];
 #pragma unroll
-    for (int k = 9; k >= 0; --k)
+    for (int k = 9; k >= 1; --k)
         q = fma(q, f, kExp2Poly[k]);
-    return ldexp(fma(q, f, 1.0), (int)n);
+    const double h = fma(f, kExp2Poly[0], 1.0);
+    return ldexp(h + fma(f * f, q, fma(f, kExp2Poly[0], 1.0 - h)), (int)n);
 }
 __device__ __forceinline__ float d_erfc_g(float x, float gauss)
 {
@@ -103,10 +106,16 @@ __device__ __forceinline__ float d_erfc_g(float x, float gauss)
     p = fmaf(p, t, -2.098618019e-04f);
     return p * gauss;
 }
-// FP64: erfc(x) = P(y) exp(-x^2), y = 12.923.. / (4 + x) - 2.230.. (1 at x = 0, -1 at x = 6.5), P the
-// degree-19 Chebyshev interpolant of erfc(x) exp(x^2) on [0, 6.5] by fit_fp64.py (relative error 8e-19
-// in exact arithmetic; beyond 6.5 the Gaussian is below 5e-19).  The library's erfc takes three of its
-// ranges in turn where a wave's pairs lie in them.
+// FP64: the library's (3.5e-16 of the value).  P(y) below made up for its roundings took as long (multipole
+// tiles of 96,000 atoms 104 us against 100; 85 us without, at errors of 1e-15 at 1 A and 6e-15 at 7 A, most of
+// it the Gaussian's argument).
+__device__ __forceinline__ double d_erfc_g(double x, double) { return erfc(x); }
+// The same in few registers, for the rare FP64 pairs of FP32 tiles (below 0.5 A): erfc(x) = P(y) exp(-x^2),
+// y = 12.923.. / (4 + x) - 2.230.. (1 at x = 0, -1 at x = 6.5), P the degree-19 Chebyshev interpolant of
+// erfc(x) exp(x^2) on [0, 6.5] by fit_fp64.py (relative error 8e-19 in exact arithmetic).  Such a pair is
+// what cancellation leaves of erfc, so the roundings of y (P'/P is 1.25 + 0.13 y within 0.05), of the last
+// step of P and of x^2 are made up for: the relative error is at most 3.3e-16 up to x = 3.8, 7e-16 up to
+// 6.5; beyond, the absolute one is below 1e-20.
 constexpr double kErfcPoly[20] = {
     0.27942855219368923, 0.3279650373568241, 0.210251198447979, 0.1110189355085153, 0.04830152065636551,
     0.017119508331621246, 0.004801406001139516, 0.0009956606891018877, 0.00012401497071885562,
@@ -114,26 +123,31 @@ constexpr double kErfcPoly[20] = {
     2.523797547203749e-08, -8.63854257232425e-10, -1.0283977471600152e-09, 1.960646173695655e-12,
     4.2527968352153286e-11, 4.331575594317064e-14, -1.5451793580623559e-12};
 constexpr double kErfcYScale = 12.923076923076923, kErfcYShift = -2.230769230769231;
-__device__ __forceinline__ double d_erfc_g(double x, double gauss)
+constexpr double kErfcSlope = 42.0 / 13.0;  // y = 1 - slope x / (4 + x)
+__device__ __forceinline__ double erfc_fit(double x)
 {
-    const double d = 4.0 + x;
-    double c = __builtin_amdgcn_rcp(d);  // 1 / d to 2^-24 or better, then cubic in its error
-    const double e = fma(-d, c, 1.0);
-    c = fma(c, fma(e, e, e), c);
+    const double d = 4.0 + x, dl = x - (d - 4.0), c = 1.0 / d;
     const double y = fma(c, kErfcYScale, kErfcYShift);
+    // the y of x less this one
+    const double w = x * c, wl = fma(-w, dl, fma(-w, d, x)) * c, s = 1.0 - y, sl = (1.0 - s) - y;
+    const double dy = fma(-kErfcSlope, w, s) + fma(-kErfcSlope, wl, sl);
     double p = kErfcPoly[19];
-#pragma unroll
-    for (int k = 18; k >= 0; --k)
+#pragma unroll 1
+    for (int k = 18; k >= 1; --k)
         p = fma(p, y, kErfcPoly[k]);
-    return p * gauss;
+    const double p0 = fma(p, y, kErfcPoly[0]), pl = fma(p, y, kErfcPoly[0] - p0) + 2.0358621873736402e-17;
+    const double h = x * x, g = exp(-h);
+    return fma(p0, g, g * fma(p0, fma(fma(y, 0.13, 1.25), dy, -fma(x, x, -h)), pl));
 }
 // hardware reciprocal square root (1 ulp); pair distances are far above the FP32 denormal range
 __device__ __forceinline__ float d_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
-// FP64: the hardware's (2^-24 or better) and one step of third order
+// FP64: the hardware's (2^-24 or better) and one step of third order in the exact residual: rounded once,
+// 1.1e-16 (1.3e-16 for the quotient by the root)
 __device__ __forceinline__ double d_rsqrt(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
+    const double h = x * y, l = fma(x, y, -h);
+    const double e = fma(-l, y, fma(-h, y, 1.0));
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 __device__ __forceinline__ float d_length(float r2) { return r2 * __builtin_amdgcn_rsqf(r2); }
@@ -392,7 +406,8 @@ template <typename R> struct MultipoleKind {
         d[2].y *= f;
     }
     static constexpr int NV = 3;
-    static constexpr int kMinWaves = 1;
+    // FP64: as many as the LDS of its workgroups of four waves leaves room for (169 registers otherwise)
+    static constexpr int kMinWaves = sizeof(R) == 8 ? 3 : 1;
     __device__ static void load(const R4* src, size_t s, R a, R4* d)
     {
         d[0] = src[3 * s];
@@ -481,7 +496,11 @@ __device__ __forceinline__ void force_pair(T rx, T ry, T rz, T aij, T wij, const
     const T gauss = d_exp(-beta * beta * r2);
     const T gb = gfac * gauss;       // 2 beta / sqrt(pi) e^{-beta^2 r^2}
     const T t = (T)2 * beta * beta;
-    const T b0 = d_erfc_g(beta * r, gauss) * rinv;
+    T b0;
+    if constexpr (sizeof(T) == 8 && sizeof(R4) == 16)  // the rare branch of an FP32 tile
+        b0 = erfc_fit(beta * r) * rinv;
+    else
+        b0 = d_erfc_g(beta * r, gauss) * rinv;
     const T b1 = (b0 + gb) * rinv2;
     const T b2 = ((T)3 * b1 + t * gb) * rinv2;
     const T b3 = ((T)5 * b2 + t * t * gb) * rinv2;

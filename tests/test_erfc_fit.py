@@ -64,3 +64,48 @@ def test_fp64_erfc_and_exp2_polynomials():
     f = np.linspace(-0.5, 0.5, 100001)
     q, bound = kernel_horner([1.0] + kernel_table("kExp2Poly"), f)
     assert np.all(np.abs(q - np.exp2(f)) <= bound + 4e-16)
+
+
+def test_fp64_pair_functions_against_exact(tmp_path):
+    """2^x, 1/sqrt and the erfc of the FP32 tiles' FP64 pairs, compiled for the host from the kernel source
+    (the hardware's estimates at 24 bits), in units of 2^-53: one rounding for the first two, with a tenth for
+    what it rounds; three for erfc up to 3.8 (the Gaussian's, the product's, and what P's inner steps leave)."""
+    import ctypes
+    import subprocess
+
+    import mpmath as mp
+    mp.mp.dps = 40
+    body = open(SRC).read()
+    body = body[body.index("constexpr double kExp2Poly"):body.index("__device__ __forceinline__ float d_length")]
+    (tmp_path / "f.cpp").write_text("""
+#include <cmath>
+#define __device__
+#define __forceinline__ inline
+#define __builtin_amdgcn_rcpf(x) (1.0f / (x))
+#define __builtin_amdgcn_rsqf(x) (1.0f / sqrtf(x))
+#define __builtin_amdgcn_rsq(x) ((double)(1.0f / sqrtf((float)(x))))
+""" + body + """
+extern "C" void run(int n, const double* x, double* o)
+{
+    for (int i = 0; i < n; ++i, o += 3) {
+        o[0] = d_exp2(-x[i] * x[i]);
+        o[1] = d_rsqrt(x[i]);
+        o[2] = erfc_fit(x[i]);
+    }
+}
+""")
+    subprocess.check_call(["g++", "-O2", "-mfma", "-ffp-contract=off", "-Wno-unknown-pragmas", "-shared", "-fPIC",
+                           str(tmp_path / "f.cpp"), "-o", str(tmp_path / "f.so")])
+    x = np.concatenate([np.random.default_rng(5).uniform(0.0, 3.8, 3000), 10.0 ** -np.arange(1.0, 9.0)])
+    out = np.empty((len(x), 3))
+    run = ctypes.CDLL(str(tmp_path / "f.so")).run
+    run(len(x), ctypes.c_void_p(x.ctypes.data), ctypes.c_void_p(out.ctypes.data))
+    for v, o in zip(x, out):
+        z = mp.mpf(float(v))
+        exact = mp.mpf(2) ** mp.mpf(float(-v * v)), 1 / mp.sqrt(z), mp.erfc(z)
+        for f, units, ref in zip(o, (1.1, 1.1, 3.0), exact):
+            assert abs(mp.mpf(float(f)) / ref - 1) <= units * mp.mpf(2) ** -53, (v, units)
+    # where 2^x ends: an argument beyond any int, zero, and a denormal
+    ends = np.array([1e200, 40.0, 32.0])
+    run(3, ctypes.c_void_p(ends.ctypes.data), ctypes.c_void_p(out.ctypes.data))
+    assert list(out[:3, 0]) == [0.0, 0.0, 2.0 ** -1024]
