@@ -184,7 +184,14 @@ template <> struct LdsAcc<false> {
     __device__ static void add_raw(T* p, T v) { atomicAdd(p, v); }
     __device__ static double value(T v) { return v; }
 };
-
+// The radial sums of an FP64 context, bitwise reproducible: integers in units of 2^-51 (half an ulp of a
+// sum from 2 to 4; sums below 4096).
+struct LdsAccRadial {
+    using T = unsigned long long;
+    __device__ static void add(T* p, double v) { atomicAdd(p, (T)rint(v * 0x1p51)); }
+    __device__ static void add_raw(T* p, T q) { atomicAdd(p, q); }
+    __device__ static double value(T q) { return (double)q * 0x1p-51; }
+};
 
 // Very close pairs: B_n ~ (2n-1)!!/r^(2n+1) and its Thole term cancel to an O(1) B_n', which the
 // direct formula cannot resolve once the rounding of the two terms exceeds the result (in FP32
@@ -657,8 +664,11 @@ template <> struct Records<double> {
     }
 };
 
+template <bool FIX, class K> struct TileAcc { using A = LdsAcc<FIX>; };
+template <> struct TileAcc<false, RadialKind<double>> { using A = LdsAccRadial; };
+
 template <typename R, bool FIX, class K, int W> struct TileLds {
-    using LT = typename LdsAcc<FIX>::T;
+    using LT = typename TileAcc<FIX, K>::A::T;
     Records<R> ip;                  // i offset from the block origin, w = alpha^-1/6
     Records<R> id[K::NV];           // i source data
     Records<R> jp[W];               // j offset from the i-block origin, w = alpha^-1/6
@@ -683,7 +693,8 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
 {
     using R4 = typename V4<R>::T;
     using R2 = typename V2<R>::T;
-    using LT = typename LdsAcc<FIX>::T;
+    using A = typename TileAcc<FIX, K>::A;
+    using LT = typename A::T;
     constexpr int NV = K::NV;
     constexpr bool SJ = FIX && K::kScaledJ;  // sources held times 2^38, fields added pre-scaled
     auto& s_ip = L.ip;
@@ -811,9 +822,9 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     if constexpr (SJ)
-                        LdsAcc<FIX>::add_scaled(&s_ei[c][i], ea[c]);
+                        A::add_scaled(&s_ei[c][i], ea[c]);
                     else
-                        LdsAcc<FIX>::add(&s_ei[c][i], ea[c]);
+                        A::add(&s_ei[c][i], ea[c]);
                 }
             };
             auto visit = [&](auto&& eval) {
@@ -839,9 +850,9 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     if constexpr (SJ)
-                        LdsAcc<FIX>::add_scaled(&s_ej[w][c][k], ej[c]);
+                        A::add_scaled(&s_ej[w][c][k], ej[c]);
                     else
-                        LdsAcc<FIX>::add(&s_ej[w][c][k], ej[c]);
+                        A::add(&s_ej[w][c][k], ej[c]);
                 }
             };
             const int n = p1 - p0;
@@ -888,11 +899,11 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
             // diagonal tile: its j-atoms are the block's own atoms
 #pragma unroll
             for (int c = 0; c < 3; ++c)
-                LdsAcc<FIX>::add_raw(&s_ei[c][lane], s_ej[w][c][lane]);
+                A::add_raw(&s_ei[c][lane], s_ej[w][c][lane]);
         } else {
             reinterpret_cast<R4*>(jbuf)[(size_t)t * kBlock + lane] =
-                R4{(R)LdsAcc<FIX>::value(s_ej[w][0][lane]), (R)LdsAcc<FIX>::value(s_ej[w][1][lane]),
-                   (R)LdsAcc<FIX>::value(s_ej[w][2][lane]), (R)0};
+                R4{(R)A::value(s_ej[w][0][lane]), (R)A::value(s_ej[w][1][lane]),
+                   (R)A::value(s_ej[w][2][lane]), (R)0};
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -901,7 +912,7 @@ __device__ __forceinline__ void block_tiles(TileLds<R, FIX, K, W>& L, int I, con
     __syncthreads();
     if (tid < 3 * kBlock) {
         const int c = tid / kBlock, l = tid % kBlock;
-        eipart[3 * ((size_t)I * kBlock + l) + c] = LdsAcc<FIX>::value(s_ei[c][l]);
+        eipart[3 * ((size_t)I * kBlock + l) + c] = A::value(s_ei[c][l]);
     }
 }
 

@@ -334,3 +334,21 @@ def test_prediction_then_products_on_the_same_positions(path):
             ctx.close()
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("waters,box", [(216, 18.63), (8640, 63.7)])
+def test_radial_sums_repeat_bitwise(waters, box):
+    """FP64 contexts: the same features from every call, and from a list of its own (eight and four waves
+    to a block)."""
+    s = synth.water_box(waters, box, 48, 3, "water")
+    first = None
+    for _ in range(2):
+        ctx, t = amoeba.context_for(s, precision="fp64", device=DEV)
+        try:
+            for _ in range(10):
+                feat, _ = ctx.guess_features(t["pos"], torch.zeros_like(t["pos"]))
+                x = feat.cpu().numpy()[:, 8:11]
+                first = x if first is None else first
+                assert np.array_equal(x, first)
+        finally:
+            ctx.close()
