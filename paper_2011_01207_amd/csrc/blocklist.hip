@@ -45,11 +45,14 @@ __device__ __forceinline__ double mimg(double d, double L) { return mimg_fp64(d,
 // atom) bucket by bucket, k_sort_rank ranks each entry among its bucket's.  These and a scan, five
 // launches, take 34 us at 288,000 atoms, positions included; a merge sort took 21 launches and 135 us,
 // the order and positions after it 18 us more.
-// Non-finite positions go to a last bucket of their own, which is not ranked (the build reports
-// them); nor is a bucket of more than kRankMax atoms (65,536 atoms within a slice of box / 4096 or
-// a few: no list capacity holds their neighbours), so that no input makes the ranking slow.
+// Non-finite positions go to a last bucket of their own, which is not ranked (the build reports them).
+// A bucket may hold all atoms of a column within a few 4096ths of the box: with even matter the two
+// above, with matter in a small part of a large box many, which the index alone then orders.  The
+// ranking's time grows with the square of the largest bucket (about 4 ms for kRankMax atoms in one), so
+// larger ones, which take a box of tens of thousands of Angstrom or all atoms in one place, are left in the
+// order of arrival: a valid list where its capacity holds it, but not the same one every time.
 // Also clears the build's error flags.
-constexpr int kRankMax = 65536;
+constexpr int kRankMax = 1 << 18;
 
 __global__ void k_sort_keys(int n, const double* __restrict__ pos, double3 box, int ny, int nz, int shift,
                             int nbucket, unsigned* __restrict__ keys, int* __restrict__ arrival,

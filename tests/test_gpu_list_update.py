@@ -114,6 +114,25 @@ def test_order_of_uneven_systems(waters, cube, box, grid):
             assert_fields(again, ref, 1e-12)
 
 
+def test_order_of_one_full_slice():
+    """65,856 atoms in one slice of one column (a box 2e6 A long): their index orders them, and the list,
+    here of blocks along the rows of a lattice, holds every pair and is the same from every build."""
+    from scipy.spatial import cKDTree
+    s = synth.water_box(28 ** 3, 28 * 3.1, 32, 5, "water")
+    s = dataclasses.replace(s, box=np.array([2.0e6, 100.0, 100.0]), grid=(64, 32, 32), cutoff=4.0)
+    mu = 0.05 * torch.tensor(np.random.default_rng(3).standard_normal((s.n, 3)), device=DEV)
+    pairs = (cKDTree(s.pos).count_neighbors(cKDTree(s.pos), s.cutoff) - s.n) // 2
+    out = []
+    for _ in range(3):
+        ctx, t = amoeba.context_for(s, precision="mixed", device=DEV)
+        try:
+            assert ctx.info()["n_pairs"] == pairs
+            out.append(ctx.dipole_field_parts(t["pos"], mu)[0].cpu().numpy())
+        finally:
+            ctx.close()
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+
+
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
 def test_masks_refreshed_ahead_of_the_flags(prec):
     """Calls on the same, on changed and on refused positions in every order, and after new atom
