@@ -1,6 +1,7 @@
 // C ABI of the induced-dipole library: context, validation, and the entry points declared in
 // include/amoeba.h.  Host code here only validates, allocates and sequences kernels; every
 // step of the computation runs in the HIP kernels of this directory.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -47,10 +48,11 @@ StageTimer::~StageTimer()
         hipEventRecord(c->tev[idx + 1], st);
 }
 
+constexpr size_t kMinAlloc = 16;
+
 int ctx_alloc(amoeba_ctx* c, void** p, size_t bytes)
 {
-    if (bytes == 0)
-        bytes = 16;
+    bytes = std::max(bytes, kMinAlloc);
     // the stored pair coefficients are optional: they give way to any other allocation
     if (c->prm.max_workspace_bytes > 0 && c->ws_bytes + (int64_t)bytes > c->prm.max_workspace_bytes && c->coef)
         coef_release(c);
@@ -66,6 +68,28 @@ int ctx_alloc(amoeba_ctx* c, void** p, size_t bytes)
     c->allocs.push_back(q);
     c->ws_bytes += (int64_t)bytes;
     *p = q;
+    return AMOEBA_OK;
+}
+
+int ctx_alloc_all(amoeba_ctx* c, std::initializer_list<AllocReq> reqs)
+{
+    const size_t n0 = c->allocs.size();
+    int64_t held = 0;
+    for (const AllocReq& r : reqs) {
+        void* p = nullptr;
+        const int rc = ctx_alloc(c, &p, r.bytes);
+        if (rc != AMOEBA_OK) {
+            for (size_t k = n0; k < c->allocs.size(); ++k)
+                hipFree(c->allocs[k]);
+            c->allocs.resize(n0);
+            c->ws_bytes -= held;
+            return rc;
+        }
+        held += (int64_t)std::max(r.bytes, kMinAlloc);
+    }
+    size_t k = n0;
+    for (const AllocReq& r : reqs)
+        *r.p = c->allocs[k++];
     return AMOEBA_OK;
 }
 
@@ -166,6 +190,16 @@ __global__ void k_gather_mpole(int npad, const int* __restrict__ perm, const dou
 }
 
 static inline int nblk(size_t n, int b) { return (int)((n + b - 1) / b); }
+
+// the multipole records, allocated by the first call that takes multipoles
+int multipole_records(amoeba_ctx* c)
+{
+    if (c->mp_d)
+        return AMOEBA_OK;
+    const size_t np3 = 3 * (size_t)c->npad;
+    return c->mixed ? ctx_alloc_all(c, {{&c->mp_d, sizeof(double4) * np3}, {&c->mp_f, sizeof(float4) * np3}})
+                    : ctx_alloc(c, (void**)&c->mp_d, sizeof(double4) * np3);
+}
 
 // multipoles of the caller into mp_d (and mp_f)
 void launch_gather_mpole(amoeba_ctx* c, const double* q, const double* dip, const double* quad, int* flags)
@@ -459,10 +493,10 @@ int amoeba_set_atoms(amoeba_ctx* c, const double* alpha, const double* thole, co
     int rc;
     if (n_scaled > c->n_scaled || !c->sc_j_in) {
         size_t cap = (size_t)std::max<int64_t>(n_scaled, 1);
-        if ((rc = ctx_alloc(c, (void**)&c->sc_j_in, sizeof(int) * cap)) ||
-            (rc = ctx_alloc(c, (void**)&c->sc_s_in, sizeof(double) * cap)) ||
-            (rc = ctx_alloc(c, (void**)&c->sc_j, sizeof(int) * cap)) ||
-            (rc = ctx_alloc(c, (void**)&c->sc_s, sizeof(double) * cap)))
+        if ((rc = ctx_alloc_all(c, {{&c->sc_j_in, sizeof(int) * cap},
+                                    {&c->sc_s_in, sizeof(double) * cap},
+                                    {&c->sc_j, sizeof(int) * cap},
+                                    {&c->sc_s, sizeof(double) * cap}})))
             return rc;
     }
     hipMemsetAsync(c->flags, 0, sizeof(int), st);
@@ -544,12 +578,8 @@ static int perm_field_parts(amoeba_ctx* c, const double* pos, const double* q, c
     int rc = flags ? AMOEBA_OK : begin_config(c, pos, what);
     if (rc)
         return rc;
-    if (!c->mp_d) {
-        if ((rc = ctx_alloc(c, (void**)&c->mp_d, sizeof(double4) * 3 * c->npad)))
-            return rc;
-        if (c->mixed && (rc = ctx_alloc(c, (void**)&c->mp_f, sizeof(float4) * 3 * c->npad)))
-            return rc;
-    }
+    if ((rc = multipole_records(c)))
+        return rc;
     // The multipole checks (finite, traceless) and the range check of the result are flags
     // written on the device and read once at the end; on an error the fields are unspecified.
     hipStream_t st = c->stream;
@@ -636,8 +666,8 @@ int amoeba_set_direct_scales(amoeba_ctx* c, const double* sc_s_d, int64_t n_scal
     hipStream_t st = c->stream;
     int rc;
     if (n_scaled > c->sc_sd_cap) {
-        if ((rc = ctx_alloc(c, (void**)&c->sc_sd_in, sizeof(double) * n_scaled)) ||
-            (rc = ctx_alloc(c, (void**)&c->sc_sd, sizeof(double) * n_scaled)))
+        if ((rc = ctx_alloc_all(c, {{&c->sc_sd_in, sizeof(double) * (size_t)n_scaled},
+                                    {&c->sc_sd, sizeof(double) * (size_t)n_scaled}})))
             return rc;
         c->sc_sd_cap = n_scaled;
     }

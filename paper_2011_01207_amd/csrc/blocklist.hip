@@ -1306,16 +1306,6 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
 
     int rc = AMOEBA_OK;
     if (!c->b_keys) {
-        if ((rc = ctx_alloc(c, (void**)&c->b_keys, sizeof(unsigned) * n)) ||
-            (rc = ctx_alloc(c, (void**)&c->b_entry, sizeof(unsigned long long) * n)) ||
-            (rc = ctx_alloc(c, (void**)&c->b_cell_blk, sizeof(int) * nb)) ||
-            (rc = ctx_alloc(c, (void**)&c->b_bc, sizeof(double4) * nb)) ||
-            (rc = ctx_alloc(c, (void**)&c->b_bh, sizeof(double4) * nb)) ||
-            (rc = ctx_alloc(c, (void**)&c->b_rowc, sizeof(int) * nb)) ||
-            (rc = ctx_alloc(c, (void**)&c->b_rowj, sizeof(int) * (size_t)nb * kMaxFiltered)) ||
-            (rc = ctx_alloc(c, (void**)&c->b_tpb, sizeof(int) * (nb + 1))) ||
-            (rc = ctx_alloc(c, (void**)&c->rev_cnt, sizeof(int) * (npad + 1))))
-            return rc;
         // block grid: at most floor(L / rcb) cells per axis (the cell width is at least rcb),
         // and not many more cells than blocks (nor than the grid kernel has counters)
         const double rcb = c->prm.cutoff + c->prm.buffer;
@@ -1329,7 +1319,16 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
             --*big;
         }
         c->b_ncell_cap = (int)ncells();
-        if ((rc = ctx_alloc(c, (void**)&c->b_cell_start, sizeof(int) * ((size_t)c->b_ncell_cap + 1))))
+        if ((rc = ctx_alloc_all(c, {{&c->b_keys, sizeof(unsigned) * n},
+                                    {&c->b_entry, sizeof(unsigned long long) * n},
+                                    {&c->b_cell_blk, sizeof(int) * nb},
+                                    {&c->b_bc, sizeof(double4) * nb},
+                                    {&c->b_bh, sizeof(double4) * nb},
+                                    {&c->b_rowc, sizeof(int) * nb},
+                                    {&c->b_rowj, sizeof(int) * (size_t)nb * kMaxFiltered},
+                                    {&c->b_tpb, sizeof(int) * (nb + 1)},
+                                    {&c->rev_cnt, sizeof(int) * (npad + 1)},
+                                    {&c->b_cell_start, sizeof(int) * ((size_t)c->b_ncell_cap + 1)}})))
             return rc;
     }
     double4 *bc = c->b_bc, *bh = c->b_bh;
@@ -1414,18 +1413,19 @@ static int build_tiles(amoeba_ctx* c, const double* pos)
         // grow the tile arrays (earlier, smaller ones stay allocated until destroy)
         size_t tb = (size_t)total * kBlock;
         size_t rs = c->mixed ? sizeof(float) : sizeof(double);
-        if ((rc = ctx_alloc(c, (void**)&c->tile_blk, sizeof(int) * total)) ||
-            (rc = ctx_alloc(c, (void**)&c->tile_j, sizeof(int) * tb)) ||
-            (rc = ctx_alloc(c, (void**)&c->tile_mask, sizeof(unsigned long long) * tb)) ||
-            (rc = ctx_alloc(c, (void**)&c->tile_np, sizeof(int) * total)) ||
-            (rc = ctx_alloc(c, (void**)&c->tile_walk, sizeof(uint16_t) * tb)) ||
-            (rc = ctx_alloc(c, (void**)&c->tile_rows, sizeof(int) * total)) ||
-            (rc = ctx_alloc(c, (void**)&c->coef_row0, sizeof(int) * (total + 1))) ||
-            (c->mixed && (rc = ctx_alloc(c, (void**)&c->jrel_f, sizeof(float4) * tb))) ||
-            (!c->mixed && (rc = ctx_alloc(c, (void**)&c->jrel_d, sizeof(double4) * tb))) ||
-            (rc = ctx_alloc(c, &c->jbuf, rs * 4 * tb)) ||
-            (rc = ctx_alloc(c, (void**)&c->rev_idx, sizeof(int) * tb)) ||
-            (rc = ctx_alloc(c, (void**)&c->pair_part, sizeof(unsigned long long) * ((size_t)total / 4 + 1))))
+        // the j records of the context's precision
+        const AllocReq jrel = c->mixed ? AllocReq(&c->jrel_f, sizeof(float4) * tb) : AllocReq(&c->jrel_d, sizeof(double4) * tb);
+        if ((rc = ctx_alloc_all(c, {{&c->tile_blk, sizeof(int) * total},
+                                    {&c->tile_j, sizeof(int) * tb},
+                                    {&c->tile_mask, sizeof(unsigned long long) * tb},
+                                    {&c->tile_np, sizeof(int) * total},
+                                    {&c->tile_walk, sizeof(uint16_t) * tb},
+                                    {&c->tile_rows, sizeof(int) * total},
+                                    {&c->coef_row0, sizeof(int) * (total + 1)},
+                                    jrel,
+                                    {&c->jbuf, rs * 4 * tb},
+                                    {&c->rev_idx, sizeof(int) * tb},
+                                    {&c->pair_part, sizeof(unsigned long long) * ((size_t)total / 4 + 1)}})))
             return fail(rc);
         c->tile_cap = total;
         c->rev_cap = (int64_t)tb;

@@ -6,6 +6,7 @@
 #include <rocfft/rocfft.h>
 
 #include <cstdint>
+#include <initializer_list>
 #include <memory>
 #include <string>
 #include <vector>
@@ -358,6 +359,14 @@ namespace amoeba {
 
 // allocation helpers (api.hip)
 int ctx_alloc(amoeba_ctx* c, void** p, size_t bytes);
+// several arrays, all or none: on an error every pointer keeps what it held, so that a later call does not
+// take a half-made set for a whole one
+struct AllocReq {
+    void** p;
+    size_t bytes;
+    template <typename T> AllocReq(T** ptr, size_t n) : p((void**)ptr), bytes(n) {}
+};
+int ctx_alloc_all(amoeba_ctx* c, std::initializer_list<AllocReq> reqs);
 int set_error(amoeba_ctx* c, int code, const std::string& msg);
 int hip_check(amoeba_ctx* c, hipError_t e, const char* what);
 
@@ -433,6 +442,7 @@ int polar_gradient(amoeba_ctx* c, const double* q, const double* dip, const doub
 int read_flags(amoeba_ctx* c, int* out);
 int check_vec_finite(amoeba_ctx* c, const double* v, size_t n, const char* what);
 void launch_check_overflow(amoeba_ctx* c, const double* v_slot);  // |v| < kFixRange, flag on the device
+int multipole_records(amoeba_ctx* c);
 void launch_gather_mpole(amoeba_ctx* c, const double* q, const double* dip, const double* quad, int* flags);
 int post_flags(amoeba_ctx* c);  // enqueue the flags' way to the host
 int wait_flags(amoeba_ctx* c, int seq, int* f, const char* who);

@@ -407,12 +407,8 @@ int polar_gradient(amoeba_ctx* c, const double* q, const double* dip, const doub
                    double* grad_out)
 {
     int rc;
-    if (!c->mp_d) {
-        if ((rc = ctx_alloc(c, (void**)&c->mp_d, sizeof(double4) * 3 * c->npad)))
-            return rc;
-        if (c->mixed && (rc = ctx_alloc(c, (void**)&c->mp_f, sizeof(float4) * 3 * c->npad)))
-            return rc;
-    }
+    if ((rc = multipole_records(c)))
+        return rc;
     if (!c->f_src &&
         (rc = ctx_alloc(c, &c->f_src, 4 * 4 * (c->mixed ? sizeof(float) : sizeof(double)) * (size_t)c->npad)))
         return rc;

@@ -835,15 +835,12 @@ static int guess_alloc_config(amoeba_ctx* c)
     if (c->g_v)
         return AMOEBA_OK;
     const size_t n3 = 3 * (size_t)c->npad;
-    int rc;
-    if ((rc = ctx_alloc(c, (void**)&c->g_v, sizeof(double) * 3 * n3)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_radial, sizeof(double) * n3)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_feat, sizeof(float) * kNF * (size_t)c->npad)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_basis, sizeof(float) * kNB * 3 * (size_t)c->npad)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_save_mu, sizeof(double) * n3)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_save_q, sizeof(double) * n3)))
-        return rc;
-    return AMOEBA_OK;
+    return ctx_alloc_all(c, {{&c->g_v, sizeof(double) * 3 * n3},
+                             {&c->g_radial, sizeof(double) * n3},
+                             {&c->g_feat, sizeof(float) * kNF * (size_t)c->npad},
+                             {&c->g_basis, sizeof(float) * kNB * 3 * (size_t)c->npad},
+                             {&c->g_save_mu, sizeof(double) * n3},
+                             {&c->g_save_q, sizeof(double) * n3}});
 }
 
 static GuessOffsets guess_offsets(const amoeba_ctx* c)
@@ -914,21 +911,18 @@ static int guess_alloc_model(amoeba_ctx* c)
 {
     if (c->g_model)
         return AMOEBA_OK;
-    int rc;
-    if ((rc = ctx_alloc(c, (void**)&c->g_model, sizeof(float) * kNM)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_adam_m, sizeof(float) * kNP)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_adam_v, sizeof(float) * kNP)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_part, sizeof(float) * kNP * (size_t)kGuessWG)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_lossp, sizeof(double) * kGuessWG)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_scal, sizeof(double) * 4)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_npart, sizeof(double) * kNF * kRedBlocks)) ||
-        (rc = ctx_alloc(c, (void**)&c->g_nmean, sizeof(double) * kNF)))
-        return rc;
-    if (hipHostMalloc((void**)&c->g_scal_host, sizeof(double) * 4, hipHostMallocDefault) != hipSuccess) {
+    if (!c->g_scal_host && hipHostMalloc((void**)&c->g_scal_host, sizeof(double) * 4, hipHostMallocDefault) != hipSuccess) {
         c->g_scal_host = nullptr;
         return set_error(c, AMOEBA_E_NOMEM, "pinned host allocation failed");
     }
-    return AMOEBA_OK;
+    return ctx_alloc_all(c, {{&c->g_model, sizeof(float) * kNM},
+                             {&c->g_adam_m, sizeof(float) * kNP},
+                             {&c->g_adam_v, sizeof(float) * kNP},
+                             {&c->g_part, sizeof(float) * kNP * (size_t)kGuessWG},
+                             {&c->g_lossp, sizeof(double) * kGuessWG},
+                             {&c->g_scal, sizeof(double) * 4},
+                             {&c->g_npart, sizeof(double) * kNF * kRedBlocks},
+                             {&c->g_nmean, sizeof(double) * kNF}});
 }
 
 // end of a features / predict call: the flag word (cleared by the e_perm check) reports a

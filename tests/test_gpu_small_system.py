@@ -71,3 +71,56 @@ def test_small_solve_without_a_product_and_at_its_limits(prec):
         ctx.close()
     ref, _, _ = O.pcg(s, e.cpu().numpy(), "spme", tol_debye=1e-9)
     assert O.rms_debye(mu.cpu().numpy() - ref) < 1e-6 * (1 if prec == "fp64" else 3)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_calls_out_of_workspace_leave_the_context_whole(prec):
+    """Caps that end between any two of a call's buffers: each call either gives the uncapped context's
+    result or refuses, a second time too, with no part of a set of buffers left to be taken for a whole one."""
+    s = synth.water648()
+    print(f"[gpu] workspace caps {prec}", flush=True)
+    mu = torch.tensor(0.05 * np.random.default_rng(3).standard_normal((s.n, 3)), device=DEV)
+
+    def calls(ctx):
+        t = {k: torch.tensor(getattr(s, k), device=DEV) for k in ("pos", "q", "dip", "quad", "alpha", "thole", "sc_s")}
+        csr = [torch.tensor(a, dtype=torch.int32, device=DEV) for a in (s.sc_ptr, s.sc_j)]
+        return [lambda: ctx.set_atoms(t["alpha"], t["thole"], *csr, t["sc_s"]),
+                lambda: ctx.build_blocklist(t["pos"]),
+                lambda: ctx.perm_field(t["pos"], t["q"], t["dip"], t["quad"]),
+                lambda: ctx.polarization_gradient(t["pos"], t["q"], t["dip"], t["quad"], mu),
+                lambda: ctx.guess_set_model(synth.guess_init_model()),
+                lambda: ctx.guess_predict(t["pos"], mu)]
+
+    def make(cap=0):
+        return amoeba.Context(s.n, s.box, cutoff=s.cutoff, ewald_alpha=s.ewald_alpha, grid=s.grid, precision=prec,
+                              max_workspace_bytes=cap)
+
+    ctx = make()
+    held, want = [ctx.info()["workspace_bytes"]], []
+    for f in calls(ctx):
+        r = f()
+        want.append(r.cpu().numpy() if isinstance(r, torch.Tensor) else None)
+        held.append(ctx.info()["workspace_bytes"])
+    ctx.close()
+    refused = 0
+    caps = np.concatenate([np.linspace(a, b, 12, endpoint=False) for a, b in zip(held[:-1], held[1:]) if b > a])
+    for cap in caps.astype(np.int64):
+        ctx = make(int(cap))
+        try:
+            for f, ref in zip(calls(ctx), want):
+                left = None   # what a refused call leaves allocated, the same after a second one
+                for _ in range(2):
+                    try:
+                        r = f()
+                    except amoeba.AmoebaError as e:
+                        assert e.status in (amoeba.AMOEBA_E_NOMEM, amoeba.AMOEBA_E_LIST, amoeba.AMOEBA_E_STATE), e
+                        now = ctx.info()["workspace_bytes"]
+                        assert now <= cap and left in (None, now)
+                        left = now
+                        refused += e.status == amoeba.AMOEBA_E_NOMEM
+                    else:
+                        if ref is not None:
+                            assert_fields(r.cpu().numpy(), ref, 1e-11 if prec == "fp64" else 2e-5)
+        finally:
+            ctx.close()
+    assert refused > len(caps)
