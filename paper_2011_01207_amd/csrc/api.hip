@@ -491,17 +491,9 @@ int amoeba_set_atoms(amoeba_ctx* c, const double* alpha, const double* thole, co
         return set_error(c, AMOEBA_E_INVALID, "amoeba_set_atoms: NULL sc_j or sc_s with n_scaled > 0");
     hipStream_t st = c->stream;
     int rc;
-    if (n_scaled > c->n_scaled || !c->sc_j_in) {
-        size_t cap = (size_t)std::max<int64_t>(n_scaled, 1);
-        if ((rc = ctx_alloc_all(c, {{&c->sc_j_in, sizeof(int) * cap},
-                                    {&c->sc_s_in, sizeof(double) * cap},
-                                    {&c->sc_j, sizeof(int) * cap},
-                                    {&c->sc_s, sizeof(double) * cap}})))
-            return rc;
-    }
     hipMemsetAsync(c->flags, 0, sizeof(int), st);
     hipLaunchKernelGGL(k_validate_atoms, dim3(nblk(c->n + 1, 256)), dim3(256), 0, st, c->n, alpha, thole, sc_ptr,
-                       n_scaled ? sc_j : c->sc_j_in, n_scaled ? sc_s : c->sc_s_in, (long long)n_scaled, c->flags);
+                       sc_j, sc_s, (long long)n_scaled, c->flags);
     int f = 0;
     if ((rc = read_flags(c, &f)))
         return rc;
@@ -514,6 +506,14 @@ int amoeba_set_atoms(amoeba_ctx* c, const double* alpha, const double* thole, co
                          "amoeba_set_atoms: scaled-pair CSR invalid (ptr not monotone from 0 to n_scaled, "
                          "partner out of range or equal to the atom, non-finite scale, or a pair not listed "
                          "in both directions with the same scale)");
+    if (n_scaled > c->n_scaled || !c->sc_j_in) {
+        size_t cap = (size_t)std::max<int64_t>(n_scaled, 1);
+        if ((rc = ctx_alloc_all(c, {{&c->sc_j_in, sizeof(int) * cap},
+                                    {&c->sc_s_in, sizeof(double) * cap},
+                                    {&c->sc_j, sizeof(int) * cap},
+                                    {&c->sc_s, sizeof(double) * cap}})))
+            return rc;
+    }
     hipMemcpyAsync(c->alpha_in, alpha, sizeof(double) * c->n, hipMemcpyDeviceToDevice, st);
     hipMemcpyAsync(c->thole_in, thole, sizeof(double) * c->n, hipMemcpyDeviceToDevice, st);
     hipMemcpyAsync(c->sc_ptr_in, sc_ptr, sizeof(int) * (c->n + 1), hipMemcpyDeviceToDevice, st);

@@ -124,3 +124,24 @@ def test_calls_out_of_workspace_leave_the_context_whole(prec):
         finally:
             ctx.close()
     assert refused > len(caps)
+
+
+def test_refused_atoms_leave_the_old_ones():
+    """A longer pair list that is refused changes nothing of the one in use."""
+    s = synth.water648()
+    ctx, t = amoeba.context_for(s, precision="mixed", device=DEV)
+    try:
+        e = ctx.perm_field(t["pos"], t["q"], t["dip"], t["quad"])
+        ptr = t["sc_ptr"].clone()
+        ptr[-1] += 2
+        sj = torch.cat([t["sc_j"], torch.full((2,), s.n, dtype=torch.int32, device=DEV)])
+        with pytest.raises(amoeba.AmoebaError) as ei:
+            ctx.set_atoms(t["alpha"], t["thole"], ptr, sj, torch.cat([t["sc_s"], t["sc_s"][:2]]))
+        assert ei.value.status == amoeba.AMOEBA_E_INVALID
+        assert torch.equal(ctx.perm_field(t["pos"], t["q"], t["dip"], t["quad"]), e)
+        moved = t["pos"] + 0.01
+        ctx.build_blocklist(moved)
+        ctx.build_blocklist(t["pos"])
+        assert torch.equal(ctx.perm_field(t["pos"], t["q"], t["dip"], t["quad"]), e)
+    finally:
+        ctx.close()
