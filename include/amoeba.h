@@ -31,7 +31,9 @@
  *    (1 e*A = 4.80320 D).
  *  - All work is enqueued on the HIP stream given to amoeba_create; every call
  *    returns after its outputs are complete.  A context is not thread-safe: use
- *    one context per host thread.
+ *    one context per host thread.  A call that waits for the device watches host
+ *    memory for up to 5 ms (its thread busy), then the stream, by the device's
+ *    schedule flags.
  *  - Errors: every call returns an amoeba_status; negative values are errors
  *    with a message in amoeba_last_error().  Host-side argument checks run
  *    before any work is queued; checks that need the data (NaN/Inf, traceless

@@ -25,6 +25,7 @@
 //      bitmasks (bit k of row i: |r_i - r_jk| < rc) and the j positions relative to the
 //      i-block origin, computed in FP64.
 #include <algorithm>
+#include <chrono>
 #include <climits>
 #include <cmath>
 
@@ -1472,16 +1473,23 @@ int post_flags(amoeba_ctx* c)
     return c->post_seq;
 }
 
+// The host watches the word for kWatch at most (every wait of a call on an idle stream is shorter), then
+// waits for the stream as the device's schedule flags say: behind a long queue it does not hold a core.
+constexpr std::chrono::milliseconds kWatch(5);
+
 int wait_flags(amoeba_ctx* c, int seq, int* f, const char* who)
 {
     int rc = AMOEBA_OK;
+    const auto t0 = std::chrono::steady_clock::now();
     for (unsigned spin = 1; __atomic_load_n(&c->post_host[0], __ATOMIC_ACQUIRE) != seq; ++spin) {
         if (spin % 4096)
             continue;
         // the stream ended or failed: its own word on it
         if (hipStreamQuery(c->stream) == hipErrorNotReady) {
-            (void)hipGetLastError();  // not an error to leave behind
-            continue;
+            if (hipPeekAtLastError() == hipErrorNotReady)
+                (void)hipGetLastError();  // not an error to leave behind
+            if (std::chrono::steady_clock::now() - t0 < kWatch)
+                continue;
         }
         if ((rc = hip_check(c, hipStreamSynchronize(c->stream), who)))
             return rc;

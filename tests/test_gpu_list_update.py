@@ -242,3 +242,27 @@ def test_pairs_of_dilute_blocks(spread, edge, prec, along):
         assert ctx.info()["n_pairs"] == 32
     finally:
         ctx.close()
+
+
+def test_checks_behind_a_long_queue():
+    """Calls behind half a second of other work on their stream, far beyond the time the host watches for the
+    flags: the same checks and results."""
+    s = synth.water648()
+    ctx, t = amoeba.context_for(s, precision="mixed", device=DEV)
+    try:
+        e = ctx.perm_field(t["pos"], t["q"], t["dip"], t["quad"])
+        start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        for cycles in (10 ** 6, 10 ** 7):   # the first also loads the kernel
+            start.record()
+            torch.cuda._sleep(cycles)
+            end.record()
+            torch.cuda.synchronize()
+        cycles = int(10 ** 7 * 500.0 / start.elapsed_time(end))
+        torch.cuda._sleep(cycles)
+        with pytest.raises(amoeba.AmoebaError) as ei:
+            ctx.set_atoms(-t["alpha"], t["thole"], t["sc_ptr"], t["sc_j"], t["sc_s"])
+        assert ei.value.status == amoeba.AMOEBA_E_INVALID
+        torch.cuda._sleep(cycles)
+        assert torch.equal(ctx.perm_field(t["pos"], t["q"], t["dip"], t["quad"]), e)
+    finally:
+        ctx.close()
