@@ -114,3 +114,23 @@ def test_gradient_under_a_workspace_cap_takes_the_brick_path(prec):
         finally:
             ctx.close()
     assert_fields(out[1], out[0], BAR[prec], what="capped vs uncapped")
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_gradient_under_a_workspace_cap_allocates_the_brick_buffers_alone(prec):
+    """The cap of the test above: what the call allocates says which path it took."""
+    s = synth.water648()
+    mu = torch.zeros((s.n, 3), dtype=torch.float64, device=DEV)
+    npad, grid = (s.n + 63) // 64 * 64, 24 ** 3
+    bricks = (96 + 128) * npad + 8 * grid if prec == "fp64" else (96 + 48 + 64) * npad + 4 * grid
+    grown, held = [], 0
+    for room in (None, bricks + 64, None):
+        kw = {"max_workspace_bytes": held + room} if room else {}
+        ctx, t = amoeba.context_for(s, precision=prec, device=DEV, **kw)
+        try:
+            held = ctx.info()["workspace_bytes"]
+            ctx.polarization_gradient(t["pos"], t["q"], t["dip"], t["quad"], mu)
+            grown.append(ctx.info()["workspace_bytes"] - held)
+        finally:
+            ctx.close()
+    assert grown[1] == bricks and grown[0] == grown[2] > bricks + 64
