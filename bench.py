@@ -500,9 +500,11 @@ def roofline(s, res):
     dom = max(["real", "spread", "gather", "fft"], key=lambda k: stages[k]["ms_total"])
     d = stages[dom]
     from paper_2011_01207_amd import profiling
-    # the profiles' name of the tile kernel ends with its waves per block (eight in a small system)
-    profiled = d["kernel"][:-1] + (", 4>" if n > 25600 else ", 8>") if dom == "real" else d["kernel"]
-    traffic = profiling.traffic_lookup(os.path.join(ROOT, "profiles", f"hbm_traffic_{s.name}_mixed.md"), profiled)
+    # the profiles' name of the tile kernel ends with its waves per block (eight in a small system); a
+    # system's profile has its own variant only
+    names = [d["kernel"][:-1] + w for w in (", 4>", ", 8>")] if dom == "real" else [d["kernel"]]
+    md = os.path.join(ROOT, "profiles", f"hbm_traffic_{s.name}_mixed.md")
+    traffic = next((t for t in (profiling.traffic_lookup(md, k) for k in names) if t is not None), None)
     avg_us = 1e3 * d["ms_total"] / max(1, d["launches"])
     top = {"bound": d["bound"], "achieved": d["achieved"], "peak": d["peak"], "unit": d["unit"],
            "frac": d["frac"], "traffic": traffic, "kernel": d["kernel"], "stage": dom,

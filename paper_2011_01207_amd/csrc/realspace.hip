@@ -954,14 +954,23 @@ __global__ void k_real_reduce(int npad, const double* __restrict__ eipart, const
 
 // Waves per block: four where the blocks fill the chip (a block's tiles share its staged i data and
 // one row of accumulators), eight for a small system, whose blocks leave the chip idle and whose
-// time is the longest wave's.
-template <typename F> static void with_waves(const amoeba_ctx* c, F&& f)
+// time is the longest wave's.  From `few` blocks on.  The limit is that of the small system's
+// iteration (small_blocks); the other tiles do not lose by it: multipoles in mixed precision, eight
+// waves against four, 15.4 / 17.2 us at 11 blocks, 15.6 / 21.7 at 47, 18.6 / 22.8 at 192, 24.4 / 25.3 at
+// 375; gradient 22.7 / 23.2, 22.0 / 29.6, 23.9 / 29.5, 33.1 / 33.9; radial sums 11.4 / 12.1, 11.5 / 14.8,
+// 12.4 / 15.0, 16.1 / 16.8; FP64 multipoles 28.8 / 32.4 at 47 blocks, 32.0 / 32.9 at 192.
+template <typename F> static void with_waves(const amoeba_ctx* c, F&& f, int few = 0)
 {
-    if (c->nb <= small_blocks(c))
+    if (c->nb >= few && c->nb <= small_blocks(c))
         f(std::integral_constant<int, kSmallWaves>{});
     else
         f(std::integral_constant<int, kWavesPerWG>{});
 }
+// FP64 tiles that evaluate their pairs are bound by their SIMD's FP64 rate: the few tiles of a block
+// among few blocks take longer as two waves to a SIMD than in turn (multipoles, eight waves against
+// four, 30.2 / 24.5 us at 11 blocks, 28.3 / 26.2 at 24, 27.5 / 26.2 at 35; gradient 38.6 / 32.0, 35.8 /
+// 34.5, 35.8 / 34.2; radial sums 19.7 / 16.8, then level).
+static int few_blocks(const amoeba_ctx* c) { return c->mixed ? 0 : 40; }
 
 template <typename R, bool FIX, bool MI, int CM, int W>
 static void dipole_tiles(amoeba_ctx* c, bool use_done, hipStream_t st, const typename V4<R>::T* jrel,
@@ -1148,7 +1157,7 @@ void launch_force_tiles(amoeba_ctx* c, const void* src, double* out, hipStream_t
                 force_tiles<false, W>(c, src, st);
             else
                 force_tiles<true, W>(c, src, st);
-        });
+        }, few_blocks(c));
         launch_real_reduce(c, out, st);
     } else {
         hipMemsetAsync(out, 0, sizeof(double) * 3 * (size_t)c->npad, st);
@@ -1187,7 +1196,7 @@ void launch_radial_sums(amoeba_ctx* c, double* out)
                 radial_tiles<false, W>(c);
             else
                 radial_tiles<true, W>(c);
-        });
+        }, few_blocks(c));
     }
     launch_real_reduce(c, out);
 }
@@ -1204,7 +1213,7 @@ void launch_perm_tiles(amoeba_ctx* c, hipStream_t st)
             perm_tiles<false, W>(c, st);
         else
             perm_tiles<true, W>(c, st);
-    });
+    }, few_blocks(c));
     launch_real_reduce(c, c->ereal, st);
 }
 

@@ -145,3 +145,19 @@ def test_refused_atoms_leave_the_old_ones():
         assert torch.equal(ctx.perm_field(t["pos"], t["q"], t["dip"], t["quad"]), e)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("waters", [832, 853])
+def test_fp64_tiles_on_both_sides_of_few_blocks(waters):
+    """FP64 permanent field and gradient of 39 and 40 blocks (four and eight waves to a block)."""
+    s = system(waters, 18.63 * (waters / 216) ** (1 / 3), (32, 32, 32))
+    print(f"[gpu] FP64 tiles N={s.n}", flush=True)
+    mu = 0.05 * np.random.default_rng(3).standard_normal((s.n, 3))
+    ctx, t = amoeba.context_for(s, precision="fp64", device=DEV)
+    try:
+        e = ctx.perm_field(t["pos"], t["q"], t["dip"], t["quad"])
+        g = ctx.polarization_gradient(t["pos"], t["q"], t["dip"], t["quad"], torch.tensor(mu, device=DEV))
+    finally:
+        ctx.close()
+    assert_fields(e.cpu().numpy(), O.perm_field(s, "spme"), 1e-11)
+    assert_fields(g.cpu().numpy(), O.polar_gradient(s, mu, "spme"), 1e-10)
