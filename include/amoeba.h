@@ -84,8 +84,8 @@ typedef enum amoeba_pme_path {
     AMOEBA_PME_AUTO = 0,    /* planes when the grid fits, else bricks                          */
     AMOEBA_PME_PLANES = 1,  /* x-planes held in LDS: spread and y-z FFT fused, x-line FFT with
                                the influence function, inverse y-z FFT and interpolation fused;
-                               needs every K a product of 2, 3, 5, 7 and a plane of
-                               ceil(K1/2) x 2(K2/2+1) complex FP64 values within 150 KB       */
+                               needs every K a product of 2, 3, 5, 7, K0 K1 <= 65536, and
+                               rows and columns that fit a workgroup (every K <= 1000 does)   */
     AMOEBA_PME_BRICKS = 2   /* 8^3-point brick spread and gather around rocFFT r2c / c2r      */
 } amoeba_pme_path;
 

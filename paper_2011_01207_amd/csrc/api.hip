@@ -1026,7 +1026,8 @@ int amoeba_set_pme_path(amoeba_ctx* c, int32_t path)
         return set_error(c, AMOEBA_E_INVALID, "amoeba_set_pme_path: unknown path");
     if (path == AMOEBA_PME_PLANES && !c->plane_ok)
         return set_error(c, AMOEBA_E_INVALID, "amoeba_set_pme_path: the PME grid does not fit the plane path "
-                                              "(K not a product of 2, 3, 5, 7, or the plane exceeds 150 KB)");
+                                              "(K not a product of 2, 3, 5, 7, K0 K1 above 65536, or rows or "
+                                              "columns beyond a workgroup)");
     c->pme_path = path;
     return AMOEBA_OK;
 }

@@ -391,7 +391,7 @@ int prepare_config(amoeba_ctx* c, const double* pos);
 void launch_mutual_tiles(amoeba_ctx* c, bool use_done, hipStream_t st = nullptr);  // null: context stream
 void iteration_graph_release(amoeba_ctx* c);  // drop the captured PCG iteration
 void coef_invalidate(amoeba_ctx* c);      // pair coefficients must be recorded again
-int coef_reserve(amoeba_ctx* c);          // size the coefficient store (host has synchronized)
+int coef_reserve(amoeba_ctx* c);          // size the coefficient store (the rows' total has been posted)
 void coef_release(amoeba_ctx* c);         // free it (other allocations come first under the cap)
 bool coef_store_on(const amoeba_ctx* c);  // the requested mode uses the store
 int begin_coef_mode(amoeba_ctx* c, bool* use_done);  // the mode of the product being enqueued

@@ -20,8 +20,8 @@
 // outside the plane path (or the brick path asked for, or no room for the planes' workspace) uses
 // the brick spread, rocFFT and a thread per atom over its 125 points.  At 288,000 atoms (mixed, two
 // configurations) a gradient with its mask refresh took 3.26 ms on the brick path (the per-atom
-// interpolation 0.65 ms of a call, the brick bins and spreads 0.27, rocFFT 0.2) and takes 1.19 ms on
-// the planes; 23,559 atoms in FP64 0.82 and 0.42 ms.
+// interpolation 0.65 ms of a call, the brick bins and spreads 0.27, rocFFT 0.2) and takes 1.13 ms on
+// the planes; 23,559 atoms in FP64 0.84 and 0.40 ms.
 #include <algorithm>
 
 #include "common.h"

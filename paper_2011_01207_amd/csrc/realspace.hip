@@ -2,8 +2,8 @@
 // interaction, "List filtering" group-atom tiles, and the real-space scheme; the scaled pairs
 // are corrected in a separate pass as in the paper's final real-space scheme).
 //
-// One workgroup (4 waves) per 64-atom i-block; the waves take the block's tiles in turn.  The
-// block's i-atoms are staged in LDS once; each wave stages its tile's 64 j-atoms (positions
+// One workgroup (four waves, eight in a small system) per 64-atom i-block; the waves share the block's
+// tiles.  The block's i-atoms are staged in LDS once; each wave stages its tile's 64 j-atoms (positions
 // relative to the i-block origin, dipoles or multipoles, damping parameters) and the tile's
 // in-cutoff bitmasks.  An exclusive wave scan of the row popcounts numbers the in-cutoff pairs,
 // and every lane evaluates an equal contiguous share of them by walking the set bits of the
@@ -166,8 +166,8 @@ constexpr int kTileCost = 256;  // per-tile cost of staging and scanning, in uni
 // or read the stored ones back.
 enum CoefMode { kCoefCompute = 0, kCoefRecord = 1, kCoefReplay = 2 };
 
-// LDS field accumulators: the block's i-field (all tiles of the block, added to by the four
-// waves on row changes) and each tile's j-field (added to per pair by the wave that walks the
+// LDS field accumulators: the block's i-field (all tiles of the block, added to by its waves
+// on row changes) and each tile's j-field (added to per pair by the wave that walks the
 // tile).  Mixed precision: 64-bit fixed-point integers (fixq: 2^-38 e/A^2) added with integer
 // atomics, exact and independent of the order of the additions; FP64 mode adds FP64 values.
 template <bool FIX> struct LdsAcc;
@@ -1059,9 +1059,9 @@ void coef_release(amoeba_ctx* c)
     coef_invalidate(c);
 }
 
-// Called with the context stream synchronized: grows the store to the rows of the last mask
-// refresh (read back with that synchronization) plus an eighth, or to what the workspace cap
-// leaves.  A store smaller than the rows is still used: the tiles beyond it evaluate their
+// Grows the store to the rows of the last mask refresh (posted with the flags that the host has just
+// waited for) plus an eighth, or to what the workspace cap leaves.  Kernels may still run on the stream
+// (the next refresh, which does not use the store): freeing the old one waits for them.  A store smaller than the rows is still used: the tiles beyond it evaluate their
 // coefficients.
 int coef_reserve(amoeba_ctx* c)
 {
